@@ -56,6 +56,7 @@ constexpr int SR_WAVES = SR_THREADS / 64;
 constexpr int SR_PER_THREAD = 16;
 constexpr int SR_CHUNK = SR_THREADS * SR_PER_THREAD;  // 8192 elements
 constexpr int SR_BINS = 4096;
+constexpr uint32_t SR_INF_BIN = 0x7f800000u >> 19;   // leading 12 key bits of infinity
 constexpr int SR_REPL = 4;    // copies of a global histogram (fewer same-address atomics)
 constexpr int64_t SR_SAMPLE = 1 << 19;
 constexpr int SR_COARSE = 1024, SR_FINE = 1 << 19;  // upper 10 and all of 19 low key bits (18 of
@@ -292,7 +293,9 @@ __device__ __forceinline__ uint32_t pick_b_lo(const int32_t* __restrict__ hist, 
   const int64_t want = rate == 1 ? k : (int64_t)(1.06 * share + 8.0 * sqrt(share) + 8.0);
   int bin;
   int32_t above;
-  return pick_bin(hist, want, &bin, &above) ? (uint32_t)bin : 0u;
+  // at most the bin of infinity: the bins above it hold NaN keys only, and a NaN is no bound that a
+  // finite residual could be compared with
+  return pick_bin(hist, want, &bin, &above) ? min((uint32_t)bin, SR_INF_BIN) : 0u;
 }
 
 // ---- step 2.

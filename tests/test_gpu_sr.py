@@ -100,6 +100,45 @@ def test_sample_that_misjudges_the_matrix():
     moe.moe_destroy(ctx)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,k,n_nan,n_inf", [
+    (4096, 2048, 2500, 0),       # the k-th largest key is a NaN's, fewer than k residuals are not NaN
+    (4096, 2048, 1500, 0),       # all NaN kept, the k-th largest is finite
+    (4096, 2048, 1500, 700),     # the k-th largest is an infinity
+    (4096, 4096, 4000, 0),       # everything kept
+    (300000, 2000, 290000, 0),   # more equal keys than the list of candidates holds
+    (2097152, 40000, 41000, 0),  # a sample of every fourth 128-byte piece decides
+])
+def test_nan_and_infinite_residuals(dtype, n, k, n_nan, n_inf):
+    """The order is that of the 31 low bits of the float32 residual: a NaN is above an infinity and
+    NaNs are ordered by payload.  Every one of the k entries is written."""
+    rng = np.random.default_rng(n + k + n_nan)
+    shared = wl.store(rng.standard_normal(n).astype(np.float32), dtype)
+    expert = wl.store(rng.standard_normal(n).astype(np.float32), dtype)
+    at = rng.permutation(n)
+    quiet = rng.integers(0x7fc0, 0x8000, n_nan).astype(np.uint32) | (rng.integers(0, 2, n_nan).astype(np.uint32) << 15)
+    inf = np.uint32(0x7f80) | (rng.integers(0, 2, n_inf).astype(np.uint32) << 15)
+    for where, bits in ((at[:n_nan], quiet), (at[n_nan:n_nan + n_inf], inf)):
+        expert[where] = bits.astype(np.uint16) if dtype == "bf16" else (bits << 16).view(np.float32)
+    ctx = _ctx(dtype)
+    dS, dW = to_device(shared, dtype), to_device(expert, dtype)
+    vals = torch.zeros(k, dtype=dS.dtype, device=dS.device)
+    idx = torch.full((k,), -1, dtype=torch.int32, device=dS.device)
+    moe.moe_sr_encode(ctx, dW, dS, k, vals, idx)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        res = sr.residual(expert, shared, dtype)
+    key = (res.view(np.uint32) & 0x7fffffff).astype(np.int64)
+    want = np.sort(np.lexsort((np.arange(n), -key))[:k])
+    assert np.array_equal(idx.cpu().numpy(), want)
+    got = to_host_bits(vals)
+    ok = ~np.isnan(res[want])
+    assert np.array_equal(got[ok], sr.to_storage(res[want][ok], dtype).view(got.dtype))
+    as_f32 = sr.bf16_to_f32(got) if dtype == "bf16" else got.view(np.float32)
+    assert np.all(np.isnan(as_f32[~ok]))
+    moe.moe_destroy(ctx)
+
+
 def wl_keep(shape):
     return sr.keep_count(shape[0] * shape[1], 50)
 
