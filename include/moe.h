@@ -335,7 +335,8 @@ int moe_route_bwd(moe_ctx* ctx, const void* x, const void* Wg, const float* logi
  * difference of the stored values; equal magnitudes: lower index first), ordered by
  * ascending index; values = that difference rounded to dtype.  1 <= k <= n.  Exact
  * (radix select), deterministic.  Uses a workspace in the context that grows with the
- * largest n seen (the growing call allocates and synchronises the device).
+ * largest n seen (about 8 bytes for every 6 elements; the growing call allocates and synchronises
+ * the device).
  *
  * moe_sr_decode: shared [dev][n] in, values/indices [dev][k] in (indices ascending, in
  * [0, n)), expert_out [dev][n] out (16-byte aligned, must not alias shared):

@@ -261,7 +261,10 @@ int moe_sr_encode(moe_ctx* c, const void* expert, const void* shared, int64_t n,
       (void)hipGetLastError();
       return MOE_ENOMEM;
     }
-    if (hipMemset(c->d_sr_ws, 0, need * sizeof(int32_t)) != hipSuccess) return MOE_EHIP;
+    // on the caller's stream, so that the encode is ordered behind it (a fill on the null stream is
+    // not: the caller's stream need not wait for that one)
+    const int st = launch_sr_clear(c->d_sr_ws, (hipStream_t)stream);
+    if (st != MOE_OK) return st;
     c->sr_ws_ints = need;
   }
   return launch_sr_encode(c, expert, shared, n, k, values, indices, (hipStream_t)stream);

@@ -177,6 +177,7 @@ int launch_route_bwd(moe_ctx* c, const void* x, const void* Wg, const float* log
                      const int32_t* topk_idx, const float* topk_w, const float* dtopk_w, int T,
                      float* dlogits, float* dWg, float* dbias, void* dx, hipStream_t s);
 size_t sr_workspace_ints(int64_t n);
+int launch_sr_clear(int32_t* ws, hipStream_t s);   // a new workspace, before its first encode
 int launch_sr_encode(moe_ctx* c, const void* W, const void* S, int64_t n, int64_t k, void* values,
                      int32_t* indices, hipStream_t s);
 int launch_sr_decode(moe_ctx* c, const void* S, const void* values, const int32_t* indices,

@@ -855,6 +855,14 @@ __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
   }
 }
 
+// A new workspace: state and histograms are zero on entry of every encode (its last launch leaves them
+// so).  The rest is written before it is read.
+__global__ __launch_bounds__(SR_THREADS) void sr_clear_kernel(int4* __restrict__ ws) {
+  static_assert((SR_STATE_INTS + SR_HIST_INTS) % 4 == 0, "cleared 16 bytes at a time");
+  const int i = blockIdx.x * SR_THREADS + threadIdx.x;
+  if (i < (SR_STATE_INTS + SR_HIST_INTS) / 4) ws[i] = make_int4(0, 0, 0, 0);
+}
+
 template <typename T>
 int encode_t(moe_ctx* c, const T* W, const T* S, int64_t n, int64_t k, T* values, int32_t* indices,
              hipStream_t s) {
@@ -898,6 +906,12 @@ size_t sr_workspace_ints(int64_t n) {
   const int64_t nc2 = (n_chunks + 3) & ~(int64_t)3;
   // state, histograms, four integers per chunk, the candidate list (8 bytes per entry)
   return (size_t)(SR_STATE_INTS + SR_HIST_INTS + 4 * nc2 + 2 * sr_list_cap(n));
+}
+
+int launch_sr_clear(int32_t* ws, hipStream_t s) {
+  const dim3 grid(((SR_STATE_INTS + SR_HIST_INTS) / 4 + SR_THREADS - 1) / SR_THREADS);
+  hipLaunchKernelGGL(sr_clear_kernel, grid, dim3(SR_THREADS), 0, s, reinterpret_cast<int4*>(ws));
+  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 
 int launch_sr_encode(moe_ctx* c, const void* W, const void* S, int64_t n, int64_t k, void* values,

@@ -164,6 +164,32 @@ def test_workspace_grows_and_calls_repeat():
     moe.moe_destroy(ctx)
 
 
+def test_new_workspace_on_a_side_stream():
+    """The first encode of a context on a stream that does not wait for the default stream, which is
+    busy meanwhile: what clears the new workspace has to come before the encode."""
+    shape = (1024, 2048)
+    k = sr.keep_count(shape[0] * shape[1], 50)
+    shared, experts = wl.make_sr_inputs(shape, 71, "bf16", n_experts=1)
+    ovals, oidx = sr.sr_encode(experts[0], shared, k, "bf16")
+    dS, dW = to_device(shared, "bf16"), to_device(experts[0], "bf16")
+    a = torch.randn(4096, 4096, device="cuda")
+    vals = torch.empty(k, dtype=dS.dtype, device="cuda")
+    idx = torch.empty(k, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+    a @ a                     # the library's first call
+    torch.cuda.synchronize()
+    for _ in range(3):        # later rounds: memory that an earlier context has used and given back
+        ctx = _ctx("bf16")
+        for _ in range(8):
+            a @ a
+        with torch.cuda.stream(side):
+            moe.moe_sr_encode(ctx, dW, dS, k, vals, idx)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy(), oidx)
+        assert np.array_equal(to_host_bits(vals), ovals)
+        moe.moe_destroy(ctx)
+
+
 def test_full_size_expert_matrix_sampled_properties():
     """One Mixtral-size matrix (14336 x 4096, CR = 50): the oracle's selection needs a sort of
     58.7 M keys (~10 s), so the check is by properties that hold at any size plus an exact
