@@ -48,6 +48,13 @@ def test_encode_decode_match_oracle(dtype, shape, k):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape,cr", [((2080, 2048), 12),   # 520 chunks: eight blocks read two of them
+                                      ((4160, 2048), 10)])  # 1040 chunks, the list almost three quarters full
+def test_chunks_that_do_not_divide_among_the_blocks(dtype, shape, cr):
+    _run(shape, 35, dtype, sr.keep_count(shape[0] * shape[1], cr))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_many_equal_magnitudes(dtype):
     # residuals quantised to a coarse grid: the threshold bin holds many equal keys and the
     # tie rule (lower index first) decides
