@@ -8,7 +8,9 @@
 // 128-byte line per weight row), and nothing is staged: a weight fragment is one 16-byte load per
 // lane, used for all of the expert's rows, and the wavefronts' sums meet in LDS (added in
 // wavefront order: deterministic).  No schedule launch, no partial sums in memory.  The token rows
-// come from L2 once per block, which is what limits the rows: see ffn_skinny_wanted.
+// come from L2 once per block, which is what limits the rows: see few_rows.
+#include <algorithm>
+
 #include "moe_internal.h"
 #include "numeric.h"
 
@@ -185,8 +187,8 @@ int launch(const SkinnyArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Reading the token rows once per 16 weight rows costs more the more rows an expert has; what the
-// tiles cost depends on whether they fill the chip.  FFN call, tiles -> this kernel, us:
+// Reading the token rows once per 16 weight rows costs more the more rows there are; what the tiles
+// cost depends on whether they fill the chip.  FFN call, tiles -> this kernel, us, rows spread evenly:
 //   (S/E: rows per expert)
 //   fewer gate/up tiles than compute units (d = 1024, f = 4096, 4 experts): S/E = 1: 57.6 -> 28.7, 8: 59.9 -> 33.8, 25: 60.0 -> 44.1, 50: 58.6 -> 59.4;
 //   d = 2048, f = 1408, 16 experts: S/E = 6: 107 -> 80, 19: 107 -> 98, 37: 109 -> 124;
@@ -195,15 +197,36 @@ int launch(const SkinnyArgs& a, hipStream_t s) {
 //   ... and long rows, which the tiles stream at 4.5 to 5.1 TB/s (d = 4096, f = 14336, 8 experts):
 //   S/E = 0.25: 164 -> 150, 4: 564 -> 557, 8: 568 -> 619; d = 4096, f = 2048, 16 experts:
 //   S/E = 2: 162 -> 160, 8: 180 -> 188
-// With at most 256 tokens no expert takes more than four passes over its weights, however the
-// tokens fall.
+// The counts stay on the device, and tokens need not fall evenly.  At most T rows go to any expert and
+// T * min(k, resident) to all of them; their rows come through L2 d * f / 16 times each (4 bytes: once
+// for gate/up, once for down), at about 8 TB/s.  The tiles are slower by their schedule launch and the
+// K-split sums, 27 us or more at these sizes.  So the rows are held to 200 MB, and to one pass over the weights.  All
+// tokens on the same k experts, tiles -> this kernel, us, on both sides of that
+// line: d = f = 3072, two-matrix, k = 6: T = 8: 98 -> 55, 24: 100 -> 79, 48: 99 -> 121; d = 2048,
+// f = 1408, k = 6: T = 32: 67 -> 44, 48: 67 -> 57, 96: 66 -> 95; d = 2048, f = 14336, two-matrix, k = 2:
+// T = 8: 87 -> 63, 16: 88 -> 70, 32: 88 -> 94; d = 4096, f = 14336, k = 2: T = 4: 161 -> 138,
+// 8: 161 -> 147, 16: 162 -> 171; d = 1024, f = 4096, k = 2: T = 64: 48 -> 37, 96: 48 -> 56.  (By S/E
+// alone, with up to 256 tokens: T = 200 with popularity falling off as rank^-1.2, 64 experts of
+// d = f = 3072, k = 6: 135 -> 352; d = 2048, f = 14336, k = 2: 229 -> 529.)
+static bool few_rows(long long T, int d, int f, int E, int k, int n_res, bool gated, int n_cu) {
+  const int bn = gated ? 128 : 256;
+  const bool fills = (long long)n_res * ((f + bn - 1) / bn) >= n_cu;
+  const int most = !fills ? 24 : d < 4096 ? 8 : 4;   // rows per expert
+  const long long l2_bytes = T * std::min(k, n_res) * d * f / 4;
+  return T <= 16 * GROUPS && l2_bytes <= 200000000ll && T * k <= (long long)most * E;
+}
+
 bool ffn_skinny_wanted(const moe_ctx* c, bool gated) {
   int n_res = 0;
   for (int e = 0; e < c->cfg.E; ++e) n_res += c->h_wtab[0][e] != nullptr;
-  const int bn = gated ? 128 : 256;
-  const bool fills = (long long)n_res * ((c->cfg.f + bn - 1) / bn) >= c->n_cu;
-  const int most = !fills ? 24 : c->cfg.d < 4096 ? 8 : 4;   // rows per expert
-  return c->S_call <= 256 * c->cfg.k && c->S_call <= most * c->cfg.E;
+  return few_rows(c->S_call / c->cfg.k, c->cfg.d, c->cfg.f, c->cfg.E, c->cfg.k, n_res, gated, c->n_cu);
+}
+
+// Not part of the interface: the rule above, for tests (one that needs no GPU, and those that want to
+// know that they reach this kernel).
+extern "C" int moe_internal_ffn_few_rows(int32_t T, int32_t d, int32_t f, int32_t E, int32_t k, int32_t n_res,
+                                         int32_t gated, int32_t n_cu) {
+  return few_rows(T, d, f, E, k, n_res, gated != 0, n_cu) ? 1 : 0;
 }
 
 int launch_ffn_skinny(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,

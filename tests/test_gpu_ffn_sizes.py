@@ -78,9 +78,9 @@ def test_forward_and_backward_match_oracle(dtype, T, d, E, k, f, gated):
     (1, 8, 4, 2, 8, 0.0),          # a single chunk of the contraction, 8 of 16 weight rows
     (7, 72, 4, 2, 136, 0.6),       # a partial unit after a whole one
     (16, 520, 8, 2, 1032, 0.0),    # one unit for each wavefront and a partial one
-    (33, 2048, 8, 2, 4104, 3.0),   # several rounds of units; 33 rows of one expert
-    (150, 1160, 16, 2, 520, 0.6),  # 16, 32 and 64 rows a pass
-    (256, 320, 24, 2, 264, 4.0),   # four passes over an expert's weights
+    (33, 2048, 8, 2, 4104, 3.0),   # several rounds of units (two-matrix; the tiles serve the gated one)
+    (150, 1160, 16, 2, 520, 0.6),  # more tokens than one pass takes rows: the tiles
+    (256, 320, 24, 2, 264, 4.0),
     (2, 64, 256, 4, 64, 0.0),      # as many experts as there can be
 ])
 def test_few_rows_per_expert_match_oracle(T, d, E, k, f, skew, gated):
@@ -104,4 +104,41 @@ def test_few_rows_per_expert_match_oracle(T, d, E, k, f, skew, gated):
         yo, Go = orc.expert_ffn2(vals(xp_st, "bf16"), cnt, off, W1, W2)
     assert nerr(to_host_f32(G), Go) <= TOL["bf16"]
     assert nerr(to_host_f32(y), yo) <= TOL["bf16"]
+    lay.close()
+
+
+# rows: of each expert, given by hand; more rows on one expert than there are tokens need another pass
+# over its weights (no routing does that, a caller's counts may)
+@pytest.mark.parametrize("gated", [True, False])
+@pytest.mark.parametrize("T,d,E,k,f,rows", [
+    (16, 2048, 8, 2, 2056, [16, 1, 0, 15, 0, 0, 0, 0]),       # four units of the contraction in flight
+    (64, 2048, 8, 2, 1032, [17, 32, 33, 0, 16, 1, 29, 0]),    # 16, 32 and 64 rows a pass
+    (64, 1160, 8, 2, 520, [0, 63, 0, 65, 0, 0, 0, 0]),        # a second pass for one row
+    (64, 320, 8, 3, 264, [0, 0, 192, 0, 0, 0, 0, 0]),         # three whole passes
+])
+def test_few_rows_per_expert_by_given_counts(T, d, E, k, f, rows, gated):
+    from gpu_common import DEV, TOL, moe, nerr, vals, to_device, to_host_f32, layer_from_inputs, say
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert moe.load_library().moe_internal_ffn_few_rows(T, d, f, E, k, E, int(gated), n_cu)
+    say(f"[few rows, given] T={T} d={d} E={E} k={k} f={f} rows={rows} gated={gated}")
+    cfg = wl.MoEConfig("given", 5 + T + d, "bf16", T=T, d=d, E=E, k=k, f=f, R=1, gated=gated)
+    inp = wl.make_inputs(cfg)
+    lay = layer_from_inputs(inp)
+    cnt = np.array(rows, np.int32)
+    off = (np.cumsum(cnt) - cnt).astype(np.int32)
+    xp_st = wl.store(np.random.default_rng(d).standard_normal((T * k, d)).astype(np.float32), "bf16")
+    y0 = torch.full((T * k, d), 3.0, dtype=torch.bfloat16, device=DEV)
+    y, G, U = moe.moe_expert_ffn(lay.ctx, to_device(xp_st, "bf16"), torch.from_numpy(cnt).to(DEV),
+                                 torch.from_numpy(off).to(DEV), lay.W1, lay.W3, lay.W2, y_packed=y0, save=True)
+    torch.cuda.synchronize()
+    n = int(cnt.sum())
+    W1, W2 = _f64(inp.W1, "bf16"), _f64(inp.W2, "bf16")
+    if gated:
+        yo, Go, Uo = orc.expert_ffn(vals(xp_st, "bf16"), cnt, off, W1, _f64(inp.W3, "bf16"), W2)
+        assert nerr(to_host_f32(U)[:n], Uo[:n]) <= TOL["bf16"]
+    else:
+        yo, Go = orc.expert_ffn2(vals(xp_st, "bf16"), cnt, off, W1, W2)
+    assert nerr(to_host_f32(G)[:n], Go[:n]) <= TOL["bf16"]
+    assert nerr(to_host_f32(y)[:n], yo[:n]) <= TOL["bf16"]
+    assert torch.all(y[n:] == 3.0)      # rows of no expert are left alone
     lay.close()
