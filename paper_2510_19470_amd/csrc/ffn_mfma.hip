@@ -55,7 +55,19 @@ __device__ __forceinline__ int swz(int row) { return ((row >> 1) & 7) ^ ((row & 
 // the row or the two 32-byte column halves; their 16 chunks must differ modulo 16
 __device__ __forceinline__ int tr_swz(int row) { return ((row & 3) << 2) ^ (((row >> 3) & 1) << 1); }
 
-// tile list entry: (mtile index << 12) | column block
+// Parts that a tile of the down GEMM's tail is cut into (see mfma_sched_kernel).
+__host__ __device__ inline int split_parts(int tail, int n_cu, int kt_down) {
+  const int pairs = kt_down / 2;
+  int split = 1;
+  while (tail > 0 && split < 8 && tail * (split + 1) <= n_cu && pairs / (split + 1) >= 4) ++split;
+  return split;
+}
+// Most partial tiles there can be with at most `tiles` tiles: parts times tiles of the tail.
+size_t split_tiles_max(long long tiles, int n_cu, int kt_down) {
+  const int most = split_parts(1, 8, kt_down);   // parts with no limit from the tail
+  return most == 1 ? 0 : (size_t)std::min<long long>(n_cu, tiles * most);
+}
+
 __global__ __launch_bounds__(256) void mfma_sched_kernel(
     const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
     const void* const* __restrict__ present, int E, int S, int max_mtiles, int nt_up, int nt_down,
@@ -96,10 +108,7 @@ __global__ __launch_bounds__(256) void mfma_sched_kernel(
     // divide evenly; all parts together still one round), summed afterwards.
     const int total = total_m * nt_down;
     const int tail = total % n_cu;
-    const int pairs = kt_down / 2;
-    int split = 1;
-    while (tail > 0 && split < 8 && tail * (split + 1) <= n_cu && pairs / (split + 1) >= 4)
-      ++split;
+    const int split = split_parts(tail, n_cu, kt_down);
     sched->down_split = split;
     sched->down_split_tiles = split > 1 ? tail : 0;
     sched->down_full = split > 1 ? total - tail : total;
@@ -774,6 +783,20 @@ size_t ffn_mfma_order_entries(const moe_ctx* c) {
 
 // k-steps of a contraction of `segs` segments of `len` each (rounded up to an even number)
 static int k_steps(int len, int segs) { return (segs * ceil_div(len, BK) + 1) & ~1; }
+
+// dX of the gated expert has the longest contraction of the down-type GEMMs.
+size_t ffn_mfma_split_tiles(const moe_ctx* c) {
+  return split_tiles_max((long long)c->max_mtiles[1] * ceil_div(c->cfg.d, 256), c->n_cu, k_steps(c->cfg.f, 2));
+}
+
+// Not part of the interface, for the test of the bound above (needs no GPU): partial tiles of a launch
+// of `tiles` tiles, and the most there can be with up to `tiles_max`.
+extern "C" void moe_internal_split_tiles(int32_t tiles, int64_t tiles_max, int32_t n_cu, int32_t kt,
+                                         int32_t* used, int64_t* most) {
+  const int tail = tiles % n_cu, split = split_parts(tail, n_cu, kt);
+  *used = split > 1 ? tail * split : 0;
+  *most = (int64_t)split_tiles_max(tiles_max, n_cu, kt);
+}
 
 static int run_sched(moe_ctx* c, const int32_t* counts, const int32_t* offsets, int nt_a, int nt_b,
                      int kt_b, const void* const* up_b0, const void* const* up_b1,

@@ -11,26 +11,32 @@ namespace {
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// The small workspaces that a context has from the start are cut out of one allocation (or two: what
+// has to be zero at first, what need not): an allocation takes 1 to 8 us of moe_create each, a fill or
+// a copy some more.
+struct Cut {
+  void* p;        // the pointer to set, of any type
+  size_t bytes;
+};
 template <typename T>
-hipError_t dev_alloc(T** p, size_t n) {
-  return hipMalloc(reinterpret_cast<void**>(p), std::max<size_t>(n, 1) * sizeof(T));
+Cut cut(T** p, size_t n) {
+  return {p, (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256};
+}
+bool carve(void** base, const Cut* cuts, int n, bool zero) {
+  size_t bytes = 0;
+  for (int i = 0; i < n; ++i) bytes += cuts[i].bytes;
+  if (hipMalloc(base, bytes) != hipSuccess) return false;
+  char* at = static_cast<char*>(*base);
+  for (int i = 0; i < n; ++i) {
+    std::memcpy(cuts[i].p, &at, sizeof(at));
+    at += cuts[i].bytes;
+  }
+  return !zero || hipMemset(*base, 0, bytes) == hipSuccess;
 }
 
 void free_all(moe_ctx* c) {
-  (void)hipFree(c->d_dest_rank);
-  (void)hipFree(c->d_seg_pos);
-  (void)hipFree(c->d_chunk_hist);
-  (void)hipFree(c->d_totals);
-  (void)hipFree(c->d_rt_rank);
-  (void)hipFree(c->d_rt_hist);
-  (void)hipFree(c->d_rt_super);
-  (void)hipFree(c->d_wtab);
-  for (int i = 0; i < 2; ++i) {
-    (void)hipFree(c->d_sched[i]);
-    (void)hipFree(c->d_mtiles[i]);
-  }
-  (void)hipFree(c->d_order_up);
-  (void)hipFree(c->d_order_down);
+  (void)hipFree(c->d_fixed);
+  (void)hipFree(c->d_fixed_zero);
   (void)hipFree(c->d_split_ws);
   (void)hipFree(c->d_sr_ws);
   (void)hipFree(c->d_rbwd_ws);
@@ -38,7 +44,6 @@ void free_all(moe_ctx* c) {
   (void)hipFree(c->d_dG);
   (void)hipFree(c->d_dU);
   (void)hipFree(c->d_dGU);
-  (void)hipFree(c->d_zero);
 }
 
 int check_ctx_T(const moe_ctx* c, int32_t T) {
@@ -132,37 +137,33 @@ int moe_create(moe_ctx** out, const moe_config* cfg) {
   c->n_chunks_max = std::max<int>(1, (int)((S + DISPATCH_CHUNK - 1) / DISPATCH_CHUNK));
   c->max_mtiles[0] = (int)(S / GENERIC_BM) + E;
   c->max_mtiles[1] = (int)(S / MFMA_BM) + E;
-  bool ok = true;
-  ok = ok && dev_alloc(&c->d_dest_rank, E) == hipSuccess;
-  ok = ok && dev_alloc(&c->d_seg_pos, E) == hipSuccess;
-  ok = ok && dev_alloc(&c->d_chunk_hist, (size_t)c->n_chunks_max * E) == hipSuccess;
-  ok = ok && dev_alloc(&c->d_totals, 2 * MOE_MAX_EXPERTS + 2) == hipSuccess;
-  ok = ok && hipMalloc(&c->d_zero, 512) == hipSuccess && hipMemset(c->d_zero, 0, 512) == hipSuccess;
-  ok = ok && dev_alloc(&c->d_wtab, MOE_WTAB_ROWS * MOE_MAX_EXPERTS) == hipSuccess;
-  for (int i = 0; i < 2 && ok; ++i) {
-    ok = ok && dev_alloc(&c->d_sched[i], 1) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_mtiles[i], c->max_mtiles[i]) == hipSuccess;
-  }
-  if (ok && ffn_mfma_supported(c)) {
-    const size_t n = ffn_mfma_order_entries(c);
-    ok = ok && dev_alloc(&c->d_order_up, n) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_order_down, n) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_split_ws, (size_t)c->n_cu * MFMA_BM * 256) == hipSuccess;
-  }
   // side products of the gate kernel (moe_dispatch_routed); left out when the histograms would
   // be large
   const long long n_blk = ((long long)cfg->T_max + GATE_BLOCK_TOKENS - 1) / GATE_BLOCK_TOKENS;
-  if (ok && cfg->T_max <= (1 << 17) && n_blk * E <= (1 << 22)) {
-    c->rt_super_max = (int32_t)((n_blk + RT_SUPER - 1) / RT_SUPER);
-    const size_t n_sup = (size_t)2 * ((size_t)c->rt_super_max * E + (size_t)E * RT_TOT_STRIDE);
-    ok = ok && dev_alloc(&c->d_rt_rank, (size_t)S) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_rt_hist, (size_t)n_blk * E) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_rt_super, n_sup) == hipSuccess;
-    ok = ok && hipMemset(c->d_rt_super, 0, n_sup * sizeof(int32_t)) == hipSuccess;
-  }
+  const bool rt = cfg->T_max <= (1 << 17) && n_blk * E <= (1 << 22);
+  c->rt_super_max = rt ? (int32_t)((n_blk + RT_SUPER - 1) / RT_SUPER) : 0;
+  const size_t n_sup = (size_t)2 * ((size_t)c->rt_super_max * E + (size_t)E * RT_TOT_STRIDE);
+  const bool mfma = ffn_mfma_supported(c);
+  const size_t n_order = mfma ? ffn_mfma_order_entries(c) : 0;
+  const size_t n_split = mfma ? ffn_mfma_split_tiles(c) : 0;
+  // those that need not be zero; the last ones not everywhere
+  const Cut plain[] = {cut(&c->d_dest_rank, E), cut(&c->d_seg_pos, E),
+                       cut(&c->d_chunk_hist, (size_t)c->n_chunks_max * E), cut(&c->d_sched[0], 1),
+                       cut(&c->d_sched[1], 1), cut(&c->d_mtiles[0], c->max_mtiles[0]),
+                       cut(&c->d_mtiles[1], c->max_mtiles[1]), cut(&c->d_order_up, n_order),
+                       cut(&c->d_order_down, n_order), cut(&c->d_rt_rank, rt ? (size_t)S : 0),
+                       cut(&c->d_rt_hist, rt ? (size_t)n_blk * E : 0)};
+  const Cut zero[] = {cut(&c->d_totals, 2 * MOE_MAX_EXPERTS + 2),
+                      cut(&c->d_wtab, MOE_WTAB_ROWS * MOE_MAX_EXPERTS),
+                      cut(&c->d_zero, 512), cut(&c->d_rt_super, rt ? n_sup : 0)};
+  // (what ran before on the null stream is over when moe_set_placement's copies below are)
+  bool ok = carve(&c->d_fixed, plain, sizeof(plain) / sizeof(plain[0]), false) &&
+            carve(&c->d_fixed_zero, zero, sizeof(zero) / sizeof(zero[0]), true);
+  if (!mfma) c->d_order_up = c->d_order_down = nullptr;
+  if (!rt) c->d_rt_rank = c->d_rt_hist = c->d_rt_super = nullptr;
+  ok = ok && (n_split == 0 || hipMalloc(reinterpret_cast<void**>(&c->d_split_ws),
+                                        n_split * MFMA_BM * 256 * sizeof(float)) == hipSuccess);
   ok = ok && hipMalloc(&c->d_H, std::max<size_t>((size_t)S * cfg->f * c->elem, 16)) == hipSuccess;
-  ok = ok && hipMemset(c->d_totals, 0, sizeof(int32_t) * (2 * MOE_MAX_EXPERTS + 2)) == hipSuccess;
-  ok = ok && hipMemset(c->d_wtab, 0, sizeof(void*) * MOE_WTAB_ROWS * MOE_MAX_EXPERTS) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
     free_all(c);

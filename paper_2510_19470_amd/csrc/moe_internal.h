@@ -40,6 +40,8 @@ struct TileSched {
 #define MOE_WTAB_ROWS 6
 
 struct moe_ctx {
+  void* d_fixed;          // the allocations that the small workspaces below are parts of
+  void* d_fixed_zero;
   moe_config cfg;
   int device;
   int elem;               // bytes per stored element
@@ -80,15 +82,14 @@ struct moe_ctx {
   TileDesc* d_order_up;   // MFMA tile order of the gate/up GEMM
   TileDesc* d_order_down; // ... and of the down GEMM
   int n_cu;               // compute units of the device
-  float* d_split_ws;      // fp32 partial tiles of the K-split tail: [n_cu][256*256]
+  float* d_split_ws;      // fp32 partial tiles of the K-split tail, as many as there can be: x [256*256]
   int32_t S_max;          // T_max*k
   int32_t S_call;         // T*k of the expert-FFN call being launched: the rows its buffers hold
   void* d_H;              // [T_max*k][f]
   void* d_dG;             // [T_max*k][f]   (vector-ALU backward)
   void* d_dU;             // [T_max*k][f]
   void* d_dGU;            // [T_max*k][2f]  (MFMA backward: dG | dU)
-  void* d_zero;           // 512 bytes of zeros (what the bf16 GEMMs fetch past the end of a
-                          // contraction)
+  char* d_zero;           // 512 bytes of zeros (what the GEMMs fetch past the end of a contraction)
   // gate backward: per-chunk partial sums of dWg, [T_max/128][E][d] (first call allocates)
   float* d_rbwd_ws;
   // shared/residual compression: selection state, histogram, per-chunk counts
@@ -160,6 +161,7 @@ int launch_ffn_generic(moe_ctx* c, bool gated, const void* x_packed, void* y_pac
                        void* U, void* H_tmp, hipStream_t s);
 bool ffn_mfma_supported(const moe_ctx* c);
 size_t ffn_mfma_order_entries(const moe_ctx* c);
+size_t ffn_mfma_split_tiles(const moe_ctx* c);   // partial tiles of the K-split tail at most
 int launch_ffn_mfma(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
                     const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s);
 // bf16, few rows per expert (S_call rows in all): a kernel that streams the weights
