@@ -440,11 +440,66 @@ def test_backward_unwanted_weight_gradients(path):
     lay.close()
 
 
+@pytest.mark.parametrize("fault", ["beyond", "negative_count", "negative_offset"])
+@pytest.mark.parametrize("dtype,T,d,f,few", [
+    ("bf16", 16, 256, 256, True),     # the kernel for few rows per expert
+    ("bf16", 400, 264, 392, False),   # tiles that the sizes do not divide
+    ("f32", 300, 64, 96, False),      # the fp32 kernels, 32x32 tiles
+    ("f32", 4000, 512, 2048, False),  # ... 64x64
+])
+def test_inconsistent_counts_compute_nothing_in_the_other_kernels(dtype, T, d, f, few, fault):
+    """The same promise where it is kept by the kernels themselves (no tile schedule) and by the
+    kernels for sizes that no tile divides."""
+    from gpu_common import DEV, moe, to_device, layer_from_inputs
+    cfg = wl.scaled(wl.CONFIGS["train"], T=T, d=d, f=f, E=8, k=2, R=2, migrated=(5,), backward=True,
+                    dtype=dtype)
+    inp = wl.make_inputs(cfg)
+    lay = layer_from_inputs(inp)
+    if dtype == "bf16":
+        n_res = sum(w is not None for w in inp.W1)
+        n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+        assert bool(moe.load_library().moe_internal_ffn_few_rows(T, d, f, 8, 2, n_res, 1, n_cu)) == few
+    idx, w, _ = moe.moe_route(lay.ctx, to_device(inp.x, dtype), lay.Wg, lay.bias)
+    disp = moe.moe_dispatch(lay.ctx, to_device(inp.x, dtype), idx)
+    good = moe.moe_expert_ffn(lay.ctx, disp.x_packed, disp.expert_counts, disp.expert_offsets, lay.W1,
+                              lay.W3, lay.W2, save=True)
+    torch.cuda.synchronize()
+    cnt, off = disp.expert_counts.clone(), disp.expert_offsets.clone()
+    res = [e for e in range(8) if inp.W1[e] is not None]
+    e = max(res, key=lambda q: int(cnt[q].item()))
+    if fault == "beyond":
+        off[e] = cfg.S - int(cnt[e].item()) + 1
+    elif fault == "negative_count":
+        cnt[e] = -5
+    else:
+        off[e] = -1
+    like = lambda t, v: torch.full_like(t, v)
+    y, G, U = moe.moe_expert_ffn(lay.ctx, disp.x_packed, cnt, off, lay.W1, lay.W3, lay.W2,
+                                 y_packed=like(good[0], 3.0), G_save=like(good[1], 5.0),
+                                 U_save=like(good[2], 7.0), save=True)
+    dxp, dW1, dW3, dW2 = moe.moe_expert_ffn_bwd(lay.ctx, torch.ones_like(disp.x_packed), disp.x_packed,
+                                                good[1], good[2], cnt, off, lay.W1, lay.W3, lay.W2,
+                                                dx_packed=like(disp.x_packed, 9.0))
+    torch.cuda.synchronize()
+    assert torch.all(y == 3.0) and torch.all(G == 5.0) and torch.all(U == 7.0)
+    assert torch.all(dxp == 9.0)
+    assert all(g is None or torch.all(g == 0) for tab in (dW1, dW3, dW2) for g in tab)
+    # the right arrays again: bit-identical to the first call
+    again = moe.moe_expert_ffn(lay.ctx, disp.x_packed, disp.expert_counts, disp.expert_offsets, lay.W1,
+                               lay.W3, lay.W2, save=True)
+    torch.cuda.synchronize()
+    rows = torch.cat([torch.arange(int(disp.expert_offsets[q]), int(disp.expert_offsets[q] + disp.expert_counts[q]))
+                      for q in res]).to(DEV)
+    for a, b in zip(again, good):
+        assert torch.equal(a[rows], b[rows])
+    lay.close()
+
+
 # ------------------------------------------------------------------ two-matrix expert
 @pytest.mark.parametrize("path", ["mfma", "valu"])
 @pytest.mark.parametrize("dtype,T,d,E,k,f,skew", [
     ("bf16", 900, 512, 4, 2, 1024, 0.5),     # MFMA shapes (f % 256 == 0)
-    ("bf16", 515, 256, 6, 3, 384, 1.5),      # f % 256 != 0: vector-ALU kernels on both paths
+    ("bf16", 515, 256, 6, 3, 384, 1.5),      # tiles that f does not divide
     ("f32", 300, 128, 8, 2, 256, 0.0),
     ("bf16", 8192, 1024, 32, 2, 4096, 0.0),  # a shape of the paper's Table 3 (H=1024, M=4096, K=2)
 ])
@@ -486,7 +541,7 @@ def test_two_matrix_expert_forward(path, dtype, T, d, E, k, f, skew):
 @pytest.mark.parametrize("path", ["mfma", "valu"])
 @pytest.mark.parametrize("dtype,T,d,E,k,f,skew", [
     ("bf16", 900, 512, 4, 2, 1024, 0.5),     # MFMA shapes (f % 256 == 0)
-    ("bf16", 515, 256, 6, 3, 384, 1.5),      # f % 256 != 0: vector-ALU kernels on both paths
+    ("bf16", 515, 256, 6, 3, 384, 1.5),      # tiles that f does not divide
     ("bf16", 300, 512, 16, 1, 256, 2.5),     # experts without tokens
     ("f32", 300, 128, 8, 2, 256, 0.0),
 ])

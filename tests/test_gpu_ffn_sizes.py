@@ -26,7 +26,7 @@ def _f64(ws, dtype):
     ("f32", 50, 8, 4, 2, 8),            # one partial contraction step, 32x32 tiles
     ("f32", 515, 136, 6, 3, 264),
     ("f32", 900, 72, 80, 2, 520),       # more experts than a wavefront has lanes
-    ("f32", 8000, 200, 3, 2, 1032),     # 64x64 tiles (in dX the 32x32 ones), all sides ragged
+    ("f32", 8000, 200, 3, 2, 1032),     # 64x64 tiles, all sides ragged
 ])
 def test_forward_and_backward_match_oracle(dtype, T, d, E, k, f, gated):
     from gpu_common import DEV, TOL, moe, nerr, vals, to_device, to_host_f32, layer_from_inputs, say

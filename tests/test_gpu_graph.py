@@ -89,3 +89,64 @@ def test_captured_step_replays_bit_identically(gated, d_model):
             assert torch.equal(g_, w_), (rep, i)
         assert int(disp.expert_counts.sum().item()) == S
     lay.close()
+
+
+@pytest.mark.parametrize("gated", [True, False])
+def test_captured_decoding_pass_replays_bit_identically(gated):
+    """The forward pass of a few tokens: under capture the kernel for few rows per expert looks at
+    every expert (a replay runs on the tables of its time), not at the resident ones only."""
+    from gpu_common import DEV, moe, say, to_device, layer_from_inputs
+    cfg = wl.scaled(wl.CONFIGS["small"], T=16, d=1024, f=1408, E=16, k=2, R=4, migrated=(5, 14), gated=gated)
+    inp = wl.make_inputs(cfg, experts="resident")
+    res = [e for e in range(cfg.E) if inp.W1[e] is not None]
+    assert 0 < len(res) < cfg.E
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert moe.load_library().moe_internal_ffn_few_rows(cfg.T, cfg.d, cfg.f, cfg.E, cfg.k, len(res),
+                                                        int(gated), n_cu)
+    say(f"[graph, few rows] T={cfg.T} d={cfg.d} E={cfg.E} k={cfg.k} f={cfg.f} resident={res} gated={gated}")
+    lay = layer_from_inputs(inp)
+    T, k, d, E, R, S = cfg.T, cfg.k, cfg.d, cfg.E, cfg.R, cfg.S
+    bf, i32 = torch.bfloat16, dict(dtype=torch.int32, device=DEV)
+    x = to_device(inp.x, "bf16").clone()
+    idx, w = torch.empty((T, k), **i32), torch.empty((T, k), dtype=torch.float32, device=DEV)
+    y, out = torch.zeros((S, d), dtype=bf, device=DEV), torch.empty((T, d), dtype=bf, device=DEV)
+    disp = moe.binding.DispatchOut()
+    disp.x_packed = torch.empty((S, d), dtype=bf, device=DEV)
+    disp.slot_to_row, disp.row_to_slot = torch.empty(S, **i32), torch.empty(S, **i32)
+    disp.expert_counts, disp.expert_offsets = torch.empty(E, **i32), torch.empty(E, **i32)
+    disp.rank_counts, disp.rank_offsets = torch.empty(R, **i32), torch.empty(R + 1, **i32)
+
+    def step():
+        moe.moe_route(lay.ctx, x, lay.Wg, lay.bias, topk_idx=idx, topk_w=w)
+        moe.moe_dispatch(lay.ctx, x, idx, out=disp)
+        moe.moe_expert_ffn(lay.ctx, disp.x_packed, disp.expert_counts, disp.expert_offsets, lay.W1,
+                           lay.W3 if gated else None, lay.W2, y_packed=y)
+        moe.moe_combine(lay.ctx, y, disp.slot_to_row, w, out=out)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for _ in range(2):
+            step()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    torch.cuda.synchronize()
+    gen = torch.Generator(device=DEV).manual_seed(17)
+    for rep in range(4):
+        x.copy_(torch.randn(x.shape, device=DEV, generator=gen).to(bf))
+        y.zero_()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in (idx, w, disp.slot_to_row, disp.expert_counts, y, out)]
+        y.zero_()
+        out.zero_()
+        step()
+        torch.cuda.synchronize()
+        for i, (a, b) in enumerate(zip(got, (idx, w, disp.slot_to_row, disp.expert_counts, y, out))):
+            assert torch.equal(a, b), (rep, i)
+        assert float(out.float().abs().max()) > 0
+    lay.close()

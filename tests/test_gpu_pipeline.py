@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
     (1000, 3, 2, "bf16", True),     # ragged last chunk
     (1000, 1, 1, "bf16", True),     # one chunk = the plain path
     (8, 4, 2, "bf16", True),        # two empty chunks
-    (700, 5, 3, "f32", True),       # fp32 storage, vector-ALU kernels
+    (700, 5, 3, "f32", True),       # fp32 storage and its kernels
     (1024, 4, 2, "bf16", False),    # two-matrix expert
 ])
 def test_pipeline_matches_oracle(T, n_chunks, n_streams, dtype, gated):
