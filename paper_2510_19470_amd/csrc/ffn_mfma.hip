@@ -632,9 +632,9 @@ __global__ __launch_bounds__(NT) void ffn_mfma_kernel(const GemmArgs p) {
         for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
   };
 
-  // Every unit has an even number of k-steps (K is a multiple of 128 and the K-split keeps
-  // its parts even).  KT == 0 cannot come out of the schedule (K >= 128); should it ever,
-  // nothing is loaded and zeros are stored.
+  // Every unit has an even number of k-steps (the steps of a tile are rounded up to one and the
+  // K-split keeps its parts even).  KT == 0 cannot come out of the schedule (K >= 8); should it
+  // ever, nothing is loaded and zeros are stored.
   if (cur.KT == 0) {
     zero_acc();
     epilogue(cur);
@@ -770,7 +770,9 @@ __global__ __launch_bounds__(NT) void ffn_split_reduce_kernel(const GemmArgs p) 
 
 }  // namespace
 
-// bf16 storage: every size the boundary takes (multiples of 8) has a tiled kernel.
+// bf16 storage: the tiled kernels take every size the boundary takes (multiples of 8) as long as the
+// 32-bit byte offsets inside a tile (255 rows of 2f or of d elements) stay far below their limit; the
+// vector-ALU kernels serve longer rows.
 bool ffn_mfma_supported(const moe_ctx* c) {
   return c->cfg.dtype == MOE_BF16 && c->cfg.f <= 128 * 4095 && c->cfg.d <= 256 * 4095;
 }

@@ -292,11 +292,11 @@ int ffn_generic_t(moe_ctx* c, bool gated, const void* xp, void* y, void* G, void
   const void* const* W3 = gated ? c->d_wtab + 1 * MOE_MAX_EXPERTS : nullptr;
   const void* const* W2 = c->d_wtab + 2 * MOE_MAX_EXPERTS;
   hipLaunchKernelGGL((ffn_gate_up_kernel<T>), dim3(mtiles, (f + BN - 1) / BN), dim3(256), 0, s,
-                     (const T*)xp, c->d_sched[0], c->d_mtiles[0], W1, W3, d, f, (T*)H, (T*)G,
+                     (const T*)xp, c->d_sched[0], c->d_mtiles, W1, W3, d, f, (T*)H, (T*)G,
                      (T*)U);
   prof_mark(c, 2, s);
   hipLaunchKernelGGL((ffn_down_kernel<T>), dim3(mtiles, (d + BN - 1) / BN), dim3(256), 0, s,
-                     (const T*)H, c->d_sched[0], c->d_mtiles[0], W2, d, f, (T*)y);
+                     (const T*)H, c->d_sched[0], c->d_mtiles, W2, d, f, (T*)y);
   prof_mark(c, 3, s);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
@@ -315,9 +315,9 @@ int ffn_bwd_generic_t(moe_ctx* c, bool gated, const void* dy, const void* xp, co
   const void* const* dW2 = c->d_wtab + 5 * MOE_MAX_EXPERTS;
   hipLaunchKernelGGL((ffn_bwd_dh_kernel<T>), dim3(mtiles, (f + BN - 1) / BN), dim3(256), 0, s,
                      (const T*)dy, (const T*)G, gated ? (const T*)U : nullptr, c->d_sched[0],
-                     c->d_mtiles[0], W2, d, f, (T*)dG, (T*)dU, (T*)H);
+                     c->d_mtiles, W2, d, f, (T*)dG, (T*)dU, (T*)H);
   hipLaunchKernelGGL((ffn_bwd_dx_kernel<T>), dim3(mtiles, (d + BN - 1) / BN), dim3(256), 0, s,
-                     (const T*)dG, (const T*)dU, c->d_sched[0], c->d_mtiles[0], W1, W3, d, f,
+                     (const T*)dG, (const T*)dU, c->d_sched[0], c->d_mtiles, W1, W3, d, f,
                      (T*)dxp);
   const dim3 g_df((f + BN - 1) / BN, (d + BM - 1) / BM, E);  // output [d,f]
   const dim3 g_fd((d + BN - 1) / BN, (f + BM - 1) / BM, E);  // output [f,d]
@@ -333,12 +333,11 @@ int ffn_bwd_generic_t(moe_ctx* c, bool gated, const void* dy, const void* xp, co
 
 }  // namespace
 
-int launch_build_sched(moe_ctx* c, const int32_t* counts, const int32_t* offsets, int which,
+int launch_build_sched(moe_ctx* c, const int32_t* counts, const int32_t* offsets,
                        hipStream_t s) {
-  const int bm = which == 0 ? GENERIC_BM : MFMA_BM;
   hipLaunchKernelGGL(build_sched_kernel, dim3(1), dim3(256), 0, s, counts, offsets,
-                     c->d_wtab + 0 * MOE_MAX_EXPERTS, c->cfg.E, c->S_call, bm, c->max_mtiles[which],
-                     c->d_sched[which], c->d_mtiles[which]);
+                     c->d_wtab + 0 * MOE_MAX_EXPERTS, c->cfg.E, c->S_call, GENERIC_BM, c->max_mtiles[0],
+                     c->d_sched[0], c->d_mtiles);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 

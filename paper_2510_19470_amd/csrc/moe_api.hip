@@ -149,9 +149,9 @@ int moe_create(moe_ctx** out, const moe_config* cfg) {
   // those that need not be zero; the last ones not everywhere
   const Cut plain[] = {cut(&c->d_dest_rank, E), cut(&c->d_seg_pos, E),
                        cut(&c->d_chunk_hist, (size_t)c->n_chunks_max * E), cut(&c->d_sched[0], 1),
-                       cut(&c->d_sched[1], 1), cut(&c->d_mtiles[0], c->max_mtiles[0]),
-                       cut(&c->d_mtiles[1], c->max_mtiles[1]), cut(&c->d_order_up, n_order),
-                       cut(&c->d_order_down, n_order), cut(&c->d_rt_rank, rt ? (size_t)S : 0),
+                       cut(&c->d_sched[1], 1), cut(&c->d_mtiles, c->max_mtiles[0]),
+                       cut(&c->d_order_up, n_order), cut(&c->d_order_down, n_order),
+                       cut(&c->d_rt_rank, rt ? (size_t)S : 0),
                        cut(&c->d_rt_hist, rt ? (size_t)n_blk * E : 0)};
   const Cut zero[] = {cut(&c->d_totals, 2 * MOE_MAX_EXPERTS + 2),
                       cut(&c->d_wtab, MOE_WTAB_ROWS * MOE_MAX_EXPERTS),
@@ -433,7 +433,7 @@ int moe_expert_ffn(moe_ctx* c, const void* x_packed, const int32_t* expert_count
     st = launch_ffn_f32(c, gated, expert_counts, expert_offsets, x_packed, y_packed, G_save, U_save, s);
   } else {
     prof_mark(c, 0, s);
-    st = launch_build_sched(c, expert_counts, expert_offsets, 0, s);
+    st = launch_build_sched(c, expert_counts, expert_offsets, s);
     if (st != MOE_OK) return st;
     prof_mark(c, 1, s);
     st = launch_ffn_generic(c, gated, x_packed, y_packed, G_save, U_save, c->d_H, s);
@@ -529,7 +529,7 @@ int moe_expert_ffn_bwd(moe_ctx* c, const void* dy_packed, const void* x_packed, 
   if (c->ffn_path == MOE_FFN_AUTO && c->cfg.dtype == MOE_F32)
     return launch_ffn_bwd_f32(c, gated, dy_packed, x_packed, G_save, U_save, expert_counts,
                               expert_offsets, dx_packed, c->d_dG, c->d_dU, c->d_H, s);
-  st = launch_build_sched(c, expert_counts, expert_offsets, 0, s);
+  st = launch_build_sched(c, expert_counts, expert_offsets, s);
   if (st != MOE_OK) return st;
   return launch_ffn_bwd_generic(c, gated, dy_packed, x_packed, G_save, U_save, expert_counts,
                                 expert_offsets, dx_packed, c->d_dG, c->d_dU, c->d_H, s);

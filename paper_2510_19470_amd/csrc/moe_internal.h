@@ -75,7 +75,7 @@ struct moe_ctx {
   int wtab_valid;
   // grouped GEMM schedules: [0] 64-row tiles (vector ALU path), [1] 256-row tiles (MFMA)
   TileSched* d_sched[2];
-  MTile* d_mtiles[2];
+  MTile* d_mtiles;        // vector ALU path: the row blocks
   int32_t max_mtiles[2];
   // activations between the two GEMMs, and the backward's temporaries (allocated on the
   // first backward call)
@@ -150,8 +150,7 @@ int launch_combine_bwd(const moe_ctx* c, const void* dout, const void* y_packed,
                        float* dw, hipStream_t s);
 int launch_dispatch_bwd(const moe_ctx* c, const void* dx_packed, const int32_t* slot_to_row, int T,
                         void* dx, hipStream_t s);
-int launch_build_sched(moe_ctx* c, const int32_t* counts, const int32_t* offsets, int which,
-                       hipStream_t s);
+int launch_build_sched(moe_ctx* c, const int32_t* counts, const int32_t* offsets, hipStream_t s);
 int launch_ffn_f32(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
                    const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s);
 int launch_ffn_bwd_f32(moe_ctx* c, bool gated, const void* dy, const void* xp, const void* G,
