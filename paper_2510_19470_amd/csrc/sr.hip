@@ -38,12 +38,12 @@
 // last launch (which otherwise only clears the histograms) emits.
 // The output never depends on the sample; it is deterministic (integer atomics only).
 //
-// What bounds it, n = 14336 x 4096 bf16: the pass over both matrices (235 MB).  Encode 157 -> 97 us against the version
-// that streamed both matrices twice (histogram, then list) and picked bins in one-block launches;
-// of it the pass takes 59 us (4.0 TB/s; 50 us with non-temporal loads, which the next reader of
-// the shared expert pays back), the five short launches 4.6-12 us each.  Decode 60 -> 46 us (5.1
-// TB/s): the shared expert is requested before the search, 1 KB per load instruction, and the LDS
-// of a block went from 40 to 17 KB.
+// What bounds it, n = 14336 x 4096 bf16: the pass over both matrices (235 MB).  Encode 157 -> 95 us
+// against the version that streamed both matrices twice (histogram, then list) and picked bins in
+// one-block launches (matrices not in the last-level cache); of it the pass takes 59 us (4.0 TB/s; 50 us
+// with non-temporal loads, which the next reader of the shared expert pays back), the five short
+// launches 4.6-12 us each.  Decode 60 -> 46 us (5.1 TB/s): the shared expert is requested before the
+// search, 1 KB per load instruction, and the LDS of a block went from 40 to 17 KB.
 #include "moe_internal.h"
 #include "numeric.h"
 
