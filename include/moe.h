@@ -77,8 +77,8 @@ const char* moe_strerror(int status);
  * dest_rank[e] = e / ceil(E/R).  *out is NULL on error.  The workspace, with S = T_max*k:
  * H [S, f] in dtype between the two GEMMs of the FFN (the largest part: 470 MB at T_max =
  * 8192, k = 2, f = 14336, bf16); up to 64 MB of fp32 partial tiles for contraction-split GEMM
- * tiles (bf16, as many as T_max, E and the sizes allow); the tile lists (32 bytes per 256-row block and column block);
- * S/1024 * E + O(E) integers for the dispatch.  The first moe_expert_ffn_bwd adds [S, 2f] in
+ * tiles (bf16, as many as T_max, E and the sizes allow); the tile lists (32 bytes per 256-row
+ * block and column block); S/1024 * E + O(E) integers for the dispatch.  The first moe_expert_ffn_bwd adds [S, 2f] in
  * dtype, the first moe_route_bwd that wants dWg ceil(T_max/128) * E * d floats.
  * MOE_EUNSUPPORTED: S > 2^22. */
 int moe_create(moe_ctx** out, const moe_config* cfg);
