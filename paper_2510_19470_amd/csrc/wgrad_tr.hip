@@ -16,12 +16,26 @@
 // such reads give the 8 consecutive k of one MFMA operand register pair.
 //
 // Block tile 256 (m) x 256 (n), 8 wavefronts (2 along m x 4 along n), wavefront tile 128 x 64
-// = 4 x 2 accumulators of v_mfma_f32_32x32x16_bf16, as in the forward kernels.  The k-loop
-// runs in half-steps of 32 token rows through 4 LDS stages of 32 KB (P tile 16 KB + Q tile
-// 16 KB); the copies of half-step h+3 are issued when half-step h starts.  16-byte chunks of
-// a row are XOR-swizzled (tr_swz below), which puts the rows x 32 bytes that the groups of 16
-// lanes sharing an LDS cycle read on distinct banks.  Rows past the end of the expert's segment are fetched
-// from a row of zeros, so a ragged segment needs no padded copy.
+// = 4 x 2 accumulators of v_mfma_f32_32x32x16_bf16, as in the forward kernels.  The contraction
+// runs in slices of 16 token rows through a ring of 8 LDS slots of 16 KB (P 8 KB + Q 8 KB), seven
+// slices ahead.  The two groups of four wavefronts (wm) alternate as in the forward kernel: while
+// one multiplies a slice (8 MFMAs), the other reads its 12 fragments of the next one and issues two
+// copies.  16-byte chunks of a row are XOR-swizzled (tr_swz below), which puts the rows x 32 bytes
+// that the groups of 16 lanes sharing an LDS cycle read on distinct banks.  Rows past the end of the
+// expert's segment are fetched from a row of zeros, so a ragged segment needs no padded copy.
+//
+// What bounds it.  The P columns are the MFMA "A" operand and the Q columns the "B" operand: a
+// lane holds one column of dW, and a store instruction writes two whole 128-byte lines.  (The other
+// way round, 16 bytes per lane spread over 32 rows, it writes 32-byte pieces of 32 lines: the same
+// loop takes 223 us instead of 204.)  The loop takes about 0.5 us per slice and neither its
+// instruction order nor the tile decides that any more: the operand copies alone take 0.25 us, MFMAs
+// and LDS reads without copies 0.42 us, and registers-only MFMAs on random operands 0.34 us (the
+// clock falls under the power limit).  6190 rows, 6 experts, d = f = 2048: 234 -> 203 us (1.5e11
+// flop, 302 MB written); 21000 rows, 12 experts, 2048 x 1408: 515 -> 475; 1500 rows, 6 experts, 1160
+// x 2888: 99 -> 91, against the loop of 32-row half-steps with one barrier each.  Within 3 % of it:
+// all reads of the next slice between the MFMAs of this one, one barrier a slice (207); 256 x 128
+// tiles with two blocks on a compute unit (204 to 209); persistent blocks that copy on across tiles
+// (208).
 #include "moe_internal.h"
 
 namespace {
@@ -33,10 +47,10 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 
 constexpr int NT = 512;
-constexpr int HK = 32;                 // token rows per half-step
-constexpr int STAGES = 4;
-constexpr int TILE_BYTES = HK * 512;   // one operand tile of a stage
-constexpr int STAGE_BYTES = 2 * TILE_BYTES;
+constexpr int HK = 16;                 // token rows per slice
+constexpr int SLOTS = 8;
+constexpr int TILE_BYTES = HK * 512;   // one operand tile of a slot
+constexpr int SLOT_BYTES = 2 * TILE_BYTES;
 
 struct WgradArgs {
   struct Job {
@@ -63,20 +77,29 @@ struct WgradArgs {
 // modulo 16: bits 2-3 of the chunk take j4, bit 1 takes hh (cb sits in bit 1 already).
 __device__ __forceinline__ int tr_swz(int row) { return ((row & 3) << 2) ^ (((row >> 3) & 1) << 1); }
 
-// 16 bytes per lane global -> LDS, per-lane 64-bit address; the wavefront's 1 KB lands at
-// lds_addr (wave-uniform, via M0) + lane * 16.
+// 16 bytes per lane global -> LDS; the wavefront's 1 KB lands at lds_addr (wave-uniform, via M0) +
+// lane * 16.  A 64-bit address per lane, or a wave-uniform base and 32 bits per lane.
 __device__ __forceinline__ void dma16v(const void* src, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr)
                : "memory", "m0");
 }
+__device__ __forceinline__ void dma16(uint32_t off, const char* base, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
+               : "memory", "m0");
+}
+
+// A pointer that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ const char* uniform_ptr(const char* q) {
+  const uint64_t v = (uint64_t)q;
+  return (const char*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+}
 
 // RAG: some last block is not whole (d or f no multiple of 256): columns are clamped and guarded.
-// A kernel of its own, so that whole sizes pay nothing for it: with the lane's clamped chunk computed
-// once, outside the copies, they took 228 us against 219 without a clamp (6100 rows, 6 experts, d = f
-// = 2048); this kernel 234 against 237, on a slower card.
+// A kernel of its own, so that whole sizes do not pay for the guards of the stores.
 template <bool RAG>
 __global__ __launch_bounds__(NT) void wgrad_tr_kernel(const WgradArgs p) {
-  __shared__ uint4 lds[STAGES * STAGE_BYTES / 16];
+  __shared__ uint4 lds[SLOTS * SLOT_BYTES / 16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
@@ -105,7 +128,7 @@ __global__ __launch_bounds__(NT) void wgrad_tr_kernel(const WgradArgs p) {
   // against the buffer size (no tiles at all if any segment does not fit: zeros come out)
   const int n_e = p.sched->n_mtiles > 0 ? p.counts[e] : 0;
   const int row0 = p.offsets[e];
-  const int NH = (n_e + HK - 1) / HK;
+  const int NS = (n_e + HK - 1) / HK;   // slices
 
   f32x16 acc[2][4];
 #pragma unroll
@@ -117,109 +140,108 @@ __global__ __launch_bounds__(NT) void wgrad_tr_kernel(const WgradArgs p) {
 
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
 
-  // ---- copies: instruction c (0..15) of a tile fills rows 2c (lanes 0-31) and 2c+1 (lanes
-  // 32-63), 32 chunk slots each; slot s of row r holds global chunk s ^ tr_swz(r).
-  // Wavefront w issues instructions w and w + 8 of the P tile and of the Q tile.
-  const int c_row = lane >> 5, c_slot = lane & 31;
-  const char* p_col = (const char*)(J.P + J.p_col0 + mblk * 256);
-  const char* q_col = (const char*)(J.Q + nblk * 256);
-  auto issue = [&](int h) {   // all copies of half-step h (rows past the segment: zeros)
-    const uint32_t sb = lds_base + (uint32_t)(h & (STAGES - 1)) * STAGE_BYTES;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = wave + 8 * u;
-      const int r = 2 * c + c_row;                     // row inside the stage
-      const int rg = h * HK + r;                       // row inside the expert's segment
-      const int gch = c_slot ^ tr_swz(r);              // global chunk this lane fetches
-      // ... held inside the matrix (multiples of 8 columns) in a last block that is not whole:
-      // what it repeats is not stored
-      const int gp = RAG ? min(gch, (J.Mo - mblk * 256) / 8 - 1) : gch;
-      const int gq = RAG ? min(gch, (J.No - nblk * 256) / 8 - 1) : gch;
-      const bool ok = rg < n_e;
-      const size_t rr = (size_t)(row0 + min(rg, n_e - 1));   // in bounds also when not used
-      const char* zp = (const char*)p.zero_row + gch * 16;
-      const char* pa = p_col + rr * J.p_pitch * 2 + gp * 16;
-      const char* qa = q_col + rr * J.q_pitch * 2 + gq * 16;
-      dma16v(ok ? pa : zp, sb + c * 1024);
-      dma16v(ok ? qa : zp, sb + TILE_BYTES + c * 1024);
+  // ---- copies: wavefront w fills rows 2w (lanes 0-31) and 2w+1 (lanes 32-63) of both operand
+  // tiles of a slice, 32 chunk slots each; slot c of row r holds global chunk c ^ tr_swz(r)
+  const int c_row = 2 * wave + (lane >> 5);
+  const int gch = (lane & 31) ^ tr_swz(c_row);
+  // ... held inside the matrix (multiples of 8 columns) in a last block that is not whole: what it
+  // repeats is not stored
+  const int gp = RAG ? min(gch, (J.Mo - mblk * 256) / 8 - 1) : gch;
+  const int gq = RAG ? min(gch, (J.No - nblk * 256) / 8 - 1) : gch;
+  const uint32_t p_pitch = J.p_pitch * 2, q_pitch = J.q_pitch * 2;
+  const uint32_t p_off = c_row * p_pitch + gp * 16, q_off = c_row * q_pitch + gq * 16;
+  const char* p_base = uniform_ptr((const char*)(J.P + J.p_col0 + mblk * 256) + (size_t)row0 * p_pitch);
+  const char* q_base = uniform_ptr((const char*)(J.Q + nblk * 256) + (size_t)row0 * q_pitch);
+  const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_base + wave * 1024);
+  const char* zp = (const char*)p.zero_row;
+  int left = n_e;        // rows from the next slice to copy on (negative: all of it are zeros)
+  uint32_t cslot = 0;    // byte offset of its slot
+  auto issue = [&]() {
+    if (left >= HK) {
+      dma16(p_off, p_base, dst + cslot);
+      dma16(q_off, q_base, dst + cslot + TILE_BYTES);
+    } else {
+      const bool ok = c_row < left;
+      dma16v(ok ? p_base + p_off : zp, dst + cslot);
+      dma16v(ok ? q_base + q_off : zp, dst + cslot + TILE_BYTES);
     }
+    p_base += HK * p_pitch;
+    q_base += HK * q_pitch;
+    left -= HK;
+    cslot = (cslot + SLOT_BYTES) & (SLOTS * SLOT_BYTES - 1);
   };
 
-  // ---- transpose reads: per-lane byte offsets inside an operand tile
+  // ---- transpose reads: LDS byte addresses of the lane's 4 columns in slot 0
   const int g16 = lane >> 4, hh = g16 >> 1, cb = g16 & 1;
   const int s16 = lane & 15, j4 = s16 >> 2, q4 = s16 & 3;
-  const int rd_row = 8 * hh + j4;                 // + 16 * kk + 4 * t
-  const int rd_swz = tr_swz(rd_row);              // + 16 * kk + 4 * t leaves the swizzle unchanged
-  const int rd_half = (q4 & 1) * 8;
-  int x_chunk[4], w_chunk[2];                     // chunk of the lane's 4 columns, before the swizzle
+  const int rd_row = 8 * hh + j4;                 // and + 4: the swizzle is the same
+  const int rd_swz = tr_swz(rd_row);
+  const uint32_t rd0 = lds_base + rd_row * 512 + (q4 & 1) * 8;
+  uint32_t x_adr[4], w_adr[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) x_chunk[i] = (wm * 128 + i * 32 + cb * 16) / 8 + (q4 >> 1);
+  for (int i = 0; i < 4; ++i)
+    x_adr[i] = rd0 + ((((wm * 128 + i * 32 + cb * 16) / 8 + (q4 >> 1)) ^ rd_swz) << 4);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) w_chunk[j] = (j * 128 + wn * 32 + cb * 16) / 8 + (q4 >> 1);
-  auto frag = [&](uint32_t tile_base, int kk, int chunk) -> bf16x8 {
-    const uint32_t a0 = tile_base + (uint32_t)(rd_row + 16 * kk) * 512 +
-                        (uint32_t)((chunk ^ rd_swz) << 4) + rd_half;
+  for (int j = 0; j < 2; ++j)
+    w_adr[j] = rd0 + TILE_BYTES + ((((wn * 64 + j * 32 + cb * 16) / 8 + (q4 >> 1)) ^ rd_swz) << 4);
+  auto frag = [&](uint32_t a0) -> bf16x8 {
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)a0);
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(a0 + 4 * 512));
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
 
-  if (NH > 0) {
-    issue(0);
-    issue(1);
-    issue(2);
-    for (int h = 0; h < NH; ++h) {
-      // half-step h has landed for this wavefront (the copies of h+1 and h+2, 8 instructions,
-      // may still be in flight) and, after the barrier, for everybody; everybody has also
-      // finished reading half-step h-1, whose stage takes half-step h+3
-      asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
-      issue(h + 3);
-      const uint32_t sb = (uint32_t)(h & (STAGES - 1)) * STAGE_BYTES;   // LDS offsets from 0: generic
-      const uint32_t pt = lds_base + sb, qt = lds_base + sb + TILE_BYTES;
-      // all 12 fragments of the half-step first (24 transpose reads in flight), then the 16
-      // MFMAs: the other wavefront of the SIMD computes meanwhile (one barrier per half-step
-      // lets the wavefronts drift apart; a strict two-group ping-pong with two barriers per
-      // half-step measured 13 % slower)
-      bf16x8 xa[2][4], wb[2][2];
+  if (NS > 0) {
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
+    for (int h = 0; h < SLOTS - 1; ++h) issue();
+    // slice 0 has landed; then the second group falls one barrier behind
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (SLOTS - 2)) : "memory");
+    if (wm == 1) asm volatile("s_barrier" ::: "memory");
+    uint32_t sb = 0;
+    for (int s = 0; s < NS; ++s) {
+      bf16x8 xa[4], wb[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) wb[kk][j] = frag(qt, kk, w_chunk[j]);
+      for (int j = 0; j < 2; ++j) wb[j] = frag(w_adr[j] + sb);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) xa[kk][i] = frag(pt, kk, x_chunk[i]);
-      }
+      for (int i = 0; i < 4; ++i) xa[i] = frag(x_adr[i] + sb);
+      // Slice s + 7 goes to the slot of slice s - 1: the other group's reads of it ended before the
+      // last barrier, at which every wavefront's reads were done (lgkmcnt below).
+      issue();
+      sb = (sb + SLOT_BYTES) & (SLOTS * SLOT_BYTES - 1);
+      // All but the last 12 copies have landed: those of slices s + 2 .. s + 7.  Every wavefront
+      // has passed this point of step s before anybody reads slice s + 1.
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * (SLOTS - 2)) : "memory");
       __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb[kk][j], xa[kk][i], acc[j][i], 0, 0, 0);
+        for (int i = 0; i < 4; ++i)
+          acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i], wb[j], acc[j][i], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy in flight into LDS at exit
+    if (wm == 0) asm volatile("s_barrier" ::: "memory");   // as many barriers as the other group
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no copy in flight into LDS at exit
   }
 
-  // ---- epilogue: lane holds row (lane & 31) of each 32-row block and the columns
-  // 8g + 4(lane >> 5) + {0..3} of each 32-column block
-  const int fr_row = lane & 31, fr_half = lane >> 5;
+  // ---- epilogue: lane holds column (lane & 31) of each 32-column block and the rows
+  // 8g + 4(lane >> 5) + {0..3} of each 32-row block
+  const int col = lane & 31, half = lane >> 5;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = mblk * 256 + wm * 128 + i * 32 + fr_row;
-    float* orow = dW + (size_t)m * J.No;
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col0 = nblk * 256 + j * 128 + wn * 32 + 4 * fr_half;
+    for (int g = 0; g < 4; ++g)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        if (!RAG || (m < J.Mo && col0 + 8 * g < J.No))
-          *reinterpret_cast<float4*>(orow + col0 + 8 * g) =
-              make_float4(acc[j][i][g * 4], acc[j][i][g * 4 + 1], acc[j][i][g * 4 + 2],
-                          acc[j][i][g * 4 + 3]);
-    }
-  }
+      for (int r = 0; r < 4; ++r) {
+        const int m = mblk * 256 + wm * 128 + i * 32 + 8 * g + 4 * half + r;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int n = nblk * 256 + wn * 64 + j * 32 + col;
+          if (!RAG || (m < J.Mo && n < J.No)) dW[(size_t)m * J.No + n] = acc[j][i][g * 4 + r];
+        }
+      }
 }
 
 }  // namespace

@@ -1,0 +1,65 @@
+"""GPU parity of the bf16 expert FFN, forward and backward, for given rows per expert: the edges of the
+16-row slices and the ring of seven that the weight gradients run ahead, and of the row blocks."""
+import numpy as np
+import pytest
+import torch
+
+import moe_workloads as wl
+from oracle import moe_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _f64(ws):
+    return [None if w is None else wl.stored_to_f32(w, "bf16").astype(np.float64) for w in ws]
+
+
+@pytest.mark.parametrize("gated", [True, False])
+@pytest.mark.parametrize("d,f,rows", [
+    (512, 256, [1, 0, 15, 16, 17, 31, 32, 33]),        # whole tiles of the weight gradients
+    (264, 520, [63, 64, 65, 0, 96, 97, 1, 2]),         # every last block 8 columns wide
+    (256, 1032, [111, 112, 113, 127, 128, 129, 0, 5]), # one more and one less than the ring holds
+    (1160, 264, [257, 0, 255, 256, 0, 385, 0, 17]),
+])
+def test_given_rows_match_oracle(d, f, rows, gated):
+    from gpu_common import DEV, TOL, moe, nerr, vals, to_device, to_host_f32, layer_from_inputs, say
+    say(f"[row edges] d={d} f={f} rows={rows} gated={gated}")
+    E, k = len(rows), 2
+    cnt = np.array(rows, np.int32)
+    T = -(-int(cnt.sum()) // k)
+    cfg = wl.MoEConfig("rows", 3 + d + f, "bf16", T=T, d=d, E=E, k=k, f=f, R=1, gated=gated)
+    inp = wl.make_inputs(cfg)
+    lay = layer_from_inputs(inp)
+    off = (np.cumsum(cnt) - cnt).astype(np.int32)
+    n = int(cnt.sum())
+    rng = np.random.default_rng(d)
+    xp_st = wl.store(rng.standard_normal((T * k, d)).astype(np.float32), "bf16")
+    dy_st = wl.store(rng.standard_normal((T * k, d)).astype(np.float32), "bf16")
+    xp, dy = to_device(xp_st, "bf16"), to_device(dy_st, "bf16")
+    cnt_d, off_d = torch.from_numpy(cnt).to(DEV), torch.from_numpy(off).to(DEV)
+    y, G, U = moe.moe_expert_ffn(lay.ctx, xp, cnt_d, off_d, lay.W1, lay.W3, lay.W2, save=True)
+    dxp, dW1, dW3, dW2 = moe.moe_expert_ffn_bwd(lay.ctx, dy, xp, G, U, cnt_d, off_d, lay.W1,
+                                                lay.W3, lay.W2)
+    torch.cuda.synchronize()
+    W1, W2 = _f64(inp.W1), _f64(inp.W2)
+    xv, dyv = vals(xp_st, "bf16"), vals(dy_st, "bf16")
+    # the backward from the GPU's saves, which are checked themselves
+    Gg = to_host_f32(G).astype(np.float64)
+    if gated:
+        W3 = _f64(inp.W3)
+        yo, Go, Uo = orc.expert_ffn(xv, cnt, off, W1, W3, W2)
+        Ug = to_host_f32(U).astype(np.float64)
+        assert nerr(Ug[:n], Uo[:n]) <= TOL["bf16"]
+        dxo, g1, g3, g2 = orc.expert_ffn_bwd(dyv, xv, Gg, Ug, cnt, off, W1, W3, W2)
+    else:
+        yo, Go = orc.expert_ffn2(xv, cnt, off, W1, W2)
+        dxo, g1, g2 = orc.expert_ffn2_bwd(dyv, xv, Gg, cnt, off, W1, W2)
+        g3 = None
+    assert nerr(Gg[:n], Go[:n]) <= TOL["bf16"]
+    assert nerr(to_host_f32(y)[:n], yo[:n]) <= TOL["bf16"]
+    assert nerr(to_host_f32(dxp)[:n], dxo[:n]) <= TOL["bf16"]
+    # every expert by itself: a row too many or too few shows where there are few
+    for got, want in ((dW1, g1), (dW3, g3), (dW2, g2)):
+        for e in range(E if want is not None else 0):
+            assert nerr(got[e].cpu().numpy(), want[e]) <= TOL["bf16"], (e, rows[e])
+    lay.close()
