@@ -309,13 +309,18 @@ __device__ __forceinline__ Unit fetch_unit(const GemmArgs& p, int idx) {
 // One cluster pair of the main loop: memory cluster of token block I in stage S (fragment
 // reads; two copies, base + offset each, into the rows read one cluster ago), then the
 // compute cluster.
-template <int S, int I, bool BKM, bool RAG>
+//
+// na: token blocks of the copies' target that are copied at all (4 unless the target is lean, see
+// the kernel).  WAIT: copies that may be outstanding at the end of the memory cluster, or < 0: 3
+// where `strict`, else 6.
+template <int S, int I, bool BKM, bool RAG, int WAIT>
 __device__ __forceinline__ void pp_cluster(f32x16 (&acc)[2][4], bf16x8 (&wb)[2][4],
                                            const uint4* lds, const int (&fr_a)[4],
                                            const int (&fr_b)[2], int fr_half, int fr_swz,
                                            uint32_t offa, const Src& srca, uint32_t offb,
                                            const Src& srcb, uint32_t a_dst, uint32_t b_dst,
-                                           int nact, int lc, int brow, const char* zero) {
+                                           int nact, int na, bool strict, int lc, int brow,
+                                           const char* zero) {
   const uint4* As = lds + (2 * S) * STAGE_VEC;
   const uint4* Bs = lds + (2 * S + 1) * STAGE_VEC;
   bf16x8 xa[4];
@@ -349,15 +354,19 @@ __device__ __forceinline__ void pp_cluster(f32x16 (&acc)[2][4], bf16x8 (&wb)[2][
   }
   constexpr int blk = (I + 3) & 3;
   constexpr int st = I == 0 ? (S ^ 1) : S;
-  dma_step<RAG>(offa, srca, a_dst + st * 65536 + blk * 4096, 8, lc, zero);
+  if (WAIT == 6 || blk < na) dma_step<RAG>(offa, srca, a_dst + st * 65536 + blk * 4096, 8, lc, zero);
   dma_step<RAG>(offb, srcb, b_dst + st * 65536 + blk * 8192, BKM ? BK : 8,
                 BKM ? brow + 16 * blk : lc, zero);
   // My fragment reads are done (the rows may be refilled after the next barrier) and all
-  // but my last 6 vector-memory operations have completed: the data read in cluster n
-  // was copied in clusters <= n-4, and every wavefront passes this point in cluster n-1
-  // before anybody reads in cluster n.  (Stores of an epilogue count as well and only
-  // make the wait stricter: copies complete in issue order among themselves.)
-  asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  // but my last 6 (3) vector-memory operations have completed: with two copies a cluster (at
+  // least one) the data read in cluster n was copied in clusters <= n-4 and every wavefront
+  // passes this point in cluster n-1 before anybody reads in cluster n.  (Stores of an epilogue
+  // count as well and only make the wait stricter: copies complete in issue order among
+  // themselves.)
+  if (WAIT == 6) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
+  else if (WAIT == 3 || strict) asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
+  asm volatile("s_barrier" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_setprio(1);
   if (act) {
@@ -482,16 +491,28 @@ __global__ __launch_bounds__(NT) void ffn_mfma_kernel(const GemmArgs p) {
 
   f32x16 acc[2][4];
 
+  // 32-row blocks of this wavefront's half of the unit that hold rows (wave-uniform).  A unit is
+  // lean for a wavefront with none or one: its other token blocks are not copied either, so that the
+  // last row block of an expert and the few rows of a decoding step do not move 32 KB of repeated
+  // rows per step beside 32 KB of weights (16 rows per expert, d = 4096, f = 14336: 592 -> 562 us the
+  // pass; 64 rows per expert, 1024 x 4096, training: 269 -> 248, of it the partial sums below half).
+  auto active = [&](const Unit& u) -> int {
+    return __builtin_amdgcn_readfirstlane(min(4, max(0, (u.rows - wm * 128 + 31) >> 5)));
+  };
+
   // ---- epilogue of one unit: lane holds, per 32x32 accumulator, token row (lane&31) and
   // the weight rows 8*g + 4*(lane>>5) + {0..3}, g = 0..3
   auto epilogue = [&](const Unit& u) {
     if (MODE == MODE_DOWN && u.ws_unit >= 0) {
-      // partial sums of one K-split part, in accumulator order: [unit][j][i][quad][thread]
+      // partial sums of one K-split part, in accumulator order: [unit][j][i][quad][thread]; the
+      // 32-row blocks that hold rows
       float4* ws = reinterpret_cast<float4*>(p.split_ws) + (size_t)u.ws_unit * (32 * NT) + tid;
+      const int n_act = active(u);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int i = 0; i < 4; ++i)
+        if (i < n_act)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
           for (int q = 0; q < 4; ++q)
             ws[((j * 4 + i) * 4 + q) * NT] = make_float4(acc[j][i][q * 4], acc[j][i][q * 4 + 1],
@@ -664,29 +685,37 @@ __global__ __launch_bounds__(NT) void ffn_mfma_kernel(const GemmArgs p) {
     const Unit nxt = fetch_unit<MODE, BKM, RAG>(p, idx + 1);
     zero_acc();
     const int KT = cur.KT;
-    const int nact = __builtin_amdgcn_readfirstlane(min(4, max(0, (cur.rows - wm * 128 + 31) >> 5)));
+    const int nact = active(cur), nact_n = nxt.valid ? active(nxt) : nact;
+    const bool lean = nact <= 1, lean_n = nact_n <= 1;
     // steady part: steps 0 .. KT-3; what was read one cluster ago is refilled with the data
     // of its next use (token block i-1 and weight row blocks 8(i-1)+wave of this stage with
     // step k+2; at i == 0 block 3 of the other stage with step k+1)
-    for (int kt = 0; kt < KT - 2; kt += 2) {
-      const Src a1 = asrc(cur, kt + 1), a2 = asrc(cur, kt + 2), a3 = asrc(cur, kt + 3);
-#define PP(S, I, OA, BA, OB, BB, NA)                                                            \
-  pp_cluster<S, I, BKM, RAG>(acc, wb, lds, fr_a, fr_b, fr_half, fr_swz, OA, BA, OB, BB, a_dst,  \
-                             b_dst, NA, lc, brow, p.zero)
-      PP(0, 0, a_off[3], a1, b_off[3], bsrc(cur, kt + 1, 1), nact);
-      PP(0, 1, a_off[0], a2, b_off[0], bsrc(cur, kt + 2, 0), nact);
-      PP(0, 2, a_off[1], a2, b_off[1], bsrc(cur, kt + 2, 0), nact);
-      PP(0, 3, a_off[2], a2, b_off[2], bsrc(cur, kt + 2, 1), nact);
-      PP(1, 0, a_off[3], a2, b_off[3], bsrc(cur, kt + 2, 1), nact);
-      PP(1, 1, a_off[0], a3, b_off[0], bsrc(cur, kt + 3, 0), nact);
-      PP(1, 2, a_off[1], a3, b_off[1], bsrc(cur, kt + 3, 0), nact);
-      PP(1, 3, a_off[2], a3, b_off[2], bsrc(cur, kt + 3, 1), nact);
+#define PP(S, I, OA, BA, OB, BB, NA, NC, W)                                                      \
+  pp_cluster<S, I, BKM, RAG, W>(acc, wb, lds, fr_a, fr_b, fr_half, fr_swz, OA, BA, OB, BB,       \
+                                a_dst, b_dst, NA, NC, lean || lean_n, lc, brow, p.zero)
+#define STEADY(W)                                                                                \
+  for (int kt = 0; kt < KT - 2; kt += 2) {                                                       \
+    const Src a1 = asrc(cur, kt + 1), a2 = asrc(cur, kt + 2), a3 = asrc(cur, kt + 3);            \
+    PP(0, 0, a_off[3], a1, b_off[3], bsrc(cur, kt + 1, 1), nact, nact, W);                       \
+    PP(0, 1, a_off[0], a2, b_off[0], bsrc(cur, kt + 2, 0), nact, nact, W);                       \
+    PP(0, 2, a_off[1], a2, b_off[1], bsrc(cur, kt + 2, 0), nact, nact, W);                       \
+    PP(0, 3, a_off[2], a2, b_off[2], bsrc(cur, kt + 2, 1), nact, nact, W);                       \
+    PP(1, 0, a_off[3], a2, b_off[3], bsrc(cur, kt + 2, 1), nact, nact, W);                       \
+    PP(1, 1, a_off[0], a3, b_off[0], bsrc(cur, kt + 3, 0), nact, nact, W);                       \
+    PP(1, 2, a_off[1], a3, b_off[1], bsrc(cur, kt + 3, 0), nact, nact, W);                       \
+    PP(1, 3, a_off[2], a3, b_off[2], bsrc(cur, kt + 3, 1), nact, nact, W);                       \
+  }
+    if (lean) {
+      STEADY(3)
+    } else {
+      STEADY(6)
     }
     // last two steps: the refills fetch steps 0 and 1 of the next unit (the token offsets
     // are switched block by block, each right after its last use for this unit).  Without a
-    // next unit the last step is fetched again (in bounds, never read): the copy count per
-    // cluster stays fixed, which the vmcnt arithmetic relies on.
+    // next unit the last step is fetched again (in bounds, never read): at least one copy per
+    // cluster, which the vmcnt arithmetic relies on.
     {
+      const int nc = lean ? nact : 4, nn = lean_n ? nact_n : 4;   // token blocks of this and the next unit
       const Src last = asrc(cur, KT - 1);
       const Src na = nxt.valid ? asrc(nxt, 0) : last;                 // next unit's step 0
       const Src nb0 = nxt.valid ? bsrc(nxt, 0, 0) : bsrc(cur, KT - 1, 0);
@@ -696,7 +725,7 @@ __global__ __launch_bounds__(NT) void ffn_mfma_kernel(const GemmArgs p) {
       const Src nc1 = nxt.valid ? bsrc(nxt, 1, 1) : nb1;
       // RAG: a last step that only rounds the count up to even holds nothing but zeros
       const int nact1 = RAG && last.nv <= 0 ? 0 : nact;
-      PP(0, 0, a_off[3], last, b_off[3], bsrc(cur, KT - 1, 1), nact);
+      PP(0, 0, a_off[3], last, b_off[3], bsrc(cur, KT - 1, 1), nact, nc, -1);
       if (nxt.valid) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
@@ -704,17 +733,18 @@ __global__ __launch_bounds__(NT) void ffn_mfma_kernel(const GemmArgs p) {
           if (RAG) b_off[i] = weight_off(nxt.nblk, i);
         }
       }
-      PP(0, 1, a_off[0], na, b_off[0], nb0, nact);
-      PP(0, 2, a_off[1], na, b_off[1], nb0, nact);
-      PP(0, 3, a_off[2], na, b_off[2], nb1, nact);
+      PP(0, 1, a_off[0], na, b_off[0], nb0, nact, nn, -1);
+      PP(0, 2, a_off[1], na, b_off[1], nb0, nact, nn, -1);
+      PP(0, 3, a_off[2], na, b_off[2], nb1, nact, nn, -1);
       if (nxt.valid) {
         a_off[3] = token_off(nxt.rows, 3);
         if (RAG) b_off[3] = weight_off(nxt.nblk, 3);
       }
-      PP(1, 0, a_off[3], na, b_off[3], nb1, nact1);
-      PP(1, 1, a_off[0], ma, b_off[0], nc0, nact1);
-      PP(1, 2, a_off[1], ma, b_off[1], nc0, nact1);
-      PP(1, 3, a_off[2], ma, b_off[2], nc1, nact1);
+      PP(1, 0, a_off[3], na, b_off[3], nb1, nact1, nn, -1);
+      PP(1, 1, a_off[0], ma, b_off[0], nc0, nact1, nn, -1);
+      PP(1, 2, a_off[1], ma, b_off[1], nc0, nact1, nn, -1);
+      PP(1, 3, a_off[2], ma, b_off[2], nc1, nact1, nn, -1);
+#undef STEADY
 #undef PP
     }
     epilogue(cur);
@@ -740,6 +770,7 @@ __global__ __launch_bounds__(NT) void ffn_split_reduce_kernel(const GemmArgs p) 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 2, wn = wave & 3;
   const int fr_row = lane & 31, fr_half = lane >> 5;
+  if (wm * 128 + i * 32 >= tl.rows) return;   // no rows here: nothing was stored
   const float4* ws = reinterpret_cast<const float4*>(p.split_ws) +
                      (size_t)tile * split * (32 * NT) + (size_t)(ji * 4) * NT + tid;
   const int m_local = wm * 128 + i * 32 + fr_row;
