@@ -13,7 +13,7 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libmoe_hip.so")
 
 SOURCES = ["moe_api.hip", "route.hip", "dispatch.hip", "combine.hip", "gemm_generic.hip",
-           "ffn_mfma.hip", "ffn_skinny.hip", "wgrad_tr.hip", "gemm_f32.hip", "sr.hip", "route_bwd.hip", "pipeline.hip", "ceilings.hip",
+           "ffn_mfma.hip", "ffn_tile128.hip", "ffn_skinny.hip", "wgrad_tr.hip", "gemm_f32.hip", "sr.hip", "route_bwd.hip", "pipeline.hip", "ceilings.hip",
            "plan.cpp"]
 
 HIPCC_FLAGS = [

@@ -1,0 +1,506 @@
+// Grouped bf16 expert GEMMs in tiles of 128 token rows x 128 weight rows, for layers whose 256 x 256
+// tiles (ffn_mfma.hip) are about two rounds on the chip or less.  (Paper Sec. 2.1, 3.1: as there.)
+//
+// Such launches are bound by the time of one tile, whatever it holds, by compute units without one and
+// by the partial sums of the K-split that fills them.  A quarter of the tile divides the work finer,
+// and two blocks of 256 threads on a compute unit cover each other's start, waits and epilogue.  What it
+// costs is half as much work per byte copied into LDS: 32 KB per 2.1e6 multiply-adds, at the copy path's
+// 15 TB/s about 1000 TFLOP/s, which is why full chips keep the larger tile.
+//
+// 4 wavefronts (2 along rows x 2 along columns), wavefront tile 64 x 64 = 2 x 2 accumulators of
+// v_mfma_f32_32x32x16_bf16; k-steps of 64 through two LDS stages of 32 KB.  A step: wait for its copies,
+// read all 16 fragments, issue the copies of the step after the next into the same stage, 16 MFMAs.
+// (Three stages where at most 64 rows need 24 KB a step: no difference.)
+// 32-row blocks that hold no rows are neither copied nor multiplied.
+// No schedule launch: every block counts the tiles from the counts (one scan over the experts) and finds
+// its own by a search.  A contraction is cut into parts only where there are tiles for at most half of
+// the resident blocks; the parts' sums (fp32, existing rows only) are added by a second kernel in a
+// fixed order.
+#include <algorithm>
+
+#include "ffn_tile.h"
+
+namespace {
+
+constexpr int TM = 128;          // token rows per tile
+constexpr int TN = 128;          // weight rows per tile (gate/up: 64 of each matrix)
+constexpr int NT = 256;          // threads
+constexpr int OPERAND = TM * BK * 2;      // bytes of an operand's part of a stage
+constexpr int STAGE = 2 * OPERAND;
+constexpr int SPLIT_MAX = 8;     // parts of a contraction at most
+constexpr int SPLIT_STEPS = 4;   // k-steps of a part at least
+constexpr int ORDER_GROUP_M = 8; // row blocks per group of the tile order
+
+struct TileArgs {
+  GemmArgs g;
+  const int32_t *counts, *offsets;
+  const void* const* present;    // [E] experts with weights
+  const void* const* b0;         // [E] weight-role operand
+  const void* const* b1;         // [E] gate/up: W3; k-major: the second segment's (may be nullptr)
+  int E, S;
+  TileSched* status;             // n_mtiles for the kernels after this one: 0 if counts do not fit
+};
+
+// Row blocks of all experts, counted by every block for itself: start[e] is the first one of expert e.
+// Everything that a tile needs to know of its expert is loaded at once here (a block's start is a chain of
+// cold loads otherwise, 1 to 2 us each).
+struct TileMap {
+  int32_t start[MOE_MAX_EXPERTS + 1];
+  int32_t wave_sum[NT / 64];
+  int32_t rows[MOE_MAX_EXPERTS], row0[MOE_MAX_EXPERTS];
+  const void *b0[MOE_MAX_EXPERTS], *b1[MOE_MAX_EXPERTS];
+};
+// Called by all threads; returns the number of row blocks (0 when a segment of a present expert does not
+// lie inside the S rows of the buffers, or they are more than S rows can have).
+__device__ __forceinline__ int count_tiles(const TileArgs& p, TileMap& m) {
+  static_assert(NT == MOE_MAX_EXPERTS, "one expert per thread");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int mine = 0;
+  bool bad = false;
+  if (tid < p.E) {
+    const void* w = p.present[tid];
+    const int n = p.counts[tid], o = p.offsets[tid];
+    const void* b0 = p.b0[tid];
+    const void* b1 = p.b1 != nullptr ? p.b1[tid] : b0;
+    if (w != nullptr) {
+      bad = n < 0 || o < 0 || (long)o + n > (long)p.S;
+      mine = bad ? 0 : (n + TM - 1) / TM;
+    }
+    m.rows[tid] = n;
+    m.row0[tid] = o;
+    m.b0[tid] = b0;
+    m.b1[tid] = b1;
+  }
+  int incl = mine;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int v = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += v;
+  }
+  if (lane == 63) m.wave_sum[wave] = incl;
+  const int any_bad = __syncthreads_or(bad);
+  for (int w = 0; w < wave; ++w) incl += m.wave_sum[w];
+  m.start[tid + 1] = incl;
+  if (tid == 0) m.start[0] = 0;
+  __syncthreads();
+  const int total = __builtin_amdgcn_readfirstlane(m.start[MOE_MAX_EXPERTS]);
+  return any_bad || total > p.S / TM + p.E ? 0 : total;   // (segments that overlap)
+}
+
+// Parts of every contraction of a launch of `tiles` tiles on `slots` resident blocks.
+__host__ __device__ inline int parts_of(int tiles, int slots, int kt) {
+  int split = 1;
+  while (tiles > 0 && split < SPLIT_MAX && tiles * (split + 1) <= slots && kt / (split + 1) >= SPLIT_STEPS) ++split;
+  return split;
+}
+
+// One tile, or one part of its contraction (all fields wave-uniform).
+struct Unit128 {
+  int valid, expert, row0, rows, nblk;
+  int kstart, KT;          // first k-step and their number
+  int ws_unit;             // >= 0: index of the partial tile in the workspace
+};
+
+// Tile L of the order: expert by expert; inside an expert in groups of 8 row blocks; inside a group
+// column block by column block, the group's row blocks in a row (they share a weight panel).
+__device__ __forceinline__ Unit128 find_tile(const TileArgs& p, const TileMap& m, int L) {
+  Unit128 u;
+  const int nt = p.g.n_tiles_n;
+  int lo = 0, hi = p.E;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (m.start[mid] * nt <= L) lo = mid; else hi = mid;
+  }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  const int first = __builtin_amdgcn_readfirstlane(m.start[lo]);
+  const int me = __builtin_amdgcn_readfirstlane(m.start[lo + 1]) - first;
+  const int rel = L - first * nt, mg = rel / (ORDER_GROUP_M * nt), r2 = rel % (ORDER_GROUP_M * nt);
+  const int gm = min(ORDER_GROUP_M, me - mg * ORDER_GROUP_M);
+  const int mb = mg * ORDER_GROUP_M + r2 % gm;
+  u.valid = 1;
+  u.expert = lo;
+  u.nblk = r2 / gm;
+  u.row0 = __builtin_amdgcn_readfirstlane(m.row0[lo]) + mb * TM;
+  u.rows = min(TM, __builtin_amdgcn_readfirstlane(m.rows[lo]) - mb * TM);
+  u.kstart = 0;
+  u.KT = p.g.kt;
+  u.ws_unit = -1;
+  return u;
+}
+
+// MODE_UP .. MODE_DH1, BKM, and what happens at sizes that the tile does not divide: as
+// ffn_mfma_kernel's (here always its RAG form).
+template <int MODE, bool BKM>
+__global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
+  __shared__ uint4 lds[2 * STAGE / 16];
+  __shared__ TileMap map;
+  const GemmArgs& g = p.g;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int total = count_tiles(p, map) * g.n_tiles_n;
+  const int split = MODE == MODE_DOWN ? parts_of(total, gridDim.x, g.kt) : 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    p.status->n_mtiles = total;
+    p.status->down_split = split;
+    p.status->down_split_tiles = split > 1 ? total : 0;
+  }
+  const int units = total * split;
+  // The idx-th unit of this block: rounds of gridDim.x units, a round in 8 chunks of consecutive ones
+  // for the XCDs (blocks with index = x mod 8 are on XCD x), the last round in 8 equal chunks as well.
+  auto fetch = [&](int idx) -> Unit128 {
+    Unit128 u;
+    u.valid = 0;
+    const int G = (int)gridDim.x, x = blockIdx.x & 7, slot = (int)(blockIdx.x >> 3);
+    const int full = units / G, last = units - full * G, per_last = (last + 7) >> 3;
+    int U;
+    if (idx < full) U = idx * G + x * (G >> 3) + slot;
+    else if (idx == full && slot < per_last && x * per_last + slot < last) U = full * G + x * per_last + slot;
+    else return u;
+    u = find_tile(p, map, U / split);
+    if (split > 1) {
+      const int part = U % split, base = g.kt / split, rem = g.kt % split;
+      u.kstart = part * base + min(part, rem);
+      u.KT = base + (part < rem ? 1 : 0);
+      u.ws_unit = U;
+    }
+    return u;
+  };
+
+  // ---- copies.  Row-major operand: instruction c (0..15) fills rows 8c + (lane >> 3), 8 chunk slots
+  // each, slot s of row r holds chunk s ^ swz(r); k-major: k-rows 4c + (lane >> 4), 16 slots each, s ^
+  // tr_swz(r).  Wavefront w issues c = w + 4i: i is the 32-row block of the tokens.
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
+  const uint32_t a_pitch = g.lda * 2, b_pitch = BKM ? g.ldb * 2 : g.K * 2;
+  const int lc = (lane & 7) ^ swz(8 * wave + (lane >> 3));   // the lane's chunk of a row-major step
+  uint32_t a_off[4], b_off[4];
+  const char *a_base, *b_base0, *b_base1;
+  auto open = [&](const Unit128& u) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 8 * (wave + 4 * i) + (lane >> 3);
+      a_off[i] = (uint32_t)min(r, u.rows - 1) * a_pitch + lc * 16;
+      if (BKM) {
+        const int kr = 4 * (wave + 4 * i) + (lane >> 4);
+        b_off[i] = (uint32_t)kr * b_pitch + min((lane & 15) ^ tr_swz(kr), (g.N - u.nblk * TN) / 8 - 1) * 16;
+      } else if (MODE == MODE_UP) {   // i = 0, 1: rows of W1; 2, 3: the same rows of W3
+        b_off[i] = (uint32_t)min(r & 63, g.N - 1 - u.nblk * 64) * b_pitch + lc * 16;
+      } else {
+        b_off[i] = (uint32_t)min(r, g.N - 1 - u.nblk * TN) * b_pitch + lc * 16;
+      }
+    }
+    a_base = uniform_ptr(g.A + (size_t)u.row0 * g.lda);
+    const size_t ofs = BKM ? (size_t)u.nblk * (TN * 2)
+                           : (size_t)u.nblk * (MODE == MODE_UP ? 64 : TN) * b_pitch;
+    b_base0 = uniform_ptr((const char*)map.b0[u.expert] + ofs);
+    b_base1 = uniform_ptr((const char*)map.b1[u.expert] + ofs);
+  };
+  // copies of step t into stage t & 1: weight rows, then the token rows' na blocks
+  auto issue = [&](const Unit128& u, int na, int t) {
+    const int kg = u.kstart + t, kk = kg < g.kseg ? kg : kg - g.kseg;   // step inside its segment
+    const int kv = g.kseg_len - kk * BK;                                // k of the step that exist
+    const uint32_t dst = lds0 + (t & 1) * STAGE + wave * 1024;
+    const Src a = {a_base + (kg < g.kseg ? 0 : (size_t)g.kseg_len * 2) + kk * (BK * 2), kv >> 3};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < na) dma_step<true>(a_off[i], a, dst + OPERAND + i * 4096, 8, lc, g.zero);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      Src b;
+      if (BKM) b = {(kg < g.kseg ? b_base0 : b_base1) + (size_t)kk * BK * b_pitch, kv};
+      else b = {(MODE == MODE_UP && i >= 2 ? b_base1 : b_base0) + kk * (BK * 2), kv >> 3};
+      dma_step<true>(b_off[i], b, dst + i * 4096, BKM ? BK : 8,
+                     BKM ? 4 * (wave + 4 * i) + (lane >> 4) : lc, g.zero);
+    }
+  };
+
+  // ---- fragment reads
+  const int fr_row = lane & 31, fr_half = lane >> 5, fr_swz = swz(fr_row);
+  uint32_t tr_adr[2];   // k-major: LDS byte address of the lane's 4 columns, k-rows 0..3 of a slice
+  {
+    const int g16 = lane >> 4, j4 = (lane & 15) >> 2, q4 = lane & 3, row = 8 * (g16 >> 1) + j4;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      tr_adr[j] = lds0 + row * 256 + (q4 & 1) * 8 +
+                  ((((j * 64 + wn * 32 + (g16 & 1) * 16) / 8 + (q4 >> 1)) ^ tr_swz(row)) << 4);
+  }
+
+  Unit128 cur = fetch(0);
+  if (!cur.valid) return;
+  auto blocks = [](const Unit128& u) { return (u.rows + 31) >> 5; };   // 32-row blocks that hold rows
+  int na = blocks(cur);
+  auto start = [&](const Unit128& u, int blocks) {
+    open(u);
+    issue(u, blocks, 0);
+    if (u.KT > 1) issue(u, blocks, 1);
+  };
+  start(cur, na);
+  f32x16 acc[2][2];
+  for (int idx = 0;; ++idx) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+    const int mine = na - 2 * wm;   // of them this wavefront's
+    for (int t = 0; t < cur.KT; ++t) {
+      // step t has landed (the 4 + na copies of step t + 1, issued last, may be in flight)
+      if (t + 1 == cur.KT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      else if (na == 4) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      else if (na == 3) asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
+      else if (na == 2) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+      asm volatile("s_barrier" ::: "memory");
+      const uint4* Bs = lds + (t & 1) * (STAGE / 16);
+      const uint4* As = Bs + OPERAND / 16;
+      bf16x8 xa[2][4], wb[2][4];
+      if (mine > 0) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            if (BKM) {
+              const uint32_t a0 = tr_adr[j] + (t & 1) * STAGE + kk * 4096;
+              const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)a0);
+              const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(a0 + 4 * 256));
+              const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+              wb[j][kk] = __builtin_bit_cast(bf16x8, v);
+            } else {
+              wb[j][kk] = __builtin_bit_cast(bf16x8, Bs[(j * 64 + wn * 32 + fr_row) * 8 + ((kk * 2 + fr_half) ^ fr_swz)]);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (i < mine)
+              xa[i][kk] = __builtin_bit_cast(bf16x8, As[(wm * 64 + i * 32 + fr_row) * 8 + ((kk * 2 + fr_half) ^ fr_swz)]);
+        }
+      }
+      // everybody's reads are done: the stage is free
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (t + 2 < cur.KT) issue(cur, na, t + 2);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (i < mine) {
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb[j][kk], xa[i][kk], acc[j][i], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the next unit's first steps fly under this one's epilogue (nobody reads either stage any more)
+    const Unit128 nxt = fetch(idx + 1);
+    const int na_n = blocks(nxt);
+    if (nxt.valid) start(nxt, na_n);
+    if (MODE == MODE_DOWN && cur.ws_unit >= 0) {
+      // partial sums, [unit][i][j][quad][thread]; the 32-row blocks that hold rows
+      float4* ws = reinterpret_cast<float4*>(g.split_ws) + (size_t)cur.ws_unit * (16 * NT) + threadIdx.x;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (i < mine)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              ws[((i * 2 + j) * 4 + q) * NT] = make_float4(acc[j][i][q * 4], acc[j][i][q * 4 + 1],
+                                                           acc[j][i][q * 4 + 2], acc[j][i][q * 4 + 3]);
+    } else {
+      tile_epilogue<MODE, true, 2>(g, acc, cur.row0, cur.rows, cur.nblk, wm, wn, lane);
+    }
+    if (!nxt.valid) break;
+    cur = nxt;
+    na = na_n;
+  }
+}
+
+// Sums the parts of every tile in a fixed order (part 0, 1, ...: deterministic) and stores the tile like
+// the GEMM's own epilogue.  Four blocks per tile, one per accumulator (j, i); thread indices mean what
+// they mean there.
+__global__ __launch_bounds__(NT) void ffn_tile128_sum_kernel(const TileArgs p) {
+  __shared__ TileMap map;
+  const int split = p.status->down_split, tiles = p.status->down_split_tiles;
+  const int tile = blockIdx.x >> 2, ij = blockIdx.x & 3;
+  if (tile >= tiles) return;
+  count_tiles(p, map);
+  const Unit128 u = find_tile(p, map, tile);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1, i = ij >> 1, j = ij & 1;
+  if (wm * 64 + i * 32 >= u.rows) return;   // no rows here: nothing was stored
+  const float4* ws = reinterpret_cast<const float4*>(p.g.split_ws) + (size_t)tile * split * (16 * NT) +
+                     (size_t)ij * 4 * NT + threadIdx.x;
+  float4 part[4][SPLIT_MAX];   // all requested before anything is added
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int t = 0; t < SPLIT_MAX; ++t)
+      part[q][t] = t < split ? ws[(size_t)t * (16 * NT) + q * NT] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const int m_local = wm * 64 + i * 32 + (lane & 31);
+  const size_t row = (size_t)(u.row0 + m_local);
+  const int col0 = u.nblk * TN + j * 64 + wn * 32 + 4 * (lane >> 5);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float4 v = part[q][0];
+#pragma unroll
+    for (int t = 1; t < SPLIT_MAX; ++t) {
+      v.x += part[q][t].x; v.y += part[q][t].y; v.z += part[q][t].z; v.w += part[q][t].w;
+    }
+    if (m_local < u.rows && col0 + 8 * q < p.g.N)
+      *reinterpret_cast<uint2*>(p.g.C + row * p.g.N + col0 + 8 * q) =
+          make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+  }
+}
+
+int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// A GEMM: A [rows, lda], contraction of `segs` segments of `seg_len`, N output columns in blocks of bn
+// (ldb: row length of a k-major weight-role operand, else 0).
+TileArgs tile_args(const moe_ctx* c, const int32_t* counts, const int32_t* offsets, const void* A, int lda,
+                   int bn, int seg_len, int segs, int ldb, int N, void* C, int w0, int w1) {
+  TileArgs a{};
+  a.g.A = (const uint16_t*)A;
+  a.g.lda = lda;
+  a.g.n_tiles_n = ceil_div(N, bn);
+  a.g.K = seg_len * segs;
+  a.g.N = N;
+  a.g.C = (uint16_t*)C;
+  a.g.ldb = ldb;
+  a.g.kseg = ceil_div(seg_len, BK);
+  a.g.kt = segs * a.g.kseg;
+  a.g.kseg_len = seg_len;
+  a.g.zero = (const char*)c->d_zero;
+  a.g.split_ws = c->d_split_ws;
+  a.counts = counts;
+  a.offsets = offsets;
+  a.present = c->d_wtab;
+  a.b0 = c->d_wtab + w0 * MOE_MAX_EXPERTS;
+  a.b1 = w1 >= 0 ? c->d_wtab + w1 * MOE_MAX_EXPERTS : nullptr;
+  a.E = c->cfg.E;
+  a.S = c->S_call;
+  a.status = c->d_sched[1];
+  return a;
+}
+
+int slots(const moe_ctx* c) { return std::max(8, (2 * c->n_cu / 8) * 8); }
+
+template <int MODE, bool BKM>
+void launch(const moe_ctx* c, const TileArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((ffn_tile128_kernel<MODE, BKM>), dim3(slots(c)), dim3(NT), 0, s, a);
+  if (MODE == MODE_DOWN && a.g.kt >= 2 * SPLIT_STEPS)
+    hipLaunchKernelGGL(ffn_tile128_sum_kernel, dim3(slots(c) / 2 * 4), dim3(NT), 0, s, a);
+}
+
+}  // namespace
+
+// Floats of the partial tiles: as many as there are resident blocks at most, fewer where there cannot be
+// as many parts (dX of the gated expert has the longest contraction).
+size_t ffn_tile128_split_floats(const moe_ctx* c) {
+  const int most = parts_of(1, SPLIT_MAX, 2 * ceil_div(c->cfg.f, BK));
+  const long long tiles = ((long long)c->S_max / TM + c->cfg.E) * ceil_div(c->cfg.d, TN);
+  return most == 1 ? 0 : (size_t)std::min<long long>(slots(c), tiles * most) * (TM * TN);
+}
+
+int launch_ffn_tile128(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
+                       const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s) {
+  const int d = c->cfg.d, f = c->cfg.f;
+  prof_mark(c, 0, s);
+  prof_mark(c, 1, s);   // no schedule launch
+  TileArgs up = tile_args(c, counts, offsets, x_packed, d, gated ? 64 : TN, d, 1, 0, f, c->d_H, 0, gated ? 1 : -1);
+  up.g.Gs = (uint16_t*)G;
+  up.g.Us = (uint16_t*)U;
+  if (gated) launch<MODE_UP, false>(c, up, s);
+  else launch<MODE_UP1, false>(c, up, s);
+  prof_mark(c, 2, s);
+  launch<MODE_DOWN, false>(c, tile_args(c, counts, offsets, c->d_H, f, TN, f, 1, 0, d, y_packed, 2, -1), s);
+  prof_mark(c, 3, s);
+  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+}
+
+// The two halves of the data gradients (the weight gradients come between them, see
+// launch_ffn_bwd_mfma): dH = dY W2 with the activation's derivative, and dX.
+int launch_ffn_tile128_dh(moe_ctx* c, bool gated, const void* dy, const void* G, const void* U,
+                          const int32_t* counts, const int32_t* offsets, hipStream_t s) {
+  const int d = c->cfg.d, f = c->cfg.f;
+  TileArgs dh = tile_args(c, counts, offsets, dy, d, TN, d, 1, f, f, c->d_dGU, 2, -1);
+  dh.g.C2 = (uint16_t*)c->d_H;
+  dh.g.Gs = (uint16_t*)const_cast<void*>(G);
+  dh.g.Us = (uint16_t*)const_cast<void*>(U);
+  if (gated) launch<MODE_DH, true>(c, dh, s);
+  else launch<MODE_DH1, true>(c, dh, s);
+  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+}
+
+int launch_ffn_tile128_dx(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets, void* dxp,
+                          hipStream_t s) {
+  const int d = c->cfg.d, f = c->cfg.f, segs = gated ? 2 : 1;
+  launch<MODE_DOWN, true>(c, tile_args(c, counts, offsets, c->d_dGU, segs * f, TN, f, segs, d, d, dxp, 0,
+                                       gated ? 1 : -1), s);
+  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+}
+
+// Time of a GEMM's launches in us, either kernel, with `rows` rows on each of `experts` experts: a k-step
+// of a round of 256 x 256 tiles takes 1.34 us and one of 128 x 128 tiles 1.0 us where a compute unit has
+// one block, 1.4 where it has two; a launch starts and ends in 7 us; the partial sums of a cut contraction
+// cost 10 and 9 us.
+static double us_256(int experts, int rows, int N, int bn, int kt, bool down, int n_cu) {
+  const int tiles = experts * ceil_div(rows, 256) * ceil_div(N, bn), tail = tiles % n_cu;
+  int split = 1;   // as split_parts of ffn_mfma.hip
+  while (down && tail > 0 && split < 8 && tail * (split + 1) <= n_cu && kt / 2 / (split + 1) >= 4) ++split;
+  return 7 + (split > 1 ? 10 : 0) + (tiles / n_cu + (tail > 0 ? 1.0 / split : 0.0)) * (kt + (kt & 1)) * 1.34;
+}
+static double us_128(int experts, int rows, int N, int bn, int kt, bool down, int n_cu) {
+  const int tiles = experts * ceil_div(rows, TM) * ceil_div(N, bn);
+  const int split = down ? parts_of(tiles, 2 * n_cu, kt) : 1;
+  const double full = (double)tiles * split / (2 * n_cu);   // rounds with two blocks per compute unit
+  return 7 + (split > 1 ? 9 : 0) + (double)kt / split * (full <= 0.5 ? 1.0 : 1.4 * std::max(1.0, full));
+}
+
+// The smaller tiles are taken where they are the faster ones for an even routing by the estimate above
+// (which is within 25 % of what was measured over 50 layers), and no routing can bring more than two
+// rounds of larger tiles -- tokens that agree on their experts fill more of them -- or, forward, more than
+// one row block per expert.  Backward, one round of larger tiles of an even routing is as far as it goes:
+// full chips that wait for their weights read them better in rows of 512 bytes.  Larger tiles -> smaller
+// ones, FFN call, us; even routing, and all tokens on the same experts (T, d, f, E, k, resident):
+//   forward: 1999, 1160, 2888, 16, 2, 6: 102 -> 97, 156 -> 161; two-matrix 1024, 1024, 4096, 32, 2, 8: 76 ->
+//   52, 79 -> 65; 200, 2048, 1408, 64, 6, 12: 94 -> 67; 512, 2048, 2048, 8, 2, 3: 70 -> 58; two-matrix 1493,
+//   392, 1984, 64, 1, 9: 56 -> 26, 54 -> 36; 751, 664, 384, 64, 3, 11: 47 -> 25, 46 -> 26; 64, 4096, 14336, 8, 2,
+//   8: 573 -> 504, 184 -> 160
+//   backward: 1999, 1160, 2888: 246 -> 209, 344 -> 351; 751, 664, 384: 87 -> 47, 111 -> 73; 2000, 768, 1024,
+//   16, 4, 6: 113 -> 86, 181 -> 150
+//   beyond the rule: forward 2034, 768, 2560, 16, 3, 11: 101 -> 105, 107 -> 120; 4096, 1024, 4096, 16, 2, 6: 118
+//   -> 131, 214 -> 268; two-matrix 7216, 1280, 768, 8, 3, 4: 68 -> 84; backward 128, 4096, 14336, 8, 2, 8: 1645
+//   -> 1724
+static bool tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu) {
+  if (n_res == 0) return false;
+  const int kd = ceil_div(d, BK), kf = ceil_div(f, BK), segs = gated ? 2 : 1;
+  const int bn = gated && !backward ? 128 : 256;   // columns of the larger tiles, first GEMM
+  const long long most = ((long long)T * std::min(k, n_res) / 256 + n_res) * ceil_div(f, bn);
+  if (most > 2 * n_cu && (backward || T > TM)) return false;
+  const int rows = (int)(((long long)T * k + E - 1) / E);
+  if (backward && (long long)n_res * ceil_div(rows, 256) * ceil_div(f, bn) > n_cu) return false;
+  const int k2 = backward ? segs * kf : kf;
+  const double large = us_256(n_res, rows, f, bn, kd, false, n_cu) + us_256(n_res, rows, d, 256, k2, true, n_cu) +
+                       9 /* schedule */ + (backward ? 8 : 0) /* dH's epilogue, behind nothing */;
+  const double small = us_128(n_res, rows, f, bn / 2, kd, false, n_cu) + us_128(n_res, rows, d, TN, k2, true, n_cu);
+  return small < large;
+}
+
+bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {
+  if (c->tile_rows != 0) return c->tile_rows == TM;
+  int n_res = 0;
+  for (int e = 0; e < c->cfg.E; ++e) n_res += c->h_wtab[0][e] != nullptr;
+  return tile128_rule(c->S_call / c->cfg.k, c->cfg.d, c->cfg.f, c->cfg.E, c->cfg.k, n_res, gated, backward,
+                      c->n_cu);
+}
+
+// Not part of the interface, for tests: the rule; the parts of a launch of `tiles` tiles; and the tiles of
+// one context whatever the rule (0: the rule).
+extern "C" int moe_internal_ffn_tile128(int32_t T, int32_t d, int32_t f, int32_t E, int32_t k, int32_t n_res,
+                                        int32_t gated, int32_t backward, int32_t n_cu) {
+  return tile128_rule(T, d, f, E, k, n_res, gated != 0, backward != 0, n_cu) ? 1 : 0;
+}
+extern "C" int moe_internal_tile128_parts(int32_t tiles, int32_t slots, int32_t kt) {
+  return parts_of(tiles, slots, kt);
+}
+extern "C" void moe_internal_ffn_tile_rows(moe_ctx* c, int32_t rows) { c->tile_rows = rows; }

@@ -145,7 +145,8 @@ int moe_create(moe_ctx** out, const moe_config* cfg) {
   const size_t n_sup = (size_t)2 * ((size_t)c->rt_super_max * E + (size_t)E * RT_TOT_STRIDE);
   const bool mfma = ffn_mfma_supported(c);
   const size_t n_order = mfma ? ffn_mfma_order_entries(c) : 0;
-  const size_t n_split = mfma ? ffn_mfma_split_tiles(c) : 0;
+  const size_t n_split =
+      mfma ? std::max(ffn_mfma_split_tiles(c) * MFMA_BM * 256, ffn_tile128_split_floats(c)) : 0;
   // those that need not be zero; the last ones not everywhere
   const Cut plain[] = {cut(&c->d_dest_rank, E), cut(&c->d_seg_pos, E),
                        cut(&c->d_chunk_hist, (size_t)c->n_chunks_max * E), cut(&c->d_sched[0], 1),
@@ -162,7 +163,7 @@ int moe_create(moe_ctx** out, const moe_config* cfg) {
   if (!mfma) c->d_order_up = c->d_order_down = nullptr;
   if (!rt) c->d_rt_rank = c->d_rt_hist = c->d_rt_super = nullptr;
   ok = ok && (n_split == 0 || hipMalloc(reinterpret_cast<void**>(&c->d_split_ws),
-                                        n_split * MFMA_BM * 256 * sizeof(float)) == hipSuccess);
+                                        n_split * sizeof(float)) == hipSuccess);
   ok = ok && hipMalloc(&c->d_H, std::max<size_t>((size_t)S * cfg->f * c->elem, 16)) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -427,7 +428,9 @@ int moe_expert_ffn(moe_ctx* c, const void* x_packed, const int32_t* expert_count
   st = sync_tables(c, tabs, s);
   if (st != MOE_OK) return st;
   if (c->ffn_path == MOE_FFN_AUTO && ffn_mfma_supported(c)) {
-    st = (ffn_skinny_wanted(c, gated) ? launch_ffn_skinny : launch_ffn_mfma)(
+    st = (ffn_skinny_wanted(c, gated)           ? launch_ffn_skinny
+          : ffn_tile128_wanted(c, gated, false) ? launch_ffn_tile128
+                                                : launch_ffn_mfma)(
         c, gated, expert_counts, expert_offsets, x_packed, y_packed, G_save, U_save, s);
   } else if (c->ffn_path == MOE_FFN_AUTO && c->cfg.dtype == MOE_F32) {
     st = launch_ffn_f32(c, gated, expert_counts, expert_offsets, x_packed, y_packed, G_save, U_save, s);

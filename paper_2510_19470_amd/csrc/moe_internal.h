@@ -46,6 +46,7 @@ struct moe_ctx {
   int device;
   int elem;               // bytes per stored element
   int ffn_path;           // MOE_FFN_AUTO / MOE_FFN_VALU
+  int tile_rows;          // tests: 128 or 256 takes the GEMMs with these tiles (0: the rule)
   // placement
   int32_t* d_dest_rank;   // [E]
   int32_t* d_seg_pos;     // [E] position of every expert in (dest_rank, id) order
@@ -82,7 +83,7 @@ struct moe_ctx {
   TileDesc* d_order_up;   // MFMA tile order of the gate/up GEMM
   TileDesc* d_order_down; // ... and of the down GEMM
   int n_cu;               // compute units of the device
-  float* d_split_ws;      // fp32 partial tiles of the K-split tail, as many as there can be: x [256*256]
+  float* d_split_ws;      // fp32 partial tiles of the contractions that are cut, as many as there can be
   int32_t S_max;          // T_max*k
   int32_t S_call;         // T*k of the expert-FFN call being launched: the rows its buffers hold
   void* d_H;              // [T_max*k][f]
@@ -163,6 +164,15 @@ size_t ffn_mfma_order_entries(const moe_ctx* c);
 size_t ffn_mfma_split_tiles(const moe_ctx* c);   // partial tiles of the K-split tail at most
 int launch_ffn_mfma(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
                     const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s);
+// bf16, launches of few tiles: 128-row tiles
+bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward);
+size_t ffn_tile128_split_floats(const moe_ctx* c);   // of the partial tiles at most
+int launch_ffn_tile128(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
+                       const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s);
+int launch_ffn_tile128_dh(moe_ctx* c, bool gated, const void* dy, const void* G, const void* U,
+                          const int32_t* counts, const int32_t* offsets, hipStream_t s);
+int launch_ffn_tile128_dx(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
+                          void* dxp, hipStream_t s);
 // bf16, few rows per expert (S_call rows in all): a kernel that streams the weights
 bool ffn_skinny_wanted(const moe_ctx* c, bool gated);
 int launch_ffn_skinny(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,

@@ -1,5 +1,6 @@
-"""GPU parity of the bf16 expert FFN, forward and backward, for given rows per expert: the edges of the
-16-row slices and the ring of seven that the weight gradients run ahead, and of the row blocks."""
+"""GPU parity of the bf16 expert FFN, forward and backward, for given rows per expert, in 128-row and in
+256-row tiles: the edges of the row blocks and their 32-row parts, of the 16-row slices and the ring of
+seven that the weight gradients run ahead, of k-steps and column blocks, and cut contractions."""
 import numpy as np
 import pytest
 import torch
@@ -14,22 +15,28 @@ def _f64(ws):
     return [None if w is None else wl.stored_to_f32(w, "bf16").astype(np.float64) for w in ws]
 
 
+@pytest.mark.parametrize("tile", [128, 256])
 @pytest.mark.parametrize("gated", [True, False])
 @pytest.mark.parametrize("d,f,rows", [
     (512, 256, [1, 0, 15, 16, 17, 31, 32, 33]),        # whole tiles of the weight gradients
     (264, 520, [63, 64, 65, 0, 96, 97, 1, 2]),         # every last block 8 columns wide
     (256, 1032, [111, 112, 113, 127, 128, 129, 0, 5]), # one more and one less than the ring holds
     (1160, 264, [257, 0, 255, 256, 0, 385, 0, 17]),
+    (8, 8, [1, 33, 0, 130]),                           # one partial k-step
+    (72, 136, [300, 0, 65, 31]),                       # 8 of 64 in the last k-step, 8 columns in a block
+    (136, 2888, [100, 200, 0, 1]),                     # several parts per contraction, the last one partial
+    (520, 4096, [0, 64, 0, 0]),                        # eight parts, one expert
 ])
-def test_given_rows_match_oracle(d, f, rows, gated):
+def test_given_rows_match_oracle(d, f, rows, gated, tile):
     from gpu_common import DEV, TOL, moe, nerr, vals, to_device, to_host_f32, layer_from_inputs, say
-    say(f"[row edges] d={d} f={f} rows={rows} gated={gated}")
+    say(f"[row edges] d={d} f={f} rows={rows} gated={gated} tile={tile}")
     E, k = len(rows), 2
     cnt = np.array(rows, np.int32)
     T = -(-int(cnt.sum()) // k)
     cfg = wl.MoEConfig("rows", 3 + d + f, "bf16", T=T, d=d, E=E, k=k, f=f, R=1, gated=gated)
     inp = wl.make_inputs(cfg)
     lay = layer_from_inputs(inp)
+    moe.load_library().moe_internal_ffn_tile_rows(lay.ctx.handle, tile)
     off = (np.cumsum(cnt) - cnt).astype(np.int32)
     n = int(cnt.sum())
     rng = np.random.default_rng(d)
@@ -62,4 +69,31 @@ def test_given_rows_match_oracle(d, f, rows, gated):
     for got, want in ((dW1, g1), (dW3, g3), (dW2, g2)):
         for e in range(E if want is not None else 0):
             assert nerr(got[e].cpu().numpy(), want[e]) <= TOL["bf16"], (e, rows[e])
+    lay.close()
+
+
+@pytest.mark.parametrize("tile", [128, 256])
+def test_counts_that_do_not_fit_compute_nothing(tile):
+    """A segment outside the buffers, a negative count, a negative offset: no output is written, the weight
+    gradients are zero."""
+    from gpu_common import DEV, moe, to_device, layer_from_inputs
+    E, k, T, d, f = 4, 2, 64, 136, 264
+    cfg = wl.MoEConfig("bad", 9, "bf16", T=T, d=d, E=E, k=k, f=f, R=1)
+    inp = wl.make_inputs(cfg)
+    lay = layer_from_inputs(inp)
+    moe.load_library().moe_internal_ffn_tile_rows(lay.ctx.handle, tile)
+    xp = to_device(wl.store(np.ones((T * k, d), np.float32), "bf16"), "bf16")
+    G, U = (torch.ones((T * k, f), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    for cnt, off in (([10, 120, 0, 0], [0, 10, 0, 0]), ([10, -1, 0, 0], [0, 10, 0, 0]),
+                     ([128, 10, 0, 0], [0, -1, 0, 0])):
+        c = torch.tensor(cnt, dtype=torch.int32, device=DEV)
+        o = torch.tensor(off, dtype=torch.int32, device=DEV)
+        y = torch.full((T * k, d), 3.0, dtype=torch.bfloat16, device=DEV)
+        moe.moe_expert_ffn(lay.ctx, xp, c, o, lay.W1, lay.W3, lay.W2, y_packed=y)
+        dxp = torch.full((T * k, d), 5.0, dtype=torch.bfloat16, device=DEV)
+        _, dW1, _, dW2 = moe.moe_expert_ffn_bwd(lay.ctx, xp, xp, G, U, c, o, lay.W1, lay.W3, lay.W2,
+                                                dx_packed=dxp)
+        torch.cuda.synchronize()
+        assert torch.all(y == 3.0) and torch.all(dxp == 5.0)
+        assert all(torch.all(w == 0) for w in dW1 + dW2)
     lay.close()
