@@ -46,7 +46,7 @@ struct moe_ctx {
   int device;
   int elem;               // bytes per stored element
   int ffn_path;           // MOE_FFN_AUTO / MOE_FFN_VALU
-  int tile_rows;          // tests: 128 or 256 takes the GEMMs with these tiles (0: the rule)
+  int tile_rows;          // tests: 128 or 256 takes the GEMMs (and weight gradients) with these tiles (0: the rules)
   // placement
   int32_t* d_dest_rank;   // [E]
   int32_t* d_seg_pos;     // [E] position of every expert in (dest_rank, id) order

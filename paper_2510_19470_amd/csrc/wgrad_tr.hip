@@ -52,6 +52,11 @@ constexpr int SLOTS = 8;
 constexpr int TILE_BYTES = HK * 512;   // one operand tile of a slot
 constexpr int SLOT_BYTES = 2 * TILE_BYTES;
 
+// few rows per expert (wgrad_few_kernel): tiles of 256 x 128, half-steps of 32 rows, 3 stages of 24 KB
+constexpr int F_NT = 256, F_BN = 128, F_HK = 32, F_STAGES = 3;
+constexpr int F_P_BYTES = F_HK * 512, F_STAGE_BYTES = F_P_BYTES + F_HK * F_BN * 2;
+constexpr int F_COPIES = F_STAGE_BYTES / 1024 / (F_NT / 64);   // per wavefront and half-step
+
 struct WgradArgs {
   struct Job {
     const uint16_t* P;   // [S, p_pitch]; the tile's columns start at p_col0 + 256 * (row block)
@@ -93,6 +98,27 @@ __device__ __forceinline__ const char* uniform_ptr(const char* q) {
   const uint64_t v = (uint64_t)q;
   return (const char*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
                        (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+}
+
+// A wavefront's 128 x 64 of dW from (m0, n0): a lane holds column (lane & 31) of each 32-column block and
+// the rows 8g + 4(lane >> 5) + {0..3} of each 32-row block.
+template <bool RAG>
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][4], float* dW, int m0, int n0, int Mo, int No,
+                                           int lane) {
+  const int col = lane & 31, half = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + i * 32 + 8 * g + 4 * half + r;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int n = n0 + j * 32 + col;
+          if (!RAG || (m < Mo && n < No)) dW[(size_t)m * No + n] = acc[j][i][g * 4 + r];
+        }
+      }
 }
 
 // RAG: some last block is not whole (d or f no multiple of 256): columns are clamped and guarded.
@@ -226,22 +252,144 @@ __global__ __launch_bounds__(NT) void wgrad_tr_kernel(const WgradArgs p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no copy in flight into LDS at exit
   }
 
-  // ---- epilogue: lane holds column (lane & 31) of each 32-column block and the rows
-  // 8g + 4(lane >> 5) + {0..3} of each 32-row block
-  const int col = lane & 31, half = lane >> 5;
+  store_tile<RAG>(acc, dW, mblk * 256 + wm * 128, nblk * 256 + wn * 64, J.Mo, J.No, lane);
+}
+
+// The same for few rows per expert, where a block's start (its expert, counts and first copies: three cold
+// loads in a row) and its stores take longer than its few slices: 256 x 128 tiles of 256 threads, two blocks
+// on a compute unit, so that one starts or stores while the other computes; one barrier per half-step.
+// 64 rows, 8 experts, 1024 x 4096: 88 -> 77 us (403 MB written); 250 rows, 6 experts, 1160 x 2888: 91 -> 95;
+// 1032 rows, 2048 x 2048: 203 -> 204 to 209 (half as much work per byte copied).
+template <bool RAG>
+__global__ __launch_bounds__(F_NT, 2) void wgrad_few_kernel(const WgradArgs p) {
+  __shared__ uint4 lds[F_STAGES * F_STAGE_BYTES / 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+
+  // block -> tile, ordered as above; the 64 blocks resident on an XCD are a 4 x 16 patch.  (The jobs have
+  // different numbers of tiles where a matrix ends inside one.)
+  auto tiles_of = [&](const WgradArgs::Job& J) { return ((J.Mo + 255) >> 8) * ((J.No + F_BN - 1) / F_BN); };
+  const int slot = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
+  int L = ((slot >> 6) * 8 + xcd) * 64 + (slot & 63);
+  const int t0 = tiles_of(p.job[0]), t1 = tiles_of(p.job[1]), per_e = t0 + (p.n_jobs - 1) * t1;
+  if (L >= p.n_list * per_e) return;
+  const int e = p.list[L / per_e];
+  L %= per_e;
+  const int ji = L < t0 ? 0 : 1 + (L - t0) / t1;
+  if (ji > 0) L = (L - t0) % t1;
+  const WgradArgs::Job& J = p.job[ji];
+  const int NoT = (J.No + F_BN - 1) / F_BN, MoT = (J.Mo + 255) >> 8;
+  const int mg = L / (4 * NoT), r2 = L % (4 * NoT);
+  const int gm = min(4, MoT - 4 * mg);
+  const int nblk = r2 / gm, mblk = 4 * mg + r2 % gm;
+  float* dW = (float*)J.dWt[e];
+  if (dW == nullptr) return;   // this gradient is not wanted
+  const int n_e = p.sched->n_mtiles > 0 ? p.counts[e] : 0;   // (checked, as above)
+  const int row0 = p.offsets[e];
+  const int NH = (n_e + F_HK - 1) / F_HK;
+
+  f32x16 acc[2][4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  // copies: instruction c of P (0..15) fills rows 2c, 2c + 1, of Q (0..7) rows 4c .. 4c + 3; wavefront w
+  // issues c = w, w + 4, ...
+  const char* p_col = (const char*)(J.P + J.p_col0 + mblk * 256);
+  const char* q_col = (const char*)(J.Q + nblk * F_BN);
+  int p_row[4], q_row[2], p_ch[4], q_ch[2];   // row inside the stage, byte offset inside the row
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    p_row[u] = 2 * (wave + 4 * u) + (lane >> 5);
+    const int ch = (lane & 31) ^ tr_swz(p_row[u]);
+    p_ch[u] = (RAG ? min(ch, (J.Mo - mblk * 256) / 8 - 1) : ch) * 16;
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    q_row[u] = 4 * (wave + 4 * u) + (lane >> 4);
+    const int ch = (lane & 15) ^ tr_swz(q_row[u]);
+    q_ch[u] = (RAG ? min(ch, (J.No - nblk * F_BN) / 8 - 1) : ch) * 16;
+  }
+  const uint32_t p_pitch = J.p_pitch * 2, q_pitch = J.q_pitch * 2;
+  const char* zp = (const char*)p.zero_row;
+  auto issue = [&](int h, uint32_t sb) {   // all copies of half-step h; rows past the segment: zeros
+    const uint32_t dp = __builtin_amdgcn_readfirstlane(sb + wave * 1024);
+    if ((h + 1) * F_HK <= n_e) {
+      const char* pb = uniform_ptr(p_col + (size_t)(row0 + h * F_HK) * p_pitch);
+      const char* qb = uniform_ptr(q_col + (size_t)(row0 + h * F_HK) * q_pitch);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) dma16(p_row[u] * p_pitch + p_ch[u], pb, dp + u * 4096);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) dma16(q_row[u] * q_pitch + q_ch[u], qb, dp + F_P_BYTES + u * 4096);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int rg = h * F_HK + p_row[u];
+        dma16v(rg < n_e ? p_col + (size_t)(row0 + rg) * p_pitch + p_ch[u] : zp, dp + u * 4096);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int rg = h * F_HK + q_row[u];
+        dma16v(rg < n_e ? q_col + (size_t)(row0 + rg) * q_pitch + q_ch[u] : zp, dp + F_P_BYTES + u * 4096);
+      }
+    }
+  };
+  const int g16 = lane >> 4, hh = g16 >> 1, cb = g16 & 1;
+  const int s16 = lane & 15, j4 = s16 >> 2, q4 = s16 & 3;
+  const int rd_row = 8 * hh + j4;                 // + 16 kk + 4 t leaves the swizzle unchanged
+  const int rd_swz = tr_swz(rd_row);
+  uint32_t x_off[4], w_off[2];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
+    x_off[i] = rd_row * 512 + (q4 & 1) * 8 +
+               ((((wm * 128 + i * 32 + cb * 16) / 8 + (q4 >> 1)) ^ rd_swz) << 4);
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+  for (int j = 0; j < 2; ++j)
+    w_off[j] = F_P_BYTES + rd_row * (F_BN * 2) + (q4 & 1) * 8 +
+               ((((wn * 64 + j * 32 + cb * 16) / 8 + (q4 >> 1)) ^ rd_swz) << 4);
+  auto frag = [&](uint32_t a0, int pitch) -> bf16x8 {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)a0);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(a0 + 4 * pitch));
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  if (NH > 0) {
+    uint32_t sb = lds_base, sb2 = lds_base + 2 * F_STAGE_BYTES;   // stages of half-steps h and h + 2
+    issue(0, sb);
+    issue(1, sb + F_STAGE_BYTES);
+    for (int h = 0; h < NH; ++h) {
+      // half-step h has landed (the copies of h + 1 may be in flight) for everybody behind the barrier;
+      // everybody has also read half-step h - 1, whose stage takes half-step h + 2
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(F_COPIES) : "memory");
+      issue(h + 2, sb2);
+      bf16x8 xa[2][4], wb[2][2];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = mblk * 256 + wm * 128 + i * 32 + 8 * g + 4 * half + r;
+      for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int n = nblk * 256 + wn * 64 + j * 32 + col;
-          if (!RAG || (m < J.Mo && n < J.No)) dW[(size_t)m * J.No + n] = acc[j][i][g * 4 + r];
-        }
+        for (int j = 0; j < 2; ++j) wb[kk][j] = frag(sb + w_off[j] + kk * 16 * (F_BN * 2), F_BN * 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xa[kk][i] = frag(sb + x_off[i] + kk * 16 * 512, 512);
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[kk][i], wb[kk][j], acc[j][i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      sb = sb == lds_base + 2 * F_STAGE_BYTES ? lds_base : sb + F_STAGE_BYTES;
+      sb2 = sb2 == lds_base + 2 * F_STAGE_BYTES ? lds_base : sb2 + F_STAGE_BYTES;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy in flight into LDS at exit
+  }
+  store_tile<RAG>(acc, dW, mblk * 256 + wm * 128, nblk * F_BN + wn * 64, J.Mo, J.No, lane);
 }
 
 }  // namespace
@@ -271,10 +419,20 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
   a.job[0] = {(const uint16_t*)dy, (const uint16_t*)H, dW2, d, 0, f, d, f};
   a.job[1] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW1, gw, 0, d, f, d};
   a.job[2] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW3, gw, f, d, f, d};
-  const int tiles = ((d + 255) / 256) * ((f + 255) / 256);
-  const int total = a.n_jobs * a.n_list * tiles;
-  const dim3 grid((total + 255) / 256 * 256);
-  if (d % 256 != 0 || f % 256 != 0) hipLaunchKernelGGL((wgrad_tr_kernel<true>), grid, dim3(NT), 0, s, a);
-  else hipLaunchKernelGGL((wgrad_tr_kernel<false>), grid, dim3(NT), 0, s, a);
+  // rows per expert of an even routing, on either side of where the two cross (see wgrad_few_kernel)
+  const bool few = c->tile_rows != 0 ? c->tile_rows == 128 : c->S_call <= 128 * E;
+  const bool rag = d % 256 != 0 || f % 256 != 0;
+  if (few) {
+    auto tiles = [](int m, int n) { return ((m + 255) / 256) * ((n + F_BN - 1) / F_BN); };
+    const int total = a.n_list * (tiles(d, f) + (a.n_jobs - 1) * tiles(f, d));
+    const dim3 grid((total + 511) / 512 * 512);
+    if (rag) hipLaunchKernelGGL((wgrad_few_kernel<true>), grid, dim3(F_NT), 0, s, a);
+    else hipLaunchKernelGGL((wgrad_few_kernel<false>), grid, dim3(F_NT), 0, s, a);
+  } else {
+    const int total = a.n_jobs * a.n_list * ((d + 255) / 256) * ((f + 255) / 256);
+    const dim3 grid((total + 255) / 256 * 256);
+    if (rag) hipLaunchKernelGGL((wgrad_tr_kernel<true>), grid, dim3(NT), 0, s, a);
+    else hipLaunchKernelGGL((wgrad_tr_kernel<false>), grid, dim3(NT), 0, s, a);
+  }
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
