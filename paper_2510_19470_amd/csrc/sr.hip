@@ -40,9 +40,10 @@
 //
 // What bounds it, n = 14336 x 4096 bf16: the pass over both matrices (235 MB).  Encode 157 -> 95 us
 // against the version that streamed both matrices twice (histogram, then list) and picked bins in
-// one-block launches (matrices not in the last-level cache); of it the pass takes 59 us (4.0 TB/s; 50 us
+// one-block launches (matrices not in the last-level cache); of it the pass takes 58 us (4.1 TB/s; 50 us
 // with non-temporal loads, which the next reader of the shared expert pays back), the five short
-// launches 4.6-12 us each.  Decode 60 -> 46 us (5.1 TB/s): the shared expert is requested before the
+// launches 4.6-12 us each.  Half of the pass is vector instructions (selecting the residual by a tree of
+// moves instead of one comparison per word made it 80 us, reading it again from memory 64).  Decode 60 -> 46 us (5.1 TB/s): the shared expert is requested before the
 // search, 1 KB per load instruction, and the LDS of a block went from 40 to 17 KB.
 #include "moe_internal.h"
 #include "numeric.h"
@@ -233,6 +234,24 @@ struct SrLane {
 };
 __device__ __forceinline__ uint32_t key_of(float r) { return __float_as_uint(r) & 0x7fffffffu; }
 
+// Inclusive prefix sum over the wavefront, with data-parallel moves instead of LDS permutes (the pass 59.3 ->
+// 57.9 us): inside rows of 16 lanes, then a row's last lane to the rows after it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t add_moved(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v = add_moved<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
+  v = add_moved<0x112, 0xf>(v);
+  v = add_moved<0x114, 0xf>(v);
+  v = add_moved<0x118, 0xf>(v);
+  v = add_moved<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3
+  return add_moved<0x143, 0xc>(v);   // row_bcast 31 into rows 2 and 3
+}
+__device__ __forceinline__ unsigned long long wave_scan(unsigned long long v) {   // halves never carry
+  return (unsigned long long)wave_scan((uint32_t)(v >> 32)) << 32 | wave_scan((uint32_t)v);
+}
+
 // Per-vector counts of a thread packed into one integer (16 bits each, a vector has at most 4096
 // elements in the block): exclusive prefix over the block and total of all of them in one scan.
 // `slot` alternates between two LDS rows, so that one barrier per scan is enough.
@@ -243,12 +262,7 @@ struct BlockScan {
   word before, total;
   __device__ __forceinline__ void run(word mine, word (*wsum)[SR_WAVES], int slot) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    word incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const word t = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += t;
-    }
+    const word incl = wave_scan(mine);
     if (lane == 63) wsum[slot][wave] = incl;
     __syncthreads();
     before = incl - mine;
