@@ -457,7 +457,10 @@ def run(cfg, args, with_ceilings: bool = True) -> dict:
 
     # the first GEMM as the kernel traces name it (third argument: sizes that the tile does not divide)
     ragged = d % 128 != 0 or f % (128 if cfg.gated else 256) != 0
-    first_gemm = (f"ffn_mfma_kernel<{0 if cfg.gated else 4}, false, {str(ragged).lower()}>" if mfma
+    small = mfma and bool(moe.load_library().moe_internal_ffn_tile128(
+        T, d, f, E, k, n_res, int(cfg.gated), 0, torch.cuda.get_device_properties(0).multi_processor_count))
+    first_gemm = (f"ffn_tile128_kernel<{0 if cfg.gated else 4}, false>" if small else
+                  f"ffn_mfma_kernel<{0 if cfg.gated else 4}, false, {str(ragged).lower()}>" if mfma
                   else "ffn_f32_kernel (fp32 matrix cores)") + \
         (" (gate/up grouped GEMM + SwiGLU)" if cfg.gated else " (first GEMM of the two-matrix expert + ReLU)")
     rec = {

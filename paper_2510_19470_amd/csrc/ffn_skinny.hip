@@ -219,6 +219,9 @@ int launch(const SkinnyArgs& a, hipStream_t s) {
 // 8: 161 -> 147, 16: 162 -> 171; d = 1024, f = 4096, k = 2: T = 64: 48 -> 37, 96: 48 -> 56.  (By S/E
 // alone, with up to 256 tokens: T = 200 with popularity falling off as rank^-1.2, 64 experts of
 // d = f = 3072, k = 6: 135 -> 352; d = 2048, f = 14336, k = 2: 229 -> 529.)
+// (The 256-row tiles, that is.  Against the 128-row tiles that most of these sizes take beside it, those ->
+// this kernel: d = 1024, f = 4096: T = 1: 31 -> 23, 8: 46 -> 41, 64: 34 -> 39 on the same experts, 47 -> 47
+// evenly; d = 4096, f = 14336, T = 4: 493 -> 474; d = 512, f = 1024, T = 40: 31 -> 21.)
 static bool few_rows(long long T, int d, int f, int E, int k, int n_res, bool gated, int n_cu) {
   const int bn = gated ? 128 : 256;
   const bool fills = (long long)n_res * ((f + bn - 1) / bn) >= n_cu;

@@ -27,10 +27,8 @@
 // What bounds it.  The P columns are the MFMA "A" operand and the Q columns the "B" operand: a
 // lane holds one column of dW, and a store instruction writes two whole 128-byte lines.  (The other
 // way round, 16 bytes per lane spread over 32 rows, it writes 32-byte pieces of 32 lines: the same
-// loop takes 223 us instead of 204.)  The loop takes about 0.5 us per slice and neither its
-// instruction order nor the tile decides that any more: the operand copies alone take 0.25 us, MFMAs
-// and LDS reads without copies 0.42 us, and registers-only MFMAs on random operands 0.34 us (the
-// clock falls under the power limit).  6190 rows, 6 experts, d = f = 2048: 234 -> 203 us (1.5e11
+// loop takes 223 us instead of 204.)  The loop takes about 0.5 us per slice, without copies 0.42 us;
+// registers-only MFMAs on random operands take 0.34 us (the clock falls under the power limit).  6190 rows, 6 experts, d = f = 2048: 234 -> 203 us (1.5e11
 // flop, 302 MB written); 21000 rows, 12 experts, 2048 x 1408: 515 -> 475; 1500 rows, 6 experts, 1160
 // x 2888: 99 -> 91, against the loop of 32-row half-steps with one barrier each.  Within 3 % of it:
 // all reads of the next slice between the MFMAs of this one, one barrier a slice (207); 256 x 128
