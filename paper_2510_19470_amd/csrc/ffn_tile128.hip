@@ -4,7 +4,7 @@
 // Such launches are bound by the time of one tile, whatever it holds, by compute units without one and
 // by the partial sums of the K-split that fills them.  A quarter of the tile divides the work finer,
 // and two blocks of 256 threads on a compute unit cover each other's start, waits and epilogue.  What it
-// costs is half as much work per byte copied into LDS: 32 KB per 2.1e6 multiply-adds, at the copy path's
+// costs is half as much work per byte copied into LDS: 32 KB per 2.1e6 operations, at the copy path's
 // 15 TB/s about 1000 TFLOP/s, which is why full chips keep the larger tile.
 //
 // 4 wavefronts (2 along rows x 2 along columns), wavefront tile 64 x 64 = 2 x 2 accumulators of
