@@ -41,13 +41,6 @@ constexpr int NT = 512;           // threads
 constexpr int STAGE_VEC = 2048;   // uint4 per operand per stage (256 rows x 8 chunks)
 constexpr int ORDER_GROUP_M = 8;  // row blocks per group of the tile order
 
-// Parts that a tile of the down GEMM's tail is cut into (see mfma_sched_kernel).
-__host__ __device__ inline int split_parts(int tail, int n_cu, int kt_down) {
-  const int pairs = kt_down / 2;
-  int split = 1;
-  while (tail > 0 && split < 8 && tail * (split + 1) <= n_cu && pairs / (split + 1) >= 4) ++split;
-  return split;
-}
 // Most partial tiles there can be with at most `tiles` tiles: parts times tiles of the tail.
 size_t split_tiles_max(long long tiles, int n_cu, int kt_down) {
   const int most = split_parts(1, 8, kt_down);   // parts with no limit from the tail
@@ -592,14 +585,9 @@ bool ffn_mfma_supported(const moe_ctx* c) {
   return c->cfg.dtype == MOE_BF16 && c->cfg.f <= 128 * 4095 && c->cfg.d <= 256 * 4095;
 }
 
-static int ceil_div(int a, int b) { return (a + b - 1) / b; }
-
 size_t ffn_mfma_order_entries(const moe_ctx* c) {
   return (size_t)c->max_mtiles[1] * std::max(ceil_div(c->cfg.f, 128), ceil_div(c->cfg.d, 256));
 }
-
-// k-steps of a contraction of `segs` segments of `len` each (rounded up to an even number)
-static int k_steps(int len, int segs) { return (segs * ceil_div(len, BK) + 1) & ~1; }
 
 // dX of the gated expert has the longest contraction of the down-type GEMMs.
 size_t ffn_mfma_split_tiles(const moe_ctx* c) {

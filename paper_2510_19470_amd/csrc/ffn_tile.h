@@ -82,6 +82,17 @@ __device__ __forceinline__ void unpair16(const uint4& v, uint2& a, uint2& b) {
   b = make_uint2(x[1], y[1]);
 }
 
+inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+// k-steps of a contraction of `segs` segments of `len` each in the 256-row tiles (an even number)
+inline int k_steps(int len, int segs) { return (segs * ceil_div(len, BK) + 1) & ~1; }
+// Parts that a 256-row tile of the down GEMM's tail is cut into (see mfma_sched_kernel).
+__host__ __device__ inline int split_parts(int tail, int n_cu, int kt_down) {
+  const int pairs = kt_down / 2;
+  int split = 1;
+  while (tail > 0 && split < 8 && tail * (split + 1) <= n_cu && pairs / (split + 1) >= 4) ++split;
+  return split;
+}
+
 enum { MODE_UP = 0, MODE_DOWN = 1, MODE_DH = 2, MODE_UP1 = 4, MODE_DH1 = 5 };
 
 struct GemmArgs {

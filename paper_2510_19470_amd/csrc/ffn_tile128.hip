@@ -352,8 +352,6 @@ __global__ __launch_bounds__(NT) void ffn_tile128_sum_kernel(const TileArgs p) {
   }
 }
 
-int ceil_div(int a, int b) { return (a + b - 1) / b; }
-
 // A GEMM: A [rows, lda], contraction of `segs` segments of `seg_len`, N output columns in blocks of bn
 // (ldb: row length of a k-major weight-role operand, else 0).
 TileArgs tile_args(const moe_ctx* c, const int32_t* counts, const int32_t* offsets, const void* A, int lda,
@@ -445,15 +443,25 @@ int launch_ffn_tile128_dx(moe_ctx* c, bool gated, const int32_t* counts, const i
 // cost 10 and 9 us.
 static double us_256(int experts, int rows, int N, int bn, int kt, bool down, int n_cu) {
   const int tiles = experts * ceil_div(rows, 256) * ceil_div(N, bn), tail = tiles % n_cu;
-  int split = 1;   // as split_parts of ffn_mfma.hip
-  while (down && tail > 0 && split < 8 && tail * (split + 1) <= n_cu && kt / 2 / (split + 1) >= 4) ++split;
-  return 7 + (split > 1 ? 10 : 0) + (tiles / n_cu + (tail > 0 ? 1.0 / split : 0.0)) * (kt + (kt & 1)) * 1.34;
+  const int split = down ? split_parts(tail, n_cu, kt) : 1;
+  return 7 + (split > 1 ? 10 : 0) + (tiles / n_cu + (tail > 0 ? 1.0 / split : 0.0)) * kt * 1.34;
 }
 static double us_128(int experts, int rows, int N, int bn, int kt, bool down, int n_cu) {
   const int tiles = experts * ceil_div(rows, TM) * ceil_div(N, bn);
   const int split = down ? parts_of(tiles, 2 * n_cu, kt) : 1;
   const double full = (double)tiles * split / (2 * n_cu);   // rounds with two blocks per compute unit
   return 7 + (split > 1 ? 9 : 0) + (double)kt / split * (full <= 0.5 ? 1.0 : 1.4 * std::max(1.0, full));
+}
+// Both GEMMs of a call with `rows` rows on each of `experts` experts.
+static void tile_us(int experts, int rows, int d, int f, bool gated, bool backward, int n_cu, double& large,
+                    double& small) {
+  const int bn = gated && !backward ? 128 : 256;   // columns of the larger tiles, first GEMM
+  const int segs = gated && backward ? 2 : 1;
+  large = us_256(experts, rows, f, bn, k_steps(d, 1), false, n_cu) +
+          us_256(experts, rows, d, 256, k_steps(f, segs), true, n_cu) + 9 /* schedule */ +
+          (backward ? 8 : 0) /* dH's epilogue, behind nothing */;
+  small = us_128(experts, rows, f, bn / 2, ceil_div(d, BK), false, n_cu) +
+          us_128(experts, rows, d, TN, segs * ceil_div(f, BK), true, n_cu);
 }
 
 // The smaller tiles are taken where they are the faster ones for an even routing by the estimate above
@@ -473,16 +481,13 @@ static double us_128(int experts, int rows, int N, int bn, int kt, bool down, in
 //   -> 1724
 static bool tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu) {
   if (n_res == 0) return false;
-  const int kd = ceil_div(d, BK), kf = ceil_div(f, BK), segs = gated ? 2 : 1;
   const int bn = gated && !backward ? 128 : 256;   // columns of the larger tiles, first GEMM
   const long long most = ((long long)T * std::min(k, n_res) / 256 + n_res) * ceil_div(f, bn);
   if (most > 2 * n_cu && (backward || T > TM)) return false;
   const int rows = (int)(((long long)T * k + E - 1) / E);
   if (backward && (long long)n_res * ceil_div(rows, 256) * ceil_div(f, bn) > n_cu) return false;
-  const int k2 = backward ? segs * kf : kf;
-  const double large = us_256(n_res, rows, f, bn, kd, false, n_cu) + us_256(n_res, rows, d, 256, k2, true, n_cu) +
-                       9 /* schedule */ + (backward ? 8 : 0) /* dH's epilogue, behind nothing */;
-  const double small = us_128(n_res, rows, f, bn / 2, kd, false, n_cu) + us_128(n_res, rows, d, TN, k2, true, n_cu);
+  double large, small;
+  tile_us(n_res, rows, d, f, gated, backward, n_cu, large, small);
   return small < large;
 }
 
@@ -494,11 +499,15 @@ bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {
                       c->n_cu);
 }
 
-// Not part of the interface, for tests: the rule; the parts of a launch of `tiles` tiles; and the tiles of
-// one context whatever the rule (0: the rule).
+// Not part of the interface, for tests: the rule and its estimate; the parts of a launch of `tiles` tiles;
+// and the tiles of one context whatever the rule (0: the rule).
 extern "C" int moe_internal_ffn_tile128(int32_t T, int32_t d, int32_t f, int32_t E, int32_t k, int32_t n_res,
                                         int32_t gated, int32_t backward, int32_t n_cu) {
   return tile128_rule(T, d, f, E, k, n_res, gated != 0, backward != 0, n_cu) ? 1 : 0;
+}
+extern "C" void moe_internal_ffn_tile_us(int32_t experts, int32_t rows, int32_t d, int32_t f, int32_t gated,
+                                         int32_t backward, int32_t n_cu, double* us) {
+  tile_us(experts, rows, d, f, gated != 0, backward != 0, n_cu, us[0], us[1]);
 }
 extern "C" int moe_internal_tile128_parts(int32_t tiles, int32_t slots, int32_t kt) {
   return parts_of(tiles, slots, kt);

@@ -1,6 +1,8 @@
 """When the expert FFN takes 128-row tiles, and the workspace of their cut contractions (host arithmetic,
 no GPU).  The host does not know how the tokens fall: the rule goes by an even routing, but not where
 another routing can bring many more tiles."""
+import ctypes
+
 import pytest
 
 import paper_2510_19470_amd as moe
@@ -51,3 +53,22 @@ def test_parts_fit_the_resident_blocks_and_the_workspace(slots):
         for tiles in list(range(0, 70)) + [127, 128, 255, 256, 257, 512, 5000]:
             n = parts(tiles, slots, kt)
             assert 1 <= n <= most and (n == 1 or (tiles * n <= slots and kt // n >= 4))
+
+
+def tile_us(experts, rows, d, f, gated, backward):
+    us = (ctypes.c_double * 2)()
+    moe.load_library().moe_internal_ffn_tile_us(experts, rows, d, f, int(gated), int(backward), N_CU, us)
+    return us[0], us[1]
+
+
+@pytest.mark.parametrize("gated,backward", [(True, False), (False, False), (False, True)])
+def test_estimate_cuts_contractions_as_the_larger_tiles_do(gated, backward):
+    """An odd number of k-steps is rounded up to an even one before the contraction is cut: a launch of 23
+    steps has the parts of one of 24.  (dX of the gated expert contracts over two segments: always even.)"""
+    for f in (1464, 1208, 952, 568):                # 23, 19, 15 and 9 steps; one more for 56 columns more
+        for experts, rows in ((5, 703), (1, 200), (3, 1000), (2, 5000)):
+            for d in (856, 264, 2056):
+                # (more columns do not add a block of the first GEMM: both end in the same one)
+                assert -(-f // 128) == -(-(f + 56) // 128)
+                assert tile_us(experts, rows, d, f, gated, backward)[0] == \
+                    tile_us(experts, rows, d, f + 56, gated, backward)[0]
