@@ -231,7 +231,7 @@ static bool few_rows(long long T, int d, int f, int E, int k, int n_res, bool ga
 }
 
 bool ffn_skinny_wanted(const moe_ctx* c, bool gated) {
-  if (c->tile_rows != 0) return false;
+  if (c->tile_rows != 0) return c->tile_rows == WROWS;
   int n_res = 0;
   for (int e = 0; e < c->cfg.E; ++e) n_res += c->h_wtab[0][e] != nullptr;
   return few_rows(c->S_call / c->cfg.k, c->cfg.d, c->cfg.f, c->cfg.E, c->cfg.k, n_res, gated, c->n_cu);

@@ -437,58 +437,73 @@ int launch_ffn_tile128_dx(moe_ctx* c, bool gated, const int32_t* counts, const i
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 
-// Time of a GEMM's launches in us, either kernel, with `rows` rows on each of `experts` experts: a k-step
-// of a round of 256 x 256 tiles takes 1.34 us and one of 128 x 128 tiles 1.0 us where a compute unit has
-// one block, 1.4 where it has two; a launch starts and ends in 7 us; the partial sums of a cut contraction
-// cost 10 and 9 us.
-static double us_256(int experts, int rows, int N, int bn, int kt, bool down, int n_cu) {
-  const int tiles = experts * ceil_div(rows, 256) * ceil_div(N, bn), tail = tiles % n_cu;
+// Time in us of a GEMM's launches with `rows` rows on each of `experts` experts and weights of `mb` MB: a
+// constant, and the rounds of tiles, or the weights from HBM where those take longer.  A k-step of a round
+// costs more the more of the chip has tiles, the more rows these hold and, in the larger tiles, where the
+// sizes are not multiples of theirs.  bwd: k-major weights, which the smaller tiles read in pieces of 256
+// bytes.  (Constants: least squares over 181 calls of 1 to 8400 tokens, forward or backward, with up to three
+// routings each and weights that are not in the last-level cache.  On 120 other calls either side is within
+// 15 % of what was measured in the mean square, their ratio within 9 %.)
+static double us_256(int experts, int rows, int N, int bn, int K, int kt, bool down, bool bwd, double mb, int n_cu) {
+  const int blocks = ceil_div(rows, 256), tiles = experts * blocks * ceil_div(N, bn), tail = tiles % n_cu;
   const int split = down ? split_parts(tail, n_cu, kt) : 1;
-  return 7 + (split > 1 ? 10 : 0) + (tiles / n_cu + (tail > 0 ? 1.0 / split : 0.0)) * kt * 1.34;
+  const double full = 1.21 * rows / (256.0 * blocks) + (K % 128 != 0 || N % bn != 0 ? 0.32 : 0);
+  const double loop = tiles / n_cu * (kt * (0.77 + full) + 2.35) +
+                      (tail > 0 ? (double)kt / split * (0.77 + full * tail * split / n_cu) + 2.35 : 0);
+  return 11.3 /* half of the schedule in it */ + (split > 1 ? 4.4 : 0) + std::max(loop, mb / (bwd ? 5.4 : 5.2));
 }
-static double us_128(int experts, int rows, int N, int bn, int kt, bool down, int n_cu) {
-  const int tiles = experts * ceil_div(rows, TM) * ceil_div(N, bn);
-  const int split = down ? parts_of(tiles, 2 * n_cu, kt) : 1;
-  const double full = (double)tiles * split / (2 * n_cu);   // rounds with two blocks per compute unit
-  return 7 + (split > 1 ? 9 : 0) + (double)kt / split * (full <= 0.5 ? 1.0 : 1.4 * std::max(1.0, full));
+static double us_128(int experts, int rows, int N, int bn, int kt, bool down, bool bwd, double mb, int n_cu) {
+  const int blocks = ceil_div(rows, TM), tiles = experts * blocks * ceil_div(N, bn), slots = 2 * n_cu;
+  const int split = down ? parts_of(tiles, slots, kt) : 1, units = tiles * split, tail = units % slots;
+  const double steps = (double)kt / split, full = 0.77 * rows / ((double)TM * blocks);
+  const double loop = units / slots * (steps * (0.67 + full) + 1.26) +
+                      (tail > 0 ? steps * (0.67 + full * tail / slots) + 1.26 : 0);
+  return 4.65 + (split > 1 ? 8.2 : 0) + std::max(loop, mb / (bwd ? 4.5 : 5.3));
 }
-// Both GEMMs of a call with `rows` rows on each of `experts` experts.
+// Both GEMMs of a call, larger and smaller tiles.
 static void tile_us(int experts, int rows, int d, int f, bool gated, bool backward, int n_cu, double& large,
                     double& small) {
   const int bn = gated && !backward ? 128 : 256;   // columns of the larger tiles, first GEMM
   const int segs = gated && backward ? 2 : 1;
-  large = us_256(experts, rows, f, bn, k_steps(d, 1), false, n_cu) +
-          us_256(experts, rows, d, 256, k_steps(f, segs), true, n_cu) + 9 /* schedule */ +
-          (backward ? 8 : 0) /* dH's epilogue, behind nothing */;
-  small = us_128(experts, rows, f, bn / 2, ceil_div(d, BK), false, n_cu) +
-          us_128(experts, rows, d, TN, segs * ceil_div(f, BK), true, n_cu);
+  const double mb = 2e-6 * experts * d * f, mb1 = bn == 128 ? 2 * mb : mb, mb2 = segs * mb;
+  large = us_256(experts, rows, f, bn, d, k_steps(d, 1), false, backward, mb1, n_cu) +
+          us_256(experts, rows, d, 256, f, k_steps(f, segs), true, backward, mb2, n_cu) +
+          (backward ? 23.3 : 0) /* dH's epilogue */;
+  small = us_128(experts, rows, f, bn / 2, ceil_div(d, BK), false, backward, mb1, n_cu) +
+          us_128(experts, rows, d, TN, segs * ceil_div(f, BK), true, backward, mb2, n_cu) + (backward ? 9.35 : 0);
 }
 
-// The smaller tiles are taken where they are the faster ones for an even routing by the estimate above
-// (which is within 25 % of what was measured over 50 layers), and no routing can bring more than two
-// rounds of larger tiles -- tokens that agree on their experts fill more of them -- or, forward, more than
-// one row block per expert.  Backward, one round of larger tiles of an even routing is as far as it goes:
-// full chips that wait for their weights read them better in rows of 512 bytes.  Larger tiles -> smaller
-// ones, FFN call, us; even routing, and all tokens on the same experts (T, d, f, E, k, resident):
-//   forward: 1999, 1160, 2888, 16, 2, 6: 102 -> 97, 156 -> 161; two-matrix 1024, 1024, 4096, 32, 2, 8: 76 ->
-//   52, 79 -> 65; 200, 2048, 1408, 64, 6, 12: 94 -> 67; 512, 2048, 2048, 8, 2, 3: 70 -> 58; two-matrix 1493,
-//   392, 1984, 64, 1, 9: 56 -> 26, 54 -> 36; 751, 664, 384, 64, 3, 11: 47 -> 25, 46 -> 26; 64, 4096, 14336, 8, 2,
-//   8: 573 -> 504, 184 -> 160
-//   backward: 1999, 1160, 2888: 246 -> 209, 344 -> 351; 751, 664, 384: 87 -> 47, 111 -> 73; 2000, 768, 1024,
-//   16, 4, 6: 113 -> 86, 181 -> 150
-//   beyond the rule: forward 2034, 768, 2560, 16, 3, 11: 101 -> 105, 107 -> 120; 4096, 1024, 4096, 16, 2, 6: 118
-//   -> 131, 214 -> 268; two-matrix 7216, 1280, 768, 8, 3, 4: 68 -> 84; backward 128, 4096, 14336, 8, 2, 8: 1645
-//   -> 1724
+// The smaller tiles are taken where by this estimate they are the faster ones for an even routing, and all
+// tokens on the same experts (more rows on fewer experts: more and fuller tiles) cost them no more than twice
+// what they gain there, and 5 us that the estimate cannot tell.  Besides, they are held to calls whose first GEMM
+// has at most two rounds of larger tiles with any routing or, forward, at most one row block per expert;
+// backward, one round with an even routing.  Both GEMMs with sums and schedule, larger tiles -> smaller ones, us:
+// even routing; popularity falling off as rank^-1.2; all tokens on the same experts
+// (T, d, f, E, k, resident):
+//   forward: 1999, 1160, 2888, 16, 2, 6: 101 -> 95; 153 -> 141; 153 -> 151
+//            two-matrix 1024, 1024, 4096, 32, 2, 8: 62 -> 50; 78 -> 69; 76 -> 65
+//            64, 4096, 14336, 8, 2, 8: 515 -> 486; 515 -> 496; 156 -> 151
+//            751, 664, 384, 64, 3, 11: 41 -> 25; 45 -> 25; 46 -> 26
+//            two-matrix 1277, 3584, 2432, 64, 2, 8: 109 -> 88; 137 -> 128; 130 -> 141
+//   backward: 2000, 768, 1024, 16, 4, 6: 83 -> 55; 94 -> 71; 100 -> 76
+//            1999, 1160, 2888, 16, 2, 6: 134 -> 101; 158 -> 182; 166 -> 187
+//   left to the larger ones, forward: 953, 4096, 1024, 64, 8, 12: 115 -> 95; 169 -> 195; 174 -> 240
+//            5765, 2816, 896, 16, 3, 3: 84 -> 87; 184 -> 202; 232 -> 327
+//            two-matrix 1000, 3072, 3072, 64, 6, 10: 128 -> 112; 162 -> 229; 260 -> 294
+//            1422, 1816, 2672, 8, 3, 3: 16 to 35 us slower with any routing
+//   backward: 2999, 3328, 1280, 64, 8, 8: 160 -> 148; 416 -> 472; 592 -> 843
+//            64, 4096, 14336, 8, 2, 8: 474 -> 547; 476 -> 570; 181 -> 172
+//            two-matrix 2166, 1792, 1408, 32, 4, 16: 102 -> 117; 117 -> 136; 112 -> 133
 static bool tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu) {
   if (n_res == 0) return false;
-  const int bn = gated && !backward ? 128 : 256;   // columns of the larger tiles, first GEMM
-  const long long most = ((long long)T * std::min(k, n_res) / 256 + n_res) * ceil_div(f, bn);
-  if (most > 2 * n_cu && (backward || T > TM)) return false;
+  const int cols = ceil_div(f, gated && !backward ? 128 : 256);
+  if (((long long)T * std::min(k, n_res) / 256 + n_res) * cols > 2 * n_cu && (backward || T > TM)) return false;
   const int rows = (int)(((long long)T * k + E - 1) / E);
-  if (backward && (long long)n_res * ceil_div(rows, 256) * ceil_div(f, bn) > n_cu) return false;
-  double large, small;
+  if (backward && (long long)n_res * ceil_div(rows, 256) * cols > n_cu) return false;
+  double large, small, large_hot, small_hot;
   tile_us(n_res, rows, d, f, gated, backward, n_cu, large, small);
-  return small < large;
+  tile_us(std::min(k, n_res), T, d, f, gated, backward, n_cu, large_hot, small_hot);
+  return small < large && small_hot - large_hot <= 2 * (large - small) + 5;
 }
 
 bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {
@@ -500,7 +515,8 @@ bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {
 }
 
 // Not part of the interface, for tests: the rule and its estimate; the parts of a launch of `tiles` tiles;
-// and the tiles of one context whatever the rule (0: the rule).
+// and the tiles of one context whatever the rule (0: the rule), of all its products or of the weight
+// gradients alone.
 extern "C" int moe_internal_ffn_tile128(int32_t T, int32_t d, int32_t f, int32_t E, int32_t k, int32_t n_res,
                                         int32_t gated, int32_t backward, int32_t n_cu) {
   return tile128_rule(T, d, f, E, k, n_res, gated != 0, backward != 0, n_cu) ? 1 : 0;
@@ -512,4 +528,5 @@ extern "C" void moe_internal_ffn_tile_us(int32_t experts, int32_t rows, int32_t 
 extern "C" int moe_internal_tile128_parts(int32_t tiles, int32_t slots, int32_t kt) {
   return parts_of(tiles, slots, kt);
 }
-extern "C" void moe_internal_ffn_tile_rows(moe_ctx* c, int32_t rows) { c->tile_rows = rows; }
+extern "C" void moe_internal_ffn_tile_rows(moe_ctx* c, int32_t rows) { c->tile_rows = c->wgrad_rows = rows; }
+extern "C" void moe_internal_wgrad_rows(moe_ctx* c, int32_t rows) { c->wgrad_rows = rows; }

@@ -46,7 +46,8 @@ struct moe_ctx {
   int device;
   int elem;               // bytes per stored element
   int ffn_path;           // MOE_FFN_AUTO / MOE_FFN_VALU
-  int tile_rows;          // tests: 128 or 256 takes the GEMMs (and weight gradients) with these tiles (0: the rules)
+  int tile_rows;          // tests: 128 or 256 takes the GEMMs with these tiles, 16 the few-rows kernel (0: the rules)
+  int wgrad_rows;         // ... 128 or 256 the weight gradients for few or for many rows per expert
   // placement
   int32_t* d_dest_rank;   // [E]
   int32_t* d_seg_pos;     // [E] position of every expert in (dest_rank, id) order

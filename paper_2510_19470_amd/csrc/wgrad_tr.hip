@@ -418,7 +418,7 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
   a.job[1] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW1, gw, 0, d, f, d};
   a.job[2] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW3, gw, f, d, f, d};
   // rows per expert of an even routing, on either side of where the two cross (see wgrad_few_kernel)
-  const bool few = c->tile_rows != 0 ? c->tile_rows == 128 : c->S_call <= 128 * E;
+  const bool few = c->wgrad_rows != 0 ? c->wgrad_rows == 128 : c->S_call <= 128 * E;
   const bool rag = d % 256 != 0 || f % 256 != 0;
   if (few) {
     auto tiles = [](int m, int n) { return ((m + 255) / 256) * ((n + F_BN - 1) / F_BN); };

@@ -1,6 +1,6 @@
 """When the expert FFN takes 128-row tiles, and the workspace of their cut contractions (host arithmetic,
-no GPU).  The host does not know how the tokens fall: the rule goes by an even routing, but not where
-another routing can bring many more tiles."""
+no GPU).  The host does not know how the tokens fall: the rule goes by an even routing and by one where all
+tokens agree."""
 import ctypes
 
 import pytest
@@ -12,6 +12,12 @@ N_CU = 256
 
 def tile128(T, d, f, E, k, n_res, gated, backward):
     return bool(moe.load_library().moe_internal_ffn_tile128(T, d, f, E, k, n_res, int(gated), int(backward), N_CU))
+
+
+def tile_us(experts, rows, d, f, gated, backward):
+    us = (ctypes.c_double * 2)()
+    moe.load_library().moe_internal_ffn_tile_us(experts, rows, d, f, int(gated), int(backward), N_CU, us)
+    return us[0], us[1]
 
 
 @pytest.mark.parametrize("T,d,f,E,k,n_res,gated,backward,want", [
@@ -32,16 +38,36 @@ def test_rule_follows_what_was_measured(T, d, f, E, k, n_res, gated, backward, w
     assert tile128(T, d, f, E, k, n_res, gated, backward) == want
 
 
-def test_no_routing_brings_more_than_two_rounds_of_larger_tiles():
+@pytest.mark.parametrize("T,d,f,E,k,n_res,gated,backward", [
+    # measured faster with the smaller tiles evenly, but up to 1.5 times slower where the tokens agree: d > f,
+    # the second GEMM has the more tiles
+    (953, 4096, 1024, 64, 8, 12, True, False), (5765, 2816, 896, 16, 3, 3, True, False),
+    (2999, 3328, 1280, 64, 8, 8, True, True), (2615, 3840, 768, 64, 3, 22, True, False),
+    # ... and where both have about as many
+    (1000, 3072, 3072, 64, 6, 10, False, False), (1000, 3072, 3072, 64, 6, 10, False, True),
+    (1441, 4096, 4352, 16, 1, 4, True, False), (2282, 1536, 1024, 32, 5, 16, True, True),
+    # slower with any routing
+    (2166, 1792, 1408, 32, 4, 16, False, True), (343, 3840, 14080, 8, 2, 3, True, True),
+    (1422, 1816, 2672, 8, 3, 3, True, False), (64, 4096, 14336, 8, 2, 8, True, True)])
+def test_rule_looks_at_both_gemms_and_at_tokens_that_agree(T, d, f, E, k, n_res, gated, backward):
+    assert not tile128(T, d, f, E, k, n_res, gated, backward)
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_tokens_that_agree_cost_no_more_than_twice_the_gain(backward):
+    taken = 0
     for d in (8, 512, 2048, 4096):
         for f in (8, 768, 4096, 14336):
             for E, k in ((4, 1), (8, 2), (64, 6), (256, 16)):
                 for n_res in (1, E // 2, E):
                     for T in (129, 200, 1000, 4096, 16384, 200000):
                         for gated in (True, False):
-                            if tile128(T, d, f, E, k, n_res, gated, False):
-                                cols = -(-f // (128 if gated else 256))
-                                assert (T * min(k, n_res) // 256 + n_res) * cols <= 2 * N_CU
+                            if tile128(T, d, f, E, k, n_res, gated, backward):
+                                large, small = tile_us(n_res, -(-T * k // E), d, f, gated, backward)
+                                large_hot, small_hot = tile_us(min(k, n_res), T, d, f, gated, backward)
+                                assert 0 < large - small and small_hot - large_hot <= 2 * (large - small) + 5
+                                taken += 1
+    assert taken > 100
 
 
 @pytest.mark.parametrize("slots", [16, 512, 608])
@@ -53,12 +79,6 @@ def test_parts_fit_the_resident_blocks_and_the_workspace(slots):
         for tiles in list(range(0, 70)) + [127, 128, 255, 256, 257, 512, 5000]:
             n = parts(tiles, slots, kt)
             assert 1 <= n <= most and (n == 1 or (tiles * n <= slots and kt // n >= 4))
-
-
-def tile_us(experts, rows, d, f, gated, backward):
-    us = (ctypes.c_double * 2)()
-    moe.load_library().moe_internal_ffn_tile_us(experts, rows, d, f, int(gated), int(backward), N_CU, us)
-    return us[0], us[1]
 
 
 @pytest.mark.parametrize("gated,backward", [(True, False), (False, False), (False, True)])
