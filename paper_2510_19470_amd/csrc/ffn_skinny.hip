@@ -219,15 +219,27 @@ int launch(const SkinnyArgs& a, hipStream_t s) {
 // 8: 161 -> 147, 16: 162 -> 171; d = 1024, f = 4096, k = 2: T = 64: 48 -> 37, 96: 48 -> 56.  (By S/E
 // alone, with up to 256 tokens: T = 200 with popularity falling off as rank^-1.2, 64 experts of
 // d = f = 3072, k = 6: 135 -> 352; d = 2048, f = 14336, k = 2: 229 -> 529.)
-// (The 256-row tiles, that is.  Against the 128-row tiles that most of these sizes take beside it, those ->
-// this kernel: d = 1024, f = 4096: T = 1: 31 -> 23, 8: 46 -> 41, 64: 34 -> 39 on the same experts, 47 -> 47
-// evenly; d = 4096, f = 14336, T = 4: 493 -> 474; d = 512, f = 1024, T = 40: 31 -> 21.)
+// (The 256-row tiles, that is.)  The 128-row tiles serve most of these sizes better than the 256-row ones, but
+// for them a longer row means more k-steps in a row: where they would take the layer, the rows are held to 48 KB
+// per element of d (98 MB up to d = 2048).  128-row tiles -> this kernel, us, all tokens on the same experts |
+// on the resident ones evenly | on all evenly:
+//   1024 x 4096, E = 16, k = 2, 6 resident: T = 8: 29 -> 20 | 44 -> 40 | 45 -> 40, 32 (67 MB): 29 -> 27 | 45 -> 46 |
+//   45 -> 42, 48 (101 MB): 33 -> 35 | 45 -> 49 | 45 -> 43, 64: 33 -> 38 | 45 -> 57 | 46 -> 45; 4 resident,
+//   T = 64 (134 MB): 34 -> 40 | 34 -> 41 | 35 -> 31
+//   2048 x 1408, E = 64, k = 6, 12 resident: T = 8: 42 -> 36 | 58 -> 58 | 60 -> 57, 16 (69 MB): 42 -> 41 | 58 -> 61 |
+//   58 -> 58, 24 (104 MB): 42 -> 49 | 58 -> 64 | 58 -> 58, 32: 42 -> 49 | 59 -> 68 | 58 -> 57
+//   4096 x 2048, E = 16, k = 2, 16 resident: T = 16: 59 -> 36 | 185 -> 165, 32 (134 MB): 59 -> 41 | 166 -> 166
+//   4096 x 14336, E = 8, k = 2, 8 resident: T = 1: 131 -> 139, 2: 139 -> 139 | 268 -> 250, 4: 139 -> 146 | 476 -> 473
+//   two-matrix: 2048 x 14336, T = 8 (117 MB): 51 -> 62 | 182 -> 196; 768 x 2048, T = 64: 26 -> 20 | 24 -> 17;
+//   3072 x 3072, k = 6, T = 8 (113 MB): 69 -> 69 | 79 -> 79
 static bool few_rows(long long T, int d, int f, int E, int k, int n_res, bool gated, int n_cu) {
   const int bn = gated ? 128 : 256;
   const bool fills = (long long)n_res * ((f + bn - 1) / bn) >= n_cu;
   const int most = !fills ? 24 : d < 4096 ? 8 : 4;   // rows per expert
   const long long l2_bytes = T * std::min(k, n_res) * d * f / 4;
-  return T <= 16 * GROUPS && l2_bytes <= 200000000ll && T * k <= (long long)most * E;
+  if (T > 16 * GROUPS || l2_bytes > 200000000ll || T * k > (long long)most * E) return false;
+  return l2_bytes <= 48000ll * std::max(d, 2048) ||
+         !ffn_tile128_rule((int)T, d, f, E, k, n_res, gated, false, n_cu);
 }
 
 bool ffn_skinny_wanted(const moe_ctx* c, bool gated) {

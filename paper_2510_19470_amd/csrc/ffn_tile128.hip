@@ -494,7 +494,7 @@ static void tile_us(int experts, int rows, int d, int f, bool gated, bool backwa
 //   backward: 2999, 3328, 1280, 64, 8, 8: 160 -> 148; 416 -> 472; 592 -> 843
 //            64, 4096, 14336, 8, 2, 8: 474 -> 547; 476 -> 570; 181 -> 172
 //            two-matrix 2166, 1792, 1408, 32, 4, 16: 102 -> 117; 117 -> 136; 112 -> 133
-static bool tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu) {
+bool ffn_tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu) {
   if (n_res == 0) return false;
   const int cols = ceil_div(f, gated && !backward ? 128 : 256);
   if (((long long)T * std::min(k, n_res) / 256 + n_res) * cols > 2 * n_cu && (backward || T > TM)) return false;
@@ -510,8 +510,8 @@ bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {
   if (c->tile_rows != 0) return c->tile_rows == TM;
   int n_res = 0;
   for (int e = 0; e < c->cfg.E; ++e) n_res += c->h_wtab[0][e] != nullptr;
-  return tile128_rule(c->S_call / c->cfg.k, c->cfg.d, c->cfg.f, c->cfg.E, c->cfg.k, n_res, gated, backward,
-                      c->n_cu);
+  return ffn_tile128_rule(c->S_call / c->cfg.k, c->cfg.d, c->cfg.f, c->cfg.E, c->cfg.k, n_res, gated, backward,
+                          c->n_cu);
 }
 
 // Not part of the interface, for tests: the rule and its estimate; the parts of a launch of `tiles` tiles;
@@ -519,7 +519,7 @@ bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {
 // gradients alone.
 extern "C" int moe_internal_ffn_tile128(int32_t T, int32_t d, int32_t f, int32_t E, int32_t k, int32_t n_res,
                                         int32_t gated, int32_t backward, int32_t n_cu) {
-  return tile128_rule(T, d, f, E, k, n_res, gated != 0, backward != 0, n_cu) ? 1 : 0;
+  return ffn_tile128_rule(T, d, f, E, k, n_res, gated != 0, backward != 0, n_cu) ? 1 : 0;
 }
 extern "C" void moe_internal_ffn_tile_us(int32_t experts, int32_t rows, int32_t d, int32_t f, int32_t gated,
                                          int32_t backward, int32_t n_cu, double* us) {

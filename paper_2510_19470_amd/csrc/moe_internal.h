@@ -166,6 +166,7 @@ size_t ffn_mfma_split_tiles(const moe_ctx* c);   // partial tiles of the K-split
 int launch_ffn_mfma(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
                     const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s);
 // bf16, launches of few tiles: 128-row tiles
+bool ffn_tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu);
 bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward);
 size_t ffn_tile128_split_floats(const moe_ctx* c);   // of the partial tiles at most
 int launch_ffn_tile128(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
