@@ -380,7 +380,16 @@ TileArgs tile_args(const moe_ctx* c, const int32_t* counts, const int32_t* offse
   return a;
 }
 
-int slots(const moe_ctx* c) { return std::max(8, (2 * c->n_cu / 8) * 8); }
+int slots_of(int n_cu) { return std::max(8, (2 * n_cu / 8) * 8); }
+int slots(const moe_ctx* c) { return slots_of(c->n_cu); }
+
+// Floats of the partial tiles of a context with S rows: as many as there are resident blocks at most, fewer
+// where there cannot be as many parts (dX of the gated expert has the longest contraction).
+size_t split_floats(int S, int E, int d, int f, int n_cu) {
+  const int most = parts_of(1, SPLIT_MAX, 2 * ceil_div(f, BK));
+  const long long tiles = ((long long)S / TM + E) * ceil_div(d, TN);
+  return most == 1 ? 0 : (size_t)std::min<long long>(slots_of(n_cu), tiles * most) * (TM * TN);
+}
 
 template <int MODE, bool BKM>
 void launch(const moe_ctx* c, const TileArgs& a, hipStream_t s) {
@@ -391,12 +400,8 @@ void launch(const moe_ctx* c, const TileArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Floats of the partial tiles: as many as there are resident blocks at most, fewer where there cannot be
-// as many parts (dX of the gated expert has the longest contraction).
 size_t ffn_tile128_split_floats(const moe_ctx* c) {
-  const int most = parts_of(1, SPLIT_MAX, 2 * ceil_div(c->cfg.f, BK));
-  const long long tiles = ((long long)c->S_max / TM + c->cfg.E) * ceil_div(c->cfg.d, TN);
-  return most == 1 ? 0 : (size_t)std::min<long long>(slots(c), tiles * most) * (TM * TN);
+  return split_floats(c->S_max, c->cfg.E, c->cfg.d, c->cfg.f, c->n_cu);
 }
 
 int launch_ffn_tile128(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
@@ -514,8 +519,8 @@ bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {
                           c->n_cu);
 }
 
-// Not part of the interface, for tests: the rule and its estimate; the parts of a launch of `tiles` tiles;
-// and the tiles of one context whatever the rule (0: the rule), of all its products or of the weight
+// Not part of the interface, for tests: the rule and its estimate; the parts of a launch of `tiles` tiles
+// and the workspace for them; and the tiles of one context whatever the rule (0: the rule), of all its products or of the weight
 // gradients alone.
 extern "C" int moe_internal_ffn_tile128(int32_t T, int32_t d, int32_t f, int32_t E, int32_t k, int32_t n_res,
                                         int32_t gated, int32_t backward, int32_t n_cu) {
@@ -527,6 +532,9 @@ extern "C" void moe_internal_ffn_tile_us(int32_t experts, int32_t rows, int32_t 
 }
 extern "C" int moe_internal_tile128_parts(int32_t tiles, int32_t slots, int32_t kt) {
   return parts_of(tiles, slots, kt);
+}
+extern "C" int64_t moe_internal_tile128_split_floats(int32_t S, int32_t E, int32_t d, int32_t f, int32_t n_cu) {
+  return (int64_t)split_floats(S, E, d, f, n_cu);
 }
 extern "C" void moe_internal_ffn_tile_rows(moe_ctx* c, int32_t rows) { c->tile_rows = c->wgrad_rows = rows; }
 extern "C" void moe_internal_wgrad_rows(moe_ctx* c, int32_t rows) { c->wgrad_rows = rows; }

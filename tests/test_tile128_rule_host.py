@@ -71,7 +71,7 @@ def test_tokens_that_agree_cost_no_more_than_twice_the_gain(backward):
 
 
 @pytest.mark.parametrize("slots", [16, 512, 608])
-def test_parts_fit_the_resident_blocks_and_the_workspace(slots):
+def test_parts_fit_the_resident_blocks(slots):
     parts = moe.load_library().moe_internal_tile128_parts
     for kt in (1, 7, 8, 9, 16, 63, 64, 448):
         most = parts(1, 8, kt)                  # what the workspace is sized with
@@ -92,3 +92,29 @@ def test_estimate_cuts_contractions_as_the_larger_tiles_do(gated, backward):
                 assert -(-f // 128) == -(-(f + 56) // 128)
                 assert tile_us(experts, rows, d, f, gated, backward)[0] == \
                     tile_us(experts, rows, d, f + 56, gated, backward)[0]
+
+
+@pytest.mark.parametrize("n_cu", [8, 256, 304])
+def test_partial_sums_fit_the_workspace(n_cu):
+    """Every launch that a context can make, forward and both dX contractions, against what moe_create
+    allocates for it."""
+    lib = moe.load_library()
+    lib.moe_internal_tile128_split_floats.restype = ctypes.c_int64
+    slots, cut = max(8, 2 * n_cu // 8 * 8), 0
+    for S in (0, 1, 100, 128, 129, 1000, 20000):
+        for E in (1, 3, 8, 256):
+            for d in (8, 128, 136, 1160, 4096):
+                for f in (8, 128, 192, 200, 256, 448, 520, 2888):
+                    have = lib.moe_internal_tile128_split_floats(S, E, d, f, n_cu)
+                    steps, cols = -(-f // 64), -(-d // 128)
+                    most_blocks = S // 128 + E      # what the kernel counts up to
+                    for blocks in {1, 2, 3, 7, 8, E, most_blocks // 2, most_blocks - 1, most_blocks}:
+                        if not 1 <= blocks <= most_blocks:
+                            continue
+                        for kt in (steps, 2 * steps):
+                            parts = lib.moe_internal_tile128_parts(blocks * cols, slots, kt)
+                            if parts > 1:
+                                assert blocks * cols * parts * 128 * 128 <= have
+                                cut += 1
+                    assert have <= slots * 128 * 128
+    assert cut > 1000
