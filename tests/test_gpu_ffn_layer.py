@@ -14,8 +14,9 @@ def _f64_list(ws, dtype):
     return [None if w is None else wl.stored_to_f32(w, dtype).astype(np.float64) for w in ws]
 
 
-def _run_ffn_case(cfg, idx_np, path, experts_present=None, save=False):
-    """FFN alone on a given routing: every float output against the oracle."""
+def _run_ffn_case(cfg, idx_np, path, experts_present=None, save=False, tile=0):
+    """FFN alone on a given routing: every float output against the oracle.  tile: 128 or 256 rows (0: as
+    the library chooses)."""
     from gpu_common import DEV, TOL, moe, nerr, vals, to_device, to_host_f32, layer_from_inputs
     inp = wl.make_inputs(cfg)
     if experts_present is not None:
@@ -24,6 +25,7 @@ def _run_ffn_case(cfg, idx_np, path, experts_present=None, save=False):
                 inp.W1[e] = inp.W3[e] = inp.W2[e] = None
     lay = layer_from_inputs(inp)
     moe.moe_set_ffn_path(lay.ctx, path)
+    moe.load_library().moe_internal_ffn_tile_rows(lay.ctx.handle, tile)
     cnt, off, _, _, s2r, r2s = orc.dispatch_maps(idx_np, inp.dest_rank, cfg.R)
     xp_st = orc.pack_rows(inp.x, r2s, cfg.k)
     xp = to_device(xp_st, cfg.dtype)
@@ -77,21 +79,22 @@ def test_ffn_bf16_reduced_shapes(path, T, d, E, k, f, skew, present):
     say(f"    normalised max error {err:.3e}")
 
 
-@pytest.mark.parametrize("T,d,E,k,f", [
-    (600, 256, 4, 2, 1024),     # 16 k-steps: the tail of the down GEMM is cut in 2
-    (900, 512, 4, 2, 2048),     # 32 k-steps: cut in 4
-    (700, 256, 3, 2, 4096),     # 64 k-steps: cut in 8
-    (700, 256, 3, 2, 1408),     # 22 k-steps: cut in 2 uneven parts (12 + 10)
-    (16600, 512, 2, 2, 4096),   # 260 tiles: one full round of whole tiles + 4 tiles cut in 8
+@pytest.mark.parametrize("tile", [256, 128])
+@pytest.mark.parametrize("T,d,E,k,f", [                        # in 256-row tiles | in 128-row tiles
+    (600, 256, 4, 2, 1024),     # 16 k-steps: the tail of the down GEMM is cut in 2 | every tile in 4
+    (900, 512, 4, 2, 2048),     # 32 k-steps: cut in 4 | in 8
+    (700, 256, 3, 2, 4096),     # 64 k-steps: cut in 8 | in 8
+    (700, 256, 3, 2, 1408),     # 22 k-steps: cut in 2 uneven parts (12 + 10) | in 5 (5 + 5 + 4 + 4 + 4)
+    (16600, 512, 2, 2, 4096),   # 260 tiles: one full round of whole tiles + 4 tiles cut in 8 | not cut
 ])
-def test_ffn_down_gemm_k_split_tail(T, d, E, k, f):
+def test_ffn_down_gemm_k_split_tail(T, d, E, k, f, tile):
     """Shapes whose last, partly filled round of down-GEMM tiles is split along the
     contraction (fp32 partial tiles summed in a fixed order) next to whole tiles."""
     from gpu_common import moe, say
-    say(f"[ffn] K-split tail T={T} d={d} E={E} k={k} f={f}")
+    say(f"[ffn] K-split tail T={T} d={d} E={E} k={k} f={f} tile={tile}")
     cfg = wl.MoEConfig("ksplit", 999 + T, "bf16", T=T, d=d, E=E, k=k, f=f, R=1)
     idx = wl.random_routing(T, E, k, seed=T + 1, skew=0.3)
-    err = _run_ffn_case(cfg, idx, moe.MOE_FFN_AUTO, save=False)
+    err = _run_ffn_case(cfg, idx, moe.MOE_FFN_AUTO, save=False, tile=tile)
     say(f"    normalised max error {err:.3e}")
 
 
@@ -257,8 +260,12 @@ def test_full_size_configs_every_element(name):
     ("train", 700, "auto", dict(d=256, f=512, E=8, k=2, R=4, migrated=(5,))),      # ragged, small
     ("train", 300, "auto", dict(d=512, f=256, E=16, k=1, R=4, migrated=())),       # empty experts
     # dX with a K-split tail whose middle part straddles the switch from W1 to W3
-    # (K = 2f = 24 k-steps in 3 parts of 8, the k-major operand changes at step 12)
+    # (256-row tiles: K = 2f = 24 k-steps in 3 parts of 8, the k-major operand changes at step 12;
+    # 26 steps in parts of 10, 8 and 8, in 128-row tiles of 5, 5 and four times 4: at step 13)
     ("train", 700, "auto", dict(d=512, f=768, E=4, k=2, R=2, migrated=(3,))),
+    ("train", 700, "tile256", dict(d=512, f=768, E=4, k=2, R=2, migrated=(3,))),
+    ("train", 700, "tile256", dict(d=512, f=832, E=4, k=2, R=2, migrated=(3,))),
+    ("train", 700, "tile128", dict(d=512, f=832, E=4, k=2, R=2, migrated=(3,))),
     # many experts with a handful of rows each (and empty ones): 64 resident experts
     ("train", 900, "auto", dict(d=256, f=256, E=128, k=8, R=2, migrated=())),
 ])
@@ -276,6 +283,8 @@ def test_backward_matches_oracle(name, T, path, shape):
     lay = layer_from_inputs(inp)
     if path == "valu":
         moe.moe_set_ffn_path(lay.ctx, moe.MOE_FFN_VALU)
+    if path.startswith("tile"):
+        moe.load_library().moe_internal_ffn_tile_rows(lay.ctx.handle, int(path[4:]))
     x = to_device(inp.x, cfg.dtype)
     dout = to_device(inp.dOut, cfg.dtype)
     fwd = lay.forward(x, save=True)
@@ -412,6 +421,8 @@ def test_backward_unwanted_weight_gradients(path):
     lay = layer_from_inputs(inp)
     if path == "valu":
         moe.moe_set_ffn_path(lay.ctx, moe.MOE_FFN_VALU)
+    if path.startswith("tile"):
+        moe.load_library().moe_internal_ffn_tile_rows(lay.ctx.handle, int(path[4:]))
     x = to_device(inp.x, cfg.dtype)
     dout = to_device(inp.dOut, cfg.dtype)
     fwd = lay.forward(x, save=True)

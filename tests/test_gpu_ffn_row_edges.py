@@ -28,6 +28,24 @@ def _f64(ws):
     (520, 4096, [0, 64, 0, 0]),                        # eight parts, one expert
 ])
 def test_given_rows_match_oracle(d, f, rows, gated, tile):
+    _check_given_rows(d, f, rows, gated, tile)
+
+
+# A block's tiles follow one another without a stop: the next one's first copies are under way while the
+# outputs of the last are stored.  512 blocks serve the 128-row tiles, 256 the 256-row ones (here 816 and 264
+# tiles or more in each of the four GEMMs), and tiles that follow one another differ in the rows they hold.
+@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("gated", [True, False])
+@pytest.mark.parametrize("d,f", [(648, 648), (768, 768)])
+def test_several_tiles_per_block_match_oracle(d, f, gated, tile):
+    rows = [1, 33, 129, 161, 300, 385, 20, 257] * 8
+    for n in (d, f):
+        n_tiles = sum(-(-r // tile) for r in rows) * -(-n // tile)
+        assert n_tiles > (2 if tile == 128 else 1) * torch.cuda.get_device_properties(0).multi_processor_count
+    _check_given_rows(d, f, rows, gated, tile)
+
+
+def _check_given_rows(d, f, rows, gated, tile):
     from gpu_common import DEV, TOL, moe, nerr, vals, to_device, to_host_f32, layer_from_inputs, say
     say(f"[row edges] d={d} f={f} rows={rows} gated={gated} tile={tile}")
     E, k = len(rows), 2
@@ -62,10 +80,14 @@ def test_given_rows_match_oracle(d, f, rows, gated, tile):
         yo, Go = orc.expert_ffn2(xv, cnt, off, W1, W2)
         dxo, g1, g2 = orc.expert_ffn2_bwd(dyv, xv, Gg, cnt, off, W1, W2)
         g3 = None
-    assert nerr(Gg[:n], Go[:n]) <= TOL["bf16"]
-    assert nerr(to_host_f32(y)[:n], yo[:n]) <= TOL["bf16"]
-    assert nerr(to_host_f32(dxp)[:n], dxo[:n]) <= TOL["bf16"]
-    # every expert by itself: a row too many or too few shows where there are few
+    # every expert by itself: a wrong tile, a row too many or too few shows where there are few
+    yg, dxg = to_host_f32(y), to_host_f32(dxp)
+    for e in range(E):
+        seg = slice(int(off[e]), int(off[e] + cnt[e]))
+        if cnt[e] > 0:
+            assert nerr(Gg[seg], Go[seg]) <= TOL["bf16"], ("G", e, rows[e])
+            assert nerr(yg[seg], yo[seg]) <= TOL["bf16"], ("y", e, rows[e])
+            assert nerr(dxg[seg], dxo[seg]) <= TOL["bf16"], ("dX", e, rows[e])
     for got, want in ((dW1, g1), (dW3, g3), (dW2, g2)):
         for e in range(E if want is not None else 0):
             assert nerr(got[e].cpu().numpy(), want[e]) <= TOL["bf16"], (e, rows[e])
