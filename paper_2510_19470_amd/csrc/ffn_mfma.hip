@@ -392,9 +392,10 @@ __global__ __launch_bounds__(NT) void ffn_mfma_kernel(const GemmArgs p) {
 
   // 32-row blocks of this wavefront's half of the unit that hold rows (wave-uniform).  A unit is
   // lean for a wavefront with none or one: its other token blocks are not copied either, so that the
-  // last row block of an expert and the few rows of a decoding step do not move 32 KB of repeated
-  // rows per step beside 32 KB of weights (16 rows per expert, d = 4096, f = 14336: 592 -> 562 us the
-  // pass; 64 rows per expert, 1024 x 4096, training: 269 -> 248, of it the partial sums below half).
+  // last row block of an expert does not move 32 KB of repeated rows per step beside 32 KB of weights.
+  // (Measured on layers that have nothing but such units and take the 128-row tiles now: 16 rows per
+  // expert, 4096 x 14336: 592 -> 562 us the pass; 64 rows per expert, 1024 x 4096, training: 269 -> 248, of
+  // it the partial sums below half.)
   auto active = [&](const Unit& u) -> int {
     return __builtin_amdgcn_readfirstlane(min(4, max(0, (u.rows - wm * 128 + 31) >> 5)));
   };

@@ -82,8 +82,8 @@ __device__ __forceinline__ void skinny_sums(f32x4 (&acc)[NF][G], const uint4* co
   // 128 registers in all.  Short rows have fewer than four units for a wavefront; one at a time they
   // waited for memory once each (FFN call, 6 experts of 1024 x 4096: 1 token 22.9 -> 19.2 us, 8 tokens
   // 43.4 -> 40.2; two-matrix, 3072 x 3072, 8 tokens: 80.7 -> 77.2).
-  if (NF + G <= 3) skinny_units<4, NF, G>(acc, w, x, full, u);
-  if (NF + G <= 5) skinny_units<2, NF, G>(acc, w, x, full, u);
+  if constexpr (NF + G <= 3) skinny_units<4, NF, G>(acc, w, x, full, u);
+  if constexpr (NF + G <= 5) skinny_units<2, NF, G>(acc, w, x, full, u);
   // the units left over, the last of which may hold fewer than 8 chunks (zeros for the rest)
   for (; u * 8 < n_chunks; u += NW)
 #pragma unroll

@@ -1,5 +1,6 @@
 // Shared pieces of the bf16 grouped expert GEMMs on the matrix cores (ffn_mfma.hip: 256-row tiles,
-// ffn_tile128.hip: 128-row tiles): LDS layouts, copies, epilogues.
+// ffn_tile128.hip: 128-row tiles) and of the weight gradients (wgrad_tr.hip): LDS layouts, copies,
+// epilogues.
 #pragma once
 #include "moe_internal.h"
 #include "numeric.h"
@@ -14,10 +15,13 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 
 constexpr int BK = 64;            // k per stage
 
+// Swizzle of the 16-byte chunks of a row-major stage's rows ...
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); }
-// ... of a k-major stage (512-byte rows, transpose reads): the groups of 16 lanes that can
-// share an LDS cycle read 4 rows (row & 3) x 32 bytes each, from the two halves of bit 3 of
-// the row or the two 32-byte column halves; their 16 chunks must differ modulo 16
+// ... and of a k-major tile's (rows of a multiple of 256 bytes, transpose reads).  A transpose read
+// takes, per group of 16 lanes, 4 rows (row & 3) x 32 bytes; the four groups of a wavefront are (bit 3 of
+// the row, the 32-byte column half).  LDS has 64 banks of 4 bytes and serves 32 lanes per cycle: the 16
+// chunks of any two groups that can share a cycle must differ modulo 16.  Bits 2-3 of the chunk take
+// row & 3, bit 1 takes bit 3 of the row (the column half sits in bit 1 already).
 __device__ __forceinline__ int tr_swz(int row) { return ((row & 3) << 2) ^ (((row >> 3) & 1) << 1); }
 
 typedef __attribute__((address_space(3))) void* lptr_t;

@@ -7,7 +7,7 @@
 //
 // Both operands are stored with the contraction index (the token row) OUTERMOST: an MFMA
 // fragment (one output row or column, 8 consecutive k) is a column of 8 rows in memory.  The
-// tiles are copied to LDS as they are (32 token rows x 256 columns, 512 bytes per row, direct
+// tiles are copied to LDS as they are (16 token rows x 256 columns, 512 bytes per row, direct
 // global -> LDS copies) and read with the LDS transpose read of gfx950,
 // ds_read_b64_tr_b16: inside a group of 16 lanes, lane s supplies the address of 4 elements
 // of row (s >> 2) -- column group (s & 3) -- and lane i receives element (i & 3) of the four
@@ -20,8 +20,8 @@
 // runs in slices of 16 token rows through a ring of 8 LDS slots of 16 KB (P 8 KB + Q 8 KB), seven
 // slices ahead.  The two groups of four wavefronts (wm) alternate as in the forward kernel: while
 // one multiplies a slice (8 MFMAs), the other reads its 12 fragments of the next one and issues two
-// copies.  16-byte chunks of a row are XOR-swizzled (tr_swz below), which puts the rows x 32 bytes
-// that the groups of 16 lanes sharing an LDS cycle read on distinct banks.  Rows past the end of the
+// copies.  16-byte chunks of a row are XOR-swizzled (tr_swz), which puts the rows x 32 bytes that the
+// groups of 16 lanes sharing an LDS cycle read on distinct banks.  Rows past the end of the
 // expert's segment are fetched from a row of zeros, so a ragged segment needs no padded copy.
 //
 // What bounds it.  The P columns are the MFMA "A" operand and the Q columns the "B" operand: a
@@ -34,15 +34,9 @@
 // all reads of the next slice between the MFMAs of this one, one barrier a slice (207); 256 x 128
 // tiles with two blocks on a compute unit (204 to 209); persistent blocks that copy on across tiles
 // (208).
-#include "moe_internal.h"
+#include "ffn_tile.h"
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 
 constexpr int NT = 512;
 constexpr int HK = 16;                 // token rows per slice
@@ -71,32 +65,6 @@ struct WgradArgs {
                               // the caller's counts and offsets do not fit the buffers
   const uint16_t* zero_row;   // 512 bytes of zeros
 };
-
-// Swizzle of the 16-byte chunks of a 512-byte tile row.  A transpose read takes, per group of
-// 16 lanes, 4 rows (j4 = row & 3) x 32 bytes; the four groups of a wavefront are (hh = bit 3
-// of the row, cb = the 32-byte column half).  LDS has 64 banks of 4 bytes and serves 32 lanes
-// per cycle, and the row pitch is a multiple of 256 bytes, so the 16 chunks of any two
-// groups that can share a cycle -- (hh, cb = 0 | 1) or (hh = 0 | 1, cb) -- must differ
-// modulo 16: bits 2-3 of the chunk take j4, bit 1 takes hh (cb sits in bit 1 already).
-__device__ __forceinline__ int tr_swz(int row) { return ((row & 3) << 2) ^ (((row >> 3) & 1) << 1); }
-
-// 16 bytes per lane global -> LDS; the wavefront's 1 KB lands at lds_addr (wave-uniform, via M0) +
-// lane * 16.  A 64-bit address per lane, or a wave-uniform base and 32 bits per lane.
-__device__ __forceinline__ void dma16v(const void* src, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma16(uint32_t off, const char* base, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
-               : "memory", "m0");
-}
-
-// A pointer that is the same in all lanes, in scalar registers.
-__device__ __forceinline__ const char* uniform_ptr(const char* q) {
-  const uint64_t v = (uint64_t)q;
-  return (const char*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
-                       (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
-}
 
 // A wavefront's 128 x 64 of dW from (m0, n0): a lane holds column (lane & 31) of each 32-column block and
 // the rows 8g + 4(lane >> 5) + {0..3} of each 32-row block.
@@ -417,7 +385,18 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
   a.job[0] = {(const uint16_t*)dy, (const uint16_t*)H, dW2, d, 0, f, d, f};
   a.job[1] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW1, gw, 0, d, f, d};
   a.job[2] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW3, gw, f, d, f, d};
-  // rows per expert of an even routing, on either side of where the two cross (see wgrad_few_kernel)
+  // By the rows per expert of an even routing.  The two cross between 96 and 512 of them, later on whole sizes
+  // and earlier where popularity falls off as rank^-1.2; up to the line the kernel for few rows gains up to 6 %
+  // of the whole backward and loses up to 1 %.  Backward, us, many -> few at 64, 128, 192, 256 rows; even, and
+  // rank^-1.2:
+  //   2048 x 2048, 6 of 32 experts: 171 -> 162, 191 -> 182, 214 -> 206, 234 -> 228; 223 -> 214, 265 -> 258,
+  //   305 -> 301, 336 -> 331
+  //   two-matrix 1024 x 4096, 8 of 32: 138 -> 130, 151 -> 146, 170 -> 164, 185 -> 182; 175 -> 171, 206 -> 204,
+  //   282 -> 287, 317 -> 326
+  //   1160 x 2888, 6 of 16: 159 -> 158, 187 -> 185, 213 -> 215, 239 -> 241; 200 -> 201, 237 -> 238, 268 -> 270,
+  //   293 -> 294
+  //   2048 x 1408, 12 of 64: 212 -> 207, 237 -> 233, 262 -> 261, 286 -> 288; 277 -> 278, 327 -> 326, 408 -> 415,
+  //   551 -> 557
   const bool few = c->wgrad_rows != 0 ? c->wgrad_rows == 128 : c->S_call <= 128 * E;
   const bool rag = d % 256 != 0 || f % 256 != 0;
   if (few) {
