@@ -355,9 +355,10 @@ int moe_sr_decode(moe_ctx* ctx, const void* shared, const void* values, const in
  * call are cut into n_chunks contiguous chunks of chunk_tokens = the next multiple of 4 of
  * ceil(T / n_chunks) tokens (the last chunk takes the rest, possibly none); chunk c runs
  * moe_route -> moe_dispatch -> moe_expert_ffn -> moe_combine on internal stream
- * c mod n_streams, which has a context of its own.  On one GPU there are no transfers: what
- * overlaps is the HBM-bound work of one chunk with the expert GEMMs of another.  The result
- * is that of the four calls made per chunk: every chunk has its own packed layout.
+ * c mod n_streams, which has a context of its own.  On one GPU there are no transfers, and the
+ * expert GEMMs of one chunk leave the HBM-bound work of another little room: in one piece the same
+ * forward is 4 to 27 % faster.  The result is that of the four calls made per chunk: every chunk has
+ * its own packed layout.
  *
  * moe_pipeline_create: cfg as for moe_create with cfg->T_max = most tokens of one call;
  * 1 <= n_chunks <= 64, 1 <= n_streams <= 8 (streams of default priority, created here).
