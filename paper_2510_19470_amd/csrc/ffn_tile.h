@@ -35,6 +35,11 @@ __device__ __forceinline__ void dma16(uint32_t off, const char* base, uint32_t l
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
                : "memory", "m0");
 }
+// The same copy of data that is read once: it does not displace what the last-level cache holds.
+__device__ __forceinline__ void dma16_once(uint32_t off, const char* base, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds_addr)
+               : "memory", "m0");
+}
 // The same copy with a 64-bit address per lane (k-steps that end inside the operand's rows:
 // the lanes past the end read zeros from elsewhere).
 __device__ __forceinline__ void dma16v(const char* src, uint32_t lds_addr) {
