@@ -67,10 +67,14 @@ struct WgradArgs {
 };
 
 // A wavefront's 128 x 64 of dW from (m0, n0): a lane holds column (lane & 31) of each 32-column block and
-// the rows 8g + 4(lane >> 5) + {0..3} of each 32-row block.
-template <bool RAG>
+// the rows 8g + 4(lane >> 5) + {0..3} of each 32-row block.  The gradients are the call's largest array, and the
+// dX GEMM after this launch reads the weights and [dG|dU]: stores past the last-level cache leave those in it
+// (training step, us: 6190 rows, 2048 x 2048, 302 MB of gradients: 782 -> 768; two-matrix, 64 rows per expert of
+// 1024 x 4096, 268 MB: 197 -> 190; 2048 tokens, 1024 x 1024, 75 MB: 174 -> 171).  Only where the 32 columns of a store are
+// a 128-byte line: pieces of lines lose (1160 x 2888: 291 -> 296; 648 x 1400: 243 -> 248).
+template <bool RAG, bool LINES>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][4], float* dW, int m0, int n0, int Mo, int No,
-                                           int lane) {
+                                              int lane) {
   const int col = lane & 31, half = lane >> 5;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -82,14 +86,16 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][4], float* dW,
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const int n = n0 + j * 32 + col;
-          if (!RAG || (m < Mo && n < No)) dW[(size_t)m * No + n] = acc[j][i][g * 4 + r];
+          if (RAG && (m >= Mo || n >= No)) continue;
+          if (LINES) __builtin_nontemporal_store(acc[j][i][g * 4 + r], dW + (size_t)m * No + n);
+          else dW[(size_t)m * No + n] = acc[j][i][g * 4 + r];
         }
       }
 }
-
 // RAG: some last block is not whole (d or f no multiple of 256): columns are clamped and guarded.
-// A kernel of its own, so that whole sizes do not pay for the guards of the stores.
-template <bool RAG>
+// A kernel of its own, so that whole sizes do not pay for the guards of the stores.  LINES: see store_tile
+// (a template argument: of two ways to store in one kernel the compiler makes one, the plain one).
+template <bool RAG, bool LINES>
 __global__ __launch_bounds__(NT) void wgrad_tr_kernel(const WgradArgs p) {
   __shared__ uint4 lds[SLOTS * SLOT_BYTES / 16];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -218,7 +224,7 @@ __global__ __launch_bounds__(NT) void wgrad_tr_kernel(const WgradArgs p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no copy in flight into LDS at exit
   }
 
-  store_tile<RAG>(acc, dW, mblk * 256 + wm * 128, nblk * 256 + wn * 64, J.Mo, J.No, lane);
+  store_tile<RAG, LINES>(acc, dW, mblk * 256 + wm * 128, nblk * 256 + wn * 64, J.Mo, J.No, lane);
 }
 
 // The same for few rows per expert, where a block's start (its expert, counts and first copies: three cold
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(NT) void wgrad_tr_kernel(const WgradArgs p) {
 // on a compute unit, so that one starts or stores while the other computes; one barrier per half-step.
 // 64 rows, 8 experts, 1024 x 4096: 88 -> 77 us (403 MB written); 250 rows, 6 experts, 1160 x 2888: 91 -> 95;
 // 1032 rows, 2048 x 2048: 203 -> 204 to 209 (half as much work per byte copied).
-template <bool RAG>
+template <bool RAG, bool LINES>
 __global__ __launch_bounds__(F_NT, 2) void wgrad_few_kernel(const WgradArgs p) {
   __shared__ uint4 lds[F_STAGES * F_STAGE_BYTES / 16];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(F_NT, 2) void wgrad_few_kernel(const WgradArgs p) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy in flight into LDS at exit
   }
-  store_tile<RAG>(acc, dW, mblk * 256 + wm * 128, nblk * F_BN + wn * 64, J.Mo, J.No, lane);
+  store_tile<RAG, LINES>(acc, dW, mblk * 256 + wm * 128, nblk * F_BN + wn * 64, J.Mo, J.No, lane);
 }
 
 }  // namespace
@@ -398,18 +404,22 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
   //   2048 x 1408, 12 of 64: 212 -> 207, 237 -> 233, 262 -> 261, 286 -> 288; 277 -> 278, 327 -> 326, 408 -> 415,
   //   551 -> 557
   const bool few = c->wgrad_rows != 0 ? c->wgrad_rows == 128 : c->S_call <= 128 * E;
-  const bool rag = d % 256 != 0 || f % 256 != 0;
+  // whole lines to store (store_tile), by the sizes and by where the gradients lie
+  bool lines = d % 32 == 0 && f % 32 == 0;
+  for (int i = 0; i < a.n_list; ++i)
+    for (int w = 3; w < 6; ++w) lines &= ((uintptr_t)c->h_wtab[w][a.list[i]] & 127) == 0;
+  const bool rag = d % 256 != 0 || f % 256 != 0 || !lines;
   if (few) {
     auto tiles = [](int m, int n) { return ((m + 255) / 256) * ((n + F_BN - 1) / F_BN); };
     const int total = a.n_list * (tiles(d, f) + (a.n_jobs - 1) * tiles(f, d));
     const dim3 grid((total + 511) / 512 * 512);
-    if (rag) hipLaunchKernelGGL((wgrad_few_kernel<true>), grid, dim3(F_NT), 0, s, a);
-    else hipLaunchKernelGGL((wgrad_few_kernel<false>), grid, dim3(F_NT), 0, s, a);
+    auto kern = !rag ? wgrad_few_kernel<false, true> : lines ? wgrad_few_kernel<true, true> : wgrad_few_kernel<true, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(F_NT), 0, s, a);
   } else {
     const int total = a.n_jobs * a.n_list * ((d + 255) / 256) * ((f + 255) / 256);
     const dim3 grid((total + 255) / 256 * 256);
-    if (rag) hipLaunchKernelGGL((wgrad_tr_kernel<true>), grid, dim3(NT), 0, s, a);
-    else hipLaunchKernelGGL((wgrad_tr_kernel<false>), grid, dim3(NT), 0, s, a);
+    auto kern = !rag ? wgrad_tr_kernel<false, true> : lines ? wgrad_tr_kernel<true, true> : wgrad_tr_kernel<true, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(NT), 0, s, a);
   }
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }

@@ -119,3 +119,34 @@ def test_counts_that_do_not_fit_compute_nothing(tile):
         assert torch.all(y == 3.0) and torch.all(dxp == 5.0)
         assert all(torch.all(w == 0) for w in dW1 + dW2)
     lay.close()
+
+
+@pytest.mark.parametrize("few", [128, 256])
+@pytest.mark.parametrize("d,f", [(256, 512), (288, 352), (264, 520)])   # whole tiles; whole lines; neither
+def test_weight_gradients_wherever_they_lie(d, f, few):
+    """Gradients that begin inside a 128-byte line are stored by another kernel: the same bits, and nothing
+    beside them is written."""
+    from gpu_common import DEV, moe, to_device, layer_from_inputs
+    E, k, T = 3, 2, 100
+    cfg = wl.MoEConfig("lines", 5, "bf16", T=T, d=d, E=E, k=k, f=f, R=1)
+    inp = wl.make_inputs(cfg)
+    lay = layer_from_inputs(inp)
+    moe.load_library().moe_internal_wgrad_rows(lay.ctx.handle, few)
+    rng = np.random.default_rng(d)
+    xp, dy = (to_device(wl.store(rng.standard_normal((T * k, d)).astype(np.float32), "bf16"), "bf16") for _ in range(2))
+    cnt = torch.tensor([90, 33, 77], dtype=torch.int32, device=DEV)
+    off = torch.tensor([0, 90, 123], dtype=torch.int32, device=DEV)
+    y, G, U = moe.moe_expert_ffn(lay.ctx, xp, cnt, off, lay.W1, lay.W3, lay.W2, save=True)
+
+    def grads(shift):   # [E] views, `shift` floats into a 128-byte line, and the buffers they lie in
+        flat = [torch.full((rows * cols + 64,), 7.0, device=DEV) for rows, cols in ((f, d), (f, d), (d, f)) for _ in range(E)]
+        views = [b[shift:shift + f * d].view(*((d, f) if i >= 2 * E else (f, d))) for i, b in enumerate(flat)]
+        moe.moe_expert_ffn_bwd(lay.ctx, dy, xp, G, U, cnt, off, lay.W1, lay.W3, lay.W2, dW1=views[:E],
+                               dW3=views[E:2 * E], dW2=views[2 * E:])
+        torch.cuda.synchronize()
+        assert all(torch.all(b[:shift] == 7.0) and torch.all(b[shift + f * d:] == 7.0) for b in flat)
+        return views
+
+    for a, b in zip(grads(0), grads(4)):
+        assert torch.equal(a, b)
+    lay.close()
