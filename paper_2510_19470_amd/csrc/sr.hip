@@ -185,11 +185,18 @@ struct SrLane {
   static constexpr int V = 16 / (int)sizeof(T);
   static constexpr int NV = SR_PER_THREAD / V;
   uint4 w[NV], s[NV];
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   __device__ __forceinline__ static int64_t first(int64_t c, int v) {
     return c * SR_CHUNK + v * (SR_THREADS * V) + (int)threadIdx.x * V;
   }
+  // ONCE: past the last-level cache (see sr_once)
+  template <bool ONCE = false>
   __device__ __forceinline__ static uint4 load_vec(const T* __restrict__ p, int64_t i, int64_t n) {
-    if (i + V <= n) return *reinterpret_cast<const uint4*>(p + i);
+    if (i + V <= n) {
+      const u32x4* q = reinterpret_cast<const u32x4*>(p + i);
+      const u32x4 r = ONCE ? __builtin_nontemporal_load(q) : *q;
+      return make_uint4(r.x, r.y, r.z, r.w);
+    }
     T e[V];   // the end of the array
 #pragma unroll
     for (int j = 0; j < V; ++j) e[j] = i + j < n ? p[i + j] : T(0);
@@ -197,12 +204,13 @@ struct SrLane {
     __builtin_memcpy(&q, e, 16);
     return q;
   }
+  template <bool ONCE = false>
   __device__ __forceinline__ void load(const T* __restrict__ W, const T* __restrict__ S, int64_t c,
                                        int64_t n) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) w[v] = load_vec(W, first(c, v), n);
+    for (int v = 0; v < NV; ++v) w[v] = load_vec<ONCE>(W, first(c, v), n);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) s[v] = load_vec(S, first(c, v), n);
+    for (int v = 0; v < NV; ++v) s[v] = load_vec<ONCE>(S, first(c, v), n);
   }
   __device__ __forceinline__ void residual(int v, float (&r)[V]) const {
     float a[V], b[V];
@@ -324,7 +332,7 @@ __device__ __forceinline__ uint32_t pick_b_lo(const int32_t* __restrict__ hist, 
 }
 
 // ---- step 2.
-template <typename T>
+template <typename T, bool ONCE>
 __global__ __launch_bounds__(SR_THREADS) void sr_compact_kernel(
     const T* __restrict__ W, const T* __restrict__ S, int64_t n, int64_t k, int64_t rate,
     int64_t n_sample, SrState* __restrict__ st, int32_t* __restrict__ hists, SrDeal deal,
@@ -336,7 +344,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_compact_kernel(
   __shared__ typename Scan::word wsum[2][SR_WAVES];
   const int64_t n_chunks = (n + SR_CHUNK - 1) / SR_CHUNK;
   Lane cur;
-  if ((int64_t)blockIdx.x < n_chunks) cur.load(W, S, blockIdx.x, n);
+  if ((int64_t)blockIdx.x < n_chunks) cur.template load<ONCE>(W, S, blockIdx.x, n);
   static_assert(SR_LIST_BINS == SR_THREADS, "a bin per thread");
   h[threadIdx.x] = 0;
   const uint32_t b_lo = pick_b_lo(hists + H_SAMPLE * SR_HIST, n, k, rate, n_sample * (8 * V));
@@ -348,7 +356,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_compact_kernel(
   int slot = 0;
   for (int64_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
     Lane nxt = cur;
-    if (c + gridDim.x < n_chunks) nxt.load(W, S, c + gridDim.x, n);   // in flight meanwhile
+    if (c + gridDim.x < n_chunks) nxt.template load<ONCE>(W, S, c + gridDim.x, n);   // in flight meanwhile
     uint32_t sel = 0;   // bit j = v * V + e
     typename Scan::word mine = 0;
 #pragma unroll
@@ -816,7 +824,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_emit_stream_kernel(
 // it requests its piece of the shared expert first, finds the chunk's contiguous piece of the
 // ascending list with a 64-wide search while those loads are in flight, puts the values into LDS
 // with a bit per element (untouched elements keep the shared expert's exact bits), and writes.
-template <typename T>
+template <typename T, bool ONCE>
 __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
     const T* __restrict__ S, const T* __restrict__ values, const int32_t* __restrict__ indices,
     int64_t n, int64_t k, T* __restrict__ out) {
@@ -828,7 +836,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
   const int64_t c = blockIdx.x, start = c * SR_CHUNK, end = min(n, start + SR_CHUNK);
   uint4 q[NV];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) q[v] = Lane::load_vec(S, Lane::first(c, v), n);
+  for (int v = 0; v < NV; ++v) q[v] = Lane::template load_vec<ONCE>(S, Lane::first(c, v), n);
   if (threadIdx.x < 128) {   // lower_bound of start (wavefront 0) / end (wavefront 1), 64 probes
                              // per round (4 rounds for a million entries)
     const int lane = threadIdx.x & 63;
@@ -872,8 +880,10 @@ __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
     }
     const int64_t i0 = start + l0;
     if (i0 + V <= n) {
-      __builtin_memcpy(&q[v], o, 16);
-      *reinterpret_cast<uint4*>(out + i0) = q[v];
+      typename Lane::u32x4 r;
+      __builtin_memcpy(&r, o, 16);
+      if (ONCE) __builtin_nontemporal_store(r, reinterpret_cast<typename Lane::u32x4*>(out + i0));
+      else *reinterpret_cast<typename Lane::u32x4*>(out + i0) = r;
     } else {
 #pragma unroll
       for (int e = 0; e < V; ++e)
@@ -881,6 +891,12 @@ __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
     }
   }
 }
+
+// Matrices that are read and written past the last-level cache (256 MB): where the encode's two do not leave
+// room in it for anything else, their next reader does not find them there either.  Encode and decode, us,
+// plain -> past the cache: 117 MB a matrix 139.5 -> 129.7, 235 MB (fp32, k = n / 10) 474 -> 451, 42 MB 80.1 -> 76.9;
+// 17 MB, three matrices in turn, which the cache holds: 41.7 -> 42.0.
+bool sr_once(int64_t n, size_t elem) { return 2 * n * (int64_t)elem >= (int64_t)64 << 20; }
 
 // blocks of the launches that deal chunks out: two per compute unit
 int64_t sr_list_blocks(int64_t n_chunks, int n_cu) { return std::min<int64_t>(n_chunks, 2 * (int64_t)n_cu); }
@@ -919,16 +935,26 @@ int encode_t(moe_ctx* c, const T* W, const T* S, int64_t n, int64_t k, T* values
   // chunks per block of the emit steps: four blocks per compute unit, at most SR_EMIT_MAX chunks each
   const int per = (int)std::max<int64_t>(1, std::min<int64_t>(SR_EMIT_MAX, (n_chunks + cu * 4 - 1) / (cu * 4)));
   const dim3 g_emit((unsigned)((n_chunks + per - 1) / per));
-#define SR_LAUNCH(kern, g, ...) hipLaunchKernelGGL((kern<T>), g, dim3(SR_THREADS), 0, s, __VA_ARGS__)
+#define SR_LAUNCH_AS(kern, g, ...) hipLaunchKernelGGL(kern, g, dim3(SR_THREADS), 0, s, __VA_ARGS__)
+#define SR_LAUNCH(kern, g, ...) SR_LAUNCH_AS((kern<T>), g, __VA_ARGS__)
   SR_LAUNCH(sr_sample_kernel, g_sample, W, S, rate, n_sample, hists + H_SAMPLE * SR_HIST);
-  SR_LAUNCH(sr_compact_kernel, g_list, W, S, n, k, rate, n_sample, st, hists, deal, list, run_start,
-            run_cnt);
+  SR_LAUNCH_AS((sr_once(n, sizeof(T)) ? sr_compact_kernel<T, true> : sr_compact_kernel<T, false>), g_list, W, S, n, k,
+               rate, n_sample, st, hists, deal, list, run_start, run_cnt);
   SR_LAUNCH(sr_fine_kernel, g_list, W, S, n, k, st, hists, coarse, fine, list, run_start, run_cnt);
   SR_LAUNCH(sr_count_kernel, g_list, W, S, n, k, st, hists, coarse, fine, cnt, list, run_start, run_cnt);
   SR_LAUNCH(sr_emit_kernel, g_emit, W, S, n, st, coarse, fine, cnt, per, k, values, indices, list,
             run_start, run_cnt);
   SR_LAUNCH(sr_emit_stream_kernel, g_emit, W, S, n, st, hists, cnt, per, k, values, indices);
 #undef SR_LAUNCH
+#undef SR_LAUNCH_AS
+  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+}
+
+template <typename T>
+int decode_t(const T* S, const T* values, const int32_t* indices, int64_t n, int64_t k, T* out, hipStream_t s) {
+  const dim3 grid((unsigned)((n + SR_CHUNK - 1) / SR_CHUNK));
+  auto kern = sr_once(n, sizeof(T)) ? sr_decode_kernel<T, true> : sr_decode_kernel<T, false>;
+  hipLaunchKernelGGL(kern, grid, dim3(SR_THREADS), 0, s, S, values, indices, n, k, out);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 
@@ -972,12 +998,7 @@ int launch_sr_encode(moe_ctx* c, const void* W, const void* S, int64_t n, int64_
 
 int launch_sr_decode(moe_ctx* c, const void* S, const void* values, const int32_t* indices,
                      int64_t n, int64_t k, void* out, hipStream_t s) {
-  const dim3 grid((unsigned)((n + SR_CHUNK - 1) / SR_CHUNK));
   if (c->cfg.dtype == MOE_BF16)
-    hipLaunchKernelGGL((sr_decode_kernel<uint16_t>), grid, dim3(SR_THREADS), 0, s,
-                       (const uint16_t*)S, (const uint16_t*)values, indices, n, k, (uint16_t*)out);
-  else
-    hipLaunchKernelGGL((sr_decode_kernel<float>), grid, dim3(SR_THREADS), 0, s,
-                       (const float*)S, (const float*)values, indices, n, k, (float*)out);
-  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+    return decode_t<uint16_t>((const uint16_t*)S, (const uint16_t*)values, indices, n, k, (uint16_t*)out, s);
+  return decode_t<float>((const float*)S, (const float*)values, indices, n, k, (float*)out, s);
 }

@@ -283,3 +283,29 @@ def test_migrated_expert_arrives_compressed_and_is_computed():
         done[off[q]:off[q] + cnt[q]] = True
     assert nerr(to_host_f32(y)[done], yo[done]) <= TOL["bf16"]
     lay.close()
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 1 << 24), ("bf16", (1 << 24) - 8), ("f32", (1 << 23) + 3)])
+def test_matrices_past_the_cache(dtype, n):
+    """Two matrices of 64 MB and more are read and written by kernels of their own: against torch's selection."""
+    ctx = _ctx(dtype)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    shared = torch.randn(n, device="cuda", generator=g).to(dt)
+    expert = (shared.float() + 0.1 * torch.randn(n, device="cuda", generator=g)).to(dt)
+    k = n // 40
+    vals, idx = moe.moe_sr_encode(ctx, expert, shared, k)
+    out = moe.moe_sr_decode(ctx, shared, vals, idx)
+    r = expert.float() - shared.float()
+    key = r.abs()
+    thr = key.kthvalue(n - k + 1).values if dtype == "f32" else key.sort().values[n - k]
+    keep = key > thr
+    ties = torch.nonzero(key == thr).flatten()[:k - int(keep.sum())]   # lower indices first
+    keep[ties] = True
+    want = torch.nonzero(keep).flatten()
+    assert torch.equal(idx.long(), want)
+    assert torch.equal(vals, r[want].to(dt))
+    ref = shared.clone()
+    ref[want] = (shared[want].float() + vals.float()).to(dt)
+    assert torch.equal(out, ref)
+    moe.moe_destroy(ctx)
