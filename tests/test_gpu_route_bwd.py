@@ -88,6 +88,7 @@ def test_determinism_and_empty():
     ("bf16", 131, 136, 17, 3),   # a second chunk of 3 tokens, second column block, second expert group
     ("bf16", 163, 1160, 65, 6),  # steps of 32 tokens and single ones; experts of a second lane group
     ("bf16", 40, 256, 256, 8),   # as many experts as there can be
+    ("bf16", 70, 1032, 40, 12),  # more than eight experts of a token, two pieces of a row and a bit
     ("f32", 33, 72, 16, 2),      # 64 columns a wavefront
     ("f32", 130, 520, 200, 4),
 ])
