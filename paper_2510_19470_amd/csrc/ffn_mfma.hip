@@ -209,6 +209,9 @@ __device__ __forceinline__ Unit fetch_unit(const GemmArgs& p, int idx) {
 // reads; two copies, base + offset each, into the rows read one cluster ago), then the
 // compute cluster.
 //
+// both: the second 128 columns of the column block hold any (RAG; in gate/up they are W3's rows).  Where a last
+// column block has none there, they are not multiplied (training step of 2048 x 1408, dH: 1415 -> 1411 us; leaving out
+// their fragment reads as well made two versions of the loop, which spilled).
 // na: token blocks of the copies' target that are copied at all (4 unless the target is lean, see
 // the kernel).  WAIT: copies that may be outstanding at the end of the memory cluster, or < 0: 3
 // where `strict`, else 6.
@@ -218,8 +221,8 @@ __device__ __forceinline__ void pp_cluster(f32x16 (&acc)[2][4], bf16x8 (&wb)[2][
                                            const int (&fr_b)[2], int fr_half, int fr_swz,
                                            uint32_t offa, const Src& srca, uint32_t offb,
                                            const Src& srcb, uint32_t a_dst, uint32_t b_dst,
-                                           int nact, int na, bool strict, int lc, int brow,
-                                           const char* zero) {
+                                           int nact, int na, bool both, bool strict, int lc,
+                                           int brow, const char* zero) {
   const uint4* As = lds + (2 * S) * STAGE_VEC;
   const uint4* Bs = lds + (2 * S + 1) * STAGE_VEC;
   bf16x8 xa[4];
@@ -268,12 +271,20 @@ __device__ __forceinline__ void pp_cluster(f32x16 (&acc)[2][4], bf16x8 (&wb)[2][
   asm volatile("s_barrier" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_setprio(1);
-  if (act) {
+  if (act && !RAG) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         acc[j][I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb[j][kk], xa[kk], acc[j][I], 0, 0, 0);
+  } else if (act) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      acc[0][I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb[0][kk], xa[kk], acc[0][I], 0, 0, 0);
+    if (both)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        acc[1][I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb[1][kk], xa[kk], acc[1][I], 0, 0, 0);
   }
   __builtin_amdgcn_s_setprio(0);
   __builtin_amdgcn_sched_barrier(0);
@@ -465,12 +476,13 @@ __global__ __launch_bounds__(NT) void ffn_mfma_kernel(const GemmArgs p) {
     const int KT = cur.KT;
     const int nact = active(cur), nact_n = nxt.valid ? active(nxt) : nact;
     const bool lean = nact <= 1, lean_n = nact_n <= 1;
+    const bool both = MODE == MODE_UP || cur.nblk * 256 + 128 < p.N;
     // steady part: steps 0 .. KT-3; what was read one cluster ago is refilled with the data
     // of its next use (token block i-1 and weight row blocks 8(i-1)+wave of this stage with
     // step k+2; at i == 0 block 3 of the other stage with step k+1)
 #define PP(S, I, OA, BA, OB, BB, NA, NC, W)                                                      \
   pp_cluster<S, I, BKM, RAG, W>(acc, wb, lds, fr_a, fr_b, fr_half, fr_swz, OA, BA, OB, BB,       \
-                                a_dst, b_dst, NA, NC, lean || lean_n, lc, brow, p.zero)
+                                a_dst, b_dst, NA, NC, both, lean || lean_n, lc, brow, p.zero)
 #define STEADY(W)                                                                                \
   for (int kt = 0; kt < KT - 2; kt += 2) {                                                       \
     const Src a1 = asrc(cur, kt + 1), a2 = asrc(cur, kt + 2), a3 = asrc(cur, kt + 3);            \
