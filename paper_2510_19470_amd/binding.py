@@ -129,14 +129,23 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device.  Without the Stream object that
+    torch.cuda.current_stream() builds: 2.9 -> 0.3 us a call, of about 10 us that the host takes
+    for one (a pass of four calls on one token: 41 -> 31 us)."""
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch._C._cuda_getDevice())
 
 
 def _table(ts: Sequence[Optional[torch.Tensor]]):
     arr = (c_void_p * len(ts))()
     for i, t in enumerate(ts):
-        arr[i] = _ptr(t)
+        if t is not None:
+            arr[i] = _ptr(t)
     return arr
 
 
