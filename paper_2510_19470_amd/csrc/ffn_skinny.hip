@@ -3,7 +3,7 @@
 // What bounds it is reading every weight of the used experts once.  The 256-row tiles of
 // ffn_mfma_kernel serve that badly where few experts are used: one block per 128 to 256 weight
 // rows leaves compute units idle and needs a K-split with partial sums through memory, and a
-// tile list has to be built first.  Here a block takes 16 weight rows (16 of W1 and the same 16
+// tile list has to be built first.  Here a block takes 16 or 32 weight rows (of W1 and the same ones
 // of W3 for gate/up), its 8 wavefronts cut the contraction among themselves in units of 64 (one
 // 128-byte line per weight row), and nothing is staged: a weight fragment is one 16-byte load per
 // lane, used for all of the expert's rows, and the wavefronts' sums meet in LDS (added in
@@ -24,7 +24,7 @@ constexpr int NW = NT / 64;
 
 enum { SK_UP = 0, SK_UP1 = 1, SK_DOWN = 2 };
 
-constexpr int WROWS = 16;    // weight rows (output columns) of a block
+constexpr int WROWS = 16;    // weight rows (output columns) of a fragment
 constexpr int GROUPS = 4;    // groups of 16 token rows that one pass over the weights serves
 
 struct SkinnyArgs {
@@ -107,18 +107,19 @@ __device__ __forceinline__ uint2 pack4(const f32x4& v) {
   return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
 }
 
-// One pass over the block's weight rows for `rows` (1 .. 16 G) token rows from packed row `row0`.
-template <int MODE, int G>
+// One pass over the block's weight rows (WG groups of 16) for `rows` (1 .. 16 G) token rows from packed row `row0`.
+template <int MODE, int G, int WG>
 __device__ __forceinline__ void skinny_pass(const SkinnyArgs& p, const void* b0, const void* b1,
                                             size_t row0, int rows, f32x4* red) {
-  constexpr int NF = MODE == SK_UP ? 2 : 1;
+  constexpr int NM = MODE == SK_UP ? 2 : 1, NF = NM * WG;   // fragment f: matrix f % NM, row group f / NM
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * WROWS;
-  const size_t wrow = min(n0 + (lane & 15), p.N - 1);   // past the matrix: not stored
+  const int n0 = blockIdx.x * (WROWS * WG);
   const uint4* w[NF];
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
-    w[f] = reinterpret_cast<const uint4*>((const uint16_t*)(f == 0 ? b0 : b1) + wrow * p.K);
+  for (int f = 0; f < NF; ++f) {
+    const size_t wrow = min(n0 + f / NM * WROWS + (lane & 15), p.N - 1);   // past the matrix: not stored
+    w[f] = reinterpret_cast<const uint4*>((const uint16_t*)(f % NM == 0 ? b0 : b1) + wrow * p.K);
+  }
   const uint4* x[G];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -134,17 +135,18 @@ __device__ __forceinline__ void skinny_pass(const SkinnyArgs& p, const void* b0,
 #pragma unroll
     for (int g = 0; g < G; ++g) red[((wave * NF + f) * G + g) * 64 + lane] = acc[f][g];
   __syncthreads();
-  // wavefront g finishes token group g: a lane holds token lane & 15, 4 consecutive columns
-  if (wave < G) {
+  // wavefront g finishes token group g % G of row group g / G: a lane holds token lane & 15, 4 consecutive columns
+  if (wave < G * WG) {
+    const int tg = wave % G, wg = wave / G;
     f32x4 s[2];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const f32x4* part = red + (f * G + wave) * 64 + lane;
-      s[f] = part[0];
+    for (int m = 0; m < NM; ++m) {
+      const f32x4* part = red + ((wg * NM + m) * G + tg) * 64 + lane;
+      s[m] = part[0];
 #pragma unroll
-      for (int v = 1; v < NW; ++v) s[f] += part[v * NF * G * 64];
+      for (int v = 1; v < NW; ++v) s[m] += part[v * NF * G * 64];
     }
-    const int r = wave * 16 + (lane & 15), col = n0 + 4 * (lane >> 4);
+    const int r = tg * 16 + (lane & 15), col = n0 + wg * WROWS + 4 * (lane >> 4);
     if (r < rows && col < p.N) {   // N is a multiple of 8: the four columns exist or do not
       const size_t o = (row0 + r) * p.N + col;
       if (MODE != SK_DOWN && p.Gs != nullptr) {
@@ -163,11 +165,11 @@ __device__ __forceinline__ void skinny_pass(const SkinnyArgs& p, const void* b0,
   __syncthreads();   // `red` is free for the next pass
 }
 
-// Block (x: 16 output columns, y: expert of the list).  128 registers: two blocks per compute
+// Block (x: 16 WG output columns, y: expert of the list).  128 registers: two blocks per compute
 // unit, 16 wavefronts with 4 to 16 KB of weights in flight each.
-template <int MODE>
+template <int MODE, int WG>
 __global__ __launch_bounds__(NT, 4) void ffn_skinny_kernel(const SkinnyArgs p) {
-  __shared__ f32x4 red[NW * (MODE == SK_UP ? 2 : 1) * GROUPS * 64];
+  __shared__ f32x4 red[NW * (MODE == SK_UP ? 2 : 1) * (WG > 1 ? WG : GROUPS) * 64];
   // counts and offsets are the caller's: nothing is computed unless every segment fits the
   // buffers (the rule of the tile schedule)
   int bad = 0;
@@ -180,19 +182,33 @@ __global__ __launch_bounds__(NT, 4) void ffn_skinny_kernel(const SkinnyArgs p) {
   const void* b0 = p.B0[e];
   if (__syncthreads_or(bad) || b0 == nullptr) return;
   const void* b1 = MODE == SK_UP ? p.B1[e] : nullptr;
+  if (WG > 1) {   // calls of at most 16 tokens: one pass, unless the caller's counts have a token twice
+    for (int r = 0; r < n_e; r += 16) skinny_pass<MODE, 1, WG>(p, b0, b1, (size_t)row0 + r, min(16, n_e - r), red);
+    return;
+  }
   for (int r = 0; r < n_e; r += 16 * GROUPS) {
     const int rows = min(16 * GROUPS, n_e - r);
     const size_t first = (size_t)row0 + r;
-    if (rows <= 16) skinny_pass<MODE, 1>(p, b0, b1, first, rows, red);
-    else if (rows <= 32) skinny_pass<MODE, 2>(p, b0, b1, first, rows, red);
-    else skinny_pass<MODE, GROUPS>(p, b0, b1, first, rows, red);
+    if (rows <= 16) skinny_pass<MODE, 1, 1>(p, b0, b1, first, rows, red);
+    else if (rows <= 32) skinny_pass<MODE, 2, 1>(p, b0, b1, first, rows, red);
+    else skinny_pass<MODE, GROUPS, 1>(p, b0, b1, first, rows, red);
   }
 }
 
 template <int MODE>
-int launch(const SkinnyArgs& a, hipStream_t s) {
+int launch(const SkinnyArgs& a, int T, hipStream_t s) {
+  // A wavefront has K / 512 units: with four or less it asks for all of them at once, and a block that takes 32
+  // weight rows has twice as much in flight behind one start (kernel arguments, counts, sums).  16 rows -> 32,
+  // pass, us: d = 1024, f = 4096, T = 8: 38.5 -> 37.2, T = 16 on 16 experts: 97.2 -> 93.3; d = 2048, f = 1408, T = 16:
+  // 75.1 -> 72.7; two-matrix, 1536 x 3072: 47.2 -> 45.7.  With longer rows there are too few blocks (up to K =
+  // 4096: 38.6 -> 40.4, 78 -> 86), and with more token rows too few registers.
+  if (T <= 16 && a.K <= 2048) {
+    const dim3 grid((a.N + 2 * WROWS - 1) / (2 * WROWS), a.n_list);
+    hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 2>), grid, dim3(NT), 0, s, a);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+  }
   const dim3 grid((a.N + WROWS - 1) / WROWS, a.n_list);
-  hipLaunchKernelGGL((ffn_skinny_kernel<MODE>), grid, dim3(NT), 0, s, a);
+  hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 1>), grid, dim3(NT), 0, s, a);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 
@@ -285,7 +301,7 @@ int launch_ffn_skinny(moe_ctx* c, bool gated, const int32_t* counts, const int32
     a.Us = (uint16_t*)U;
     a.K = c->cfg.d;
     a.N = c->cfg.f;
-    const int st = gated ? launch<SK_UP>(a, s) : launch<SK_UP1>(a, s);
+    const int st = gated ? launch<SK_UP>(a, c->S_call / c->cfg.k, s) : launch<SK_UP1>(a, c->S_call / c->cfg.k, s);
     if (st != MOE_OK) return st;
   }
   prof_mark(c, 2, s);
@@ -297,7 +313,7 @@ int launch_ffn_skinny(moe_ctx* c, bool gated, const int32_t* counts, const int32
     a.Gs = a.Us = nullptr;
     a.K = c->cfg.f;
     a.N = c->cfg.d;
-    const int st = launch<SK_DOWN>(a, s);
+    const int st = launch<SK_DOWN>(a, c->S_call / c->cfg.k, s);
     if (st != MOE_OK) return st;
   }
   prof_mark(c, 3, s);
