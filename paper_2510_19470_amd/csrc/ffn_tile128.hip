@@ -14,8 +14,7 @@
 // 32-row blocks that hold no rows are neither copied nor multiplied.
 // No schedule launch: every block counts the tiles from the counts (one scan over the experts) and finds
 // its own by a search.  A contraction is cut into parts only where there are tiles for at most half of
-// the resident blocks; the parts' sums (fp32, existing rows only) are added by a second kernel in a
-// fixed order.
+// the resident blocks; the blocks add the parts themselves (join_parts).
 #include <algorithm>
 
 #include "ffn_tile.h"
@@ -27,7 +26,7 @@ constexpr int TN = 128;          // weight rows per tile (gate/up: 64 of each ma
 constexpr int NT = 256;          // threads
 constexpr int OPERAND = TM * BK * 2;      // bytes of an operand's part of a stage
 constexpr int STAGE = 2 * OPERAND;
-constexpr int SPLIT_MAX = 8;     // parts of a contraction at most
+constexpr int SPLIT_MAX = JOIN_PARTS;
 constexpr int SPLIT_STEPS = 4;   // k-steps of a part at least
 constexpr int ORDER_GROUP_M = 8; // row blocks per group of the tile order
 
@@ -87,18 +86,34 @@ __device__ __forceinline__ int count_tiles(const TileArgs& p, TileMap& m) {
   return any_bad || total > p.S / TM + p.E ? 0 : total;   // (segments that overlap)
 }
 
-// Parts of every contraction of a launch of `tiles` tiles on `slots` resident blocks.
+// Parts of every contraction of a launch of `tiles` tiles on `slots` resident blocks, two on a compute unit: the
+// number that is done first by its k-steps, each 2.3 times as long where there are units with two blocks, and a
+// level of neighbours that add their sums (join_parts) counted as 3.5 of them.  Kernel time, us, 1, 2, 3, 4 ... 8
+// parts (behind the semicolon units have two blocks): 64 tiles of 64 steps 44, 28, 23, 22; 28, 28, 29, 29; 48 of 32:
+// 24, 18, 17, 16, 18; 20, 21, 22; 96 of 16: 16, 15; 17, 21; 120 of 46: 44, 31; 40, 41; 140 of 46: 44; 49, 41; 168 of 64:
+// 52; 52, 43; 192 of 22: 24; 29, of 64: 56; 57.  Pass, us, as many parts as there are blocks for -> these: two-matrix
+// step, 64 rows, 1024 x 4096: 195 -> 179; step of 2048 tokens, 1024 x 1024: 172 -> 155; step, 125 rows, 1160 x 2888:
+// 294 -> 270.
+__host__ __device__ inline int join_levels(int parts) { return parts > 4 ? 3 : parts > 2 ? 2 : parts - 1; }
 __host__ __device__ inline int parts_of(int tiles, int slots, int kt) {
-  int split = 1;
-  while (tiles > 0 && split < SPLIT_MAX && tiles * (split + 1) <= slots && kt / (split + 1) >= SPLIT_STEPS) ++split;
-  return split;
+  auto best = [&](int most, float two) {
+    const int one_each = slots / 2 > SPLIT_MAX ? slots / 2 : SPLIT_MAX;
+    int parts = 1;
+    float least = (float)kt;
+    for (int n = 2; n <= most && tiles * n <= slots && kt / n >= SPLIT_STEPS; ++n) {
+      const float t = (float)((kt + n - 1) / n) * (tiles * n <= one_each ? 1.f : two) + 3.5f * join_levels(n);
+      if (t < least) least = t, parts = n;
+    }
+    return parts;
+  };
+  return best(best(SPLIT_MAX, 1.f), 2.3f);   // no more than of one tile alone: the workspace is sized for those
 }
 
 // One tile, or one part of its contraction (all fields wave-uniform).
 struct Unit128 {
   int valid, expert, row0, rows, nblk;
   int kstart, KT;          // first k-step and their number
-  int ws_unit;             // >= 0: index of the partial tile in the workspace
+  int tile, part, parts;   // index in the order; parts > 1: this is one of them
   int once;                // the expert's only row block: nobody else reads these weights
 };
 
@@ -125,7 +140,9 @@ __device__ __forceinline__ Unit128 find_tile(const TileArgs& p, const TileMap& m
   u.rows = min(TM, __builtin_amdgcn_readfirstlane(m.rows[lo]) - mb * TM);
   u.kstart = 0;
   u.KT = p.g.kt;
-  u.ws_unit = -1;
+  u.tile = L;
+  u.part = 0;
+  u.parts = 1;
   u.once = me == 1;
   return u;
 }
@@ -136,16 +153,16 @@ template <int MODE, bool BKM>
 __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
   __shared__ uint4 lds[2 * STAGE / 16];
   __shared__ TileMap map;
+  __shared__ int32_t join_flag[JOIN_COUNTERS];
   const GemmArgs& g = p.g;
+  // (dH, whose epilogue is long, is not cut: 1 % slower where it need not be.  Gate/up, 3 experts of 2048 x 2048, 100
+  // tokens: pass 51.7 -> 46.2 us)
+  constexpr bool CUT = MODE != MODE_DH && MODE != MODE_DH1;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int total = count_tiles(p, map) * g.n_tiles_n;
-  const int split = MODE == MODE_DOWN ? parts_of(total, gridDim.x, g.kt) : 1;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    p.status->n_mtiles = total;
-    p.status->down_split = split;
-    p.status->down_split_tiles = split > 1 ? total : 0;
-  }
+  const int split = CUT ? parts_of(total, gridDim.x, g.kt) : 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) p.status->n_mtiles = total;
   const int units = total * split;
   // The idx-th unit of this block: rounds of gridDim.x units, a round in 8 chunks of consecutive ones
   // for the XCDs (blocks with index = x mod 8 are on XCD x), the last round in 8 equal chunks as well.
@@ -163,7 +180,8 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
       const int part = U % split, base = g.kt / split, rem = g.kt % split;
       u.kstart = part * base + min(part, rem);
       u.KT = base + (part < rem ? 1 : 0);
-      u.ws_unit = U;
+      u.part = part;
+      u.parts = split;
     }
     return u;
   };
@@ -314,61 +332,13 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
     const Unit128 nxt = fetch(idx + 1);
     const int na_n = blocks(nxt);
     if (nxt.valid) start(nxt, na_n);
-    if (MODE == MODE_DOWN && cur.ws_unit >= 0) {
-      // partial sums, [unit][i][j][quad][thread]; the 32-row blocks that hold rows
-      float4* ws = reinterpret_cast<float4*>(g.split_ws) + (size_t)cur.ws_unit * (16 * NT) + threadIdx.x;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        if (i < mine)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              ws[((i * 2 + j) * 4 + q) * NT] = make_float4(acc[j][i][q * 4], acc[j][i][q * 4 + 1],
-                                                           acc[j][i][q * 4 + 2], acc[j][i][q * 4 + 3]);
-    } else {
+    if (!CUT || cur.parts == 1 ||
+        join_parts<2, NT>(acc, g.split_ws + (size_t)cur.tile * cur.parts * (TM * TN), g.joined + cur.tile * JOIN_COUNTERS,
+                          cur.part, cur.parts, mine, join_flag))
       tile_epilogue<MODE, true, 2>(g, acc, cur.row0, cur.rows, cur.nblk, wm, wn, lane);
-    }
     if (!nxt.valid) break;
     cur = nxt;
     na = na_n;
-  }
-}
-
-// Sums the parts of every tile in a fixed order (part 0, 1, ...: deterministic) and stores the tile like
-// the GEMM's own epilogue.  Four blocks per tile, one per accumulator (j, i); thread indices mean what
-// they mean there.
-__global__ __launch_bounds__(NT) void ffn_tile128_sum_kernel(const TileArgs p) {
-  __shared__ TileMap map;
-  const int split = p.status->down_split, tiles = p.status->down_split_tiles;
-  const int tile = blockIdx.x >> 2, ij = blockIdx.x & 3;
-  if (tile >= tiles) return;
-  count_tiles(p, map);
-  const Unit128 u = find_tile(p, map, tile);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave >> 1, wn = wave & 1, i = ij >> 1, j = ij & 1;
-  if (wm * 64 + i * 32 >= u.rows) return;   // no rows here: nothing was stored
-  const float4* ws = reinterpret_cast<const float4*>(p.g.split_ws) + (size_t)tile * split * (16 * NT) +
-                     (size_t)ij * 4 * NT + threadIdx.x;
-  float4 part[4][SPLIT_MAX];   // all requested before anything is added
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int t = 0; t < SPLIT_MAX; ++t)
-      part[q][t] = t < split ? ws[(size_t)t * (16 * NT) + q * NT] : make_float4(0.f, 0.f, 0.f, 0.f);
-  const int m_local = wm * 64 + i * 32 + (lane & 31);
-  const size_t row = (size_t)(u.row0 + m_local);
-  const int col0 = u.nblk * TN + j * 64 + wn * 32 + 4 * (lane >> 5);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    float4 v = part[q][0];
-#pragma unroll
-    for (int t = 1; t < SPLIT_MAX; ++t) {
-      v.x += part[q][t].x; v.y += part[q][t].y; v.z += part[q][t].z; v.w += part[q][t].w;
-    }
-    if (m_local < u.rows && col0 + 8 * q < p.g.N)
-      *reinterpret_cast<uint2*>(p.g.C + row * p.g.N + col0 + 8 * q) =
-          make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
   }
 }
 
@@ -389,6 +359,7 @@ TileArgs tile_args(const moe_ctx* c, const int32_t* counts, const int32_t* offse
   a.g.kseg_len = seg_len;
   a.g.zero = (const char*)c->d_zero;
   a.g.split_ws = c->d_split_ws;
+  a.g.joined = c->d_joined;
   a.counts = counts;
   a.offsets = offsets;
   a.present = c->d_wtab;
@@ -406,19 +377,24 @@ int slots(const moe_ctx* c) { return slots_of(c->n_cu); }
 // Floats of the partial tiles of a context with S rows: as many as there are resident blocks at most, fewer
 // where there cannot be as many parts (dX of the gated expert has the longest contraction).
 size_t split_floats(int S, int E, int d, int f, int n_cu) {
-  const int most = parts_of(1, SPLIT_MAX, 2 * ceil_div(f, BK));
-  const long long tiles = ((long long)S / TM + E) * ceil_div(d, TN);
-  return most == 1 ? 0 : (size_t)std::min<long long>(slots_of(n_cu), tiles * most) * (TM * TN);
+  const long long blocks = (long long)S / TM + E;
+  auto tiles = [&](int kt, int cols) {
+    const int most = parts_of(1, SPLIT_MAX, kt);
+    return most == 1 ? 0 : std::min<long long>(slots_of(n_cu), blocks * cols * most);
+  };
+  return (size_t)std::max(tiles(2 * ceil_div(f, BK), ceil_div(d, TN)) /* dX */,
+                          tiles(ceil_div(d, BK), ceil_div(f, 64)) /* gate/up */) * (TM * TN);
 }
 
 template <int MODE, bool BKM>
 void launch(const moe_ctx* c, const TileArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((ffn_tile128_kernel<MODE, BKM>), dim3(slots(c)), dim3(NT), 0, s, a);
-  if (MODE == MODE_DOWN && a.g.kt >= 2 * SPLIT_STEPS)
-    hipLaunchKernelGGL(ffn_tile128_sum_kernel, dim3(slots(c) / 2 * 4), dim3(NT), 0, s, a);
 }
 
 }  // namespace
+
+// (two parts at least, on at most `slots` blocks; the 256-row tiles have half as many blocks)
+size_t ffn_join_counters(const moe_ctx* c) { return (size_t)slots(c) / 2 * JOIN_COUNTERS; }
 
 size_t ffn_tile128_split_floats(const moe_ctx* c) {
   return split_floats(c->S_max, c->cfg.E, c->cfg.d, c->cfg.f, c->n_cu);
@@ -475,7 +451,7 @@ static double us_256(int experts, int rows, int N, int bn, int K, int kt, bool d
   const double full = 1.21 * rows / (256.0 * blocks) + (K % 128 != 0 || N % bn != 0 ? 0.32 : 0);
   const double loop = tiles / n_cu * (kt * (0.77 + full) + 2.35) +
                       (tail > 0 ? (double)kt / split * (0.77 + full * tail * split / n_cu) + 2.35 : 0);
-  return 11.3 /* half of the schedule in it */ + (split > 1 ? 4.4 : 0) + std::max(loop, mb / (bwd ? 5.4 : 5.2));
+  return (bwd ? 11.3 : 11.8) /* half of the schedule in it */ + (split > 1 ? 4.4 : 0) + std::max(loop, mb / (bwd ? 5.4 : 5.2));
 }
 static double us_128(int experts, int rows, int N, int bn, int kt, bool down, bool bwd, double mb, int n_cu) {
   const int blocks = ceil_div(rows, TM), tiles = experts * blocks * ceil_div(N, bn), slots = 2 * n_cu;
@@ -483,7 +459,7 @@ static double us_128(int experts, int rows, int N, int bn, int kt, bool down, bo
   const double steps = (double)kt / split, full = 0.77 * rows / ((double)TM * blocks);
   const double loop = units / slots * (steps * (0.67 + full) + 1.26) +
                       (tail > 0 ? steps * (0.67 + full * tail / slots) + 1.26 : 0);
-  return 4.65 + (split > 1 ? 8.2 : 0) + std::max(loop, mb / (bwd ? 4.5 : 5.3));
+  return 4.65 + (split > 1 ? 2.2 * join_levels(split) - 1 : 0) + std::max(loop, mb / (bwd ? 4.5 : 5.3));
 }
 // Both GEMMs of a call, larger and smaller tiles.
 static void tile_us(int experts, int rows, int d, int f, bool gated, bool backward, int n_cu, double& large,

@@ -84,6 +84,7 @@ struct moe_ctx {
   TileDesc* d_order_up;   // MFMA tile order of the gate/up GEMM
   TileDesc* d_order_down; // ... and of the down GEMM
   int n_cu;               // compute units of the device
+  int32_t* d_joined;      // counters of the tiles whose parts the blocks add: zero between launches
   float* d_split_ws;      // fp32 partial tiles of the contractions that are cut, as many as there can be
   int32_t S_max;          // T_max*k
   int32_t S_call;         // T*k of the expert-FFN call being launched: the rows its buffers hold
@@ -169,6 +170,7 @@ int launch_ffn_mfma(moe_ctx* c, bool gated, const int32_t* counts, const int32_t
 bool ffn_tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu);
 bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward);
 size_t ffn_tile128_split_floats(const moe_ctx* c);   // of the partial tiles at most
+size_t ffn_join_counters(const moe_ctx* c);          // counters of the tiles that have them at most
 int launch_ffn_tile128(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
                        const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s);
 int launch_ffn_tile128_dh(moe_ctx* c, bool gated, const void* dy, const void* G, const void* U,
