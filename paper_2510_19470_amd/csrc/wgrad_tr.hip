@@ -410,6 +410,11 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
   a.job[0] = {(const uint16_t*)dy, (const uint16_t*)H, dW2, d, 0, f, d, f};
   a.job[1] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW1, gw, 0, d, f, d};
   a.job[2] = {(const uint16_t*)dGU, (const uint16_t*)xp, dW3, gw, f, d, f, d};
+  // whole lines to store (store_tile), by the sizes and by where the gradients lie
+  bool lines = d % 32 == 0 && f % 32 == 0;
+  for (int i = 0; i < a.n_list; ++i)
+    for (int w = 3; w < 6; ++w) lines &= ((uintptr_t)c->h_wtab[w][a.list[i]] & 127) == 0;
+  const bool rag = d % 256 != 0 || f % 256 != 0 || !lines;
   // By the rows per expert of an even routing.  The two cross between 96 and 512 of them, later on whole sizes
   // and earlier where popularity falls off as rank^-1.2; up to the line the kernel for few rows gains up to 6 %
   // of the whole backward and loses up to 1 %.  Backward, us, many -> few at 64, 128, 192, 256 rows; even, and
@@ -422,12 +427,13 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
   //   293 -> 294
   //   2048 x 1408, 12 of 64: 212 -> 207, 237 -> 233, 262 -> 261, 286 -> 288; 277 -> 278, 327 -> 326, 408 -> 415,
   //   551 -> 557
-  const bool few = c->wgrad_rows != 0 ? c->wgrad_rows == 128 : c->S_call <= 128 * E;
-  // whole lines to store (store_tile), by the sizes and by where the gradients lie
-  bool lines = d % 32 == 0 && f % 32 == 0;
-  for (int i = 0; i < a.n_list; ++i)
-    for (int w = 3; w < 6; ++w) lines &= ((uintptr_t)c->h_wtab[w][a.list[i]] & 127) == 0;
-  const bool rag = d % 256 != 0 || f % 256 != 0 || !lines;
+  // With whole lines to store that kernel gains by its stores too: on whole tiles and at least three rounds of the
+  // larger ones (fewer are one round more in the smaller ones), many -> few at 512 rows, step, even routing: 2048 x 2048,
+  // 6 experts: 524 -> 514; 1536 x 2048: 400 -> 391; popularity rank^-1, 2048 x 2048: 1094 -> 1103.  At 1024 rows: 774
+  // -> 772; 288 tiles of 1024 x 1024, 256 rows: 158 -> 161; 2048 x 1408, 256 rows: 264 -> 273.
+  const int tiles256 = a.n_jobs * a.n_list * ((d + 255) / 256) * ((f + 255) / 256);
+  const int line = !rag && tiles256 >= 3 * c->n_cu ? 512 : 128;
+  const bool few = c->wgrad_rows != 0 ? c->wgrad_rows == 128 : c->S_call <= line * E;
   if (few) {
     auto tiles = [](int m, int n) { return ((m + 255) / 256) * ((n + F_BN - 1) / F_BN); };
     const int total = a.n_list * (tiles(d, f) + (a.n_jobs - 1) * tiles(f, d));
@@ -435,8 +441,7 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
     auto kern = !rag ? wgrad_few_kernel<false, true> : lines ? wgrad_few_kernel<true, true> : wgrad_few_kernel<true, false>;
     hipLaunchKernelGGL(kern, grid, dim3(F_NT), 0, s, a);
   } else {
-    const int total = a.n_jobs * a.n_list * ((d + 255) / 256) * ((f + 255) / 256);
-    const dim3 grid((total + 255) / 256 * 256);
+    const dim3 grid((tiles256 + 255) / 256 * 256);
     auto kern = !rag ? wgrad_tr_kernel<false, true> : lines ? wgrad_tr_kernel<true, true> : wgrad_tr_kernel<true, false>;
     hipLaunchKernelGGL(kern, grid, dim3(NT), 0, s, a);
   }
