@@ -50,16 +50,17 @@ size_t split_tiles_max(long long tiles, int n_cu, int kt_down) {
 __global__ __launch_bounds__(256) void mfma_sched_kernel(
     const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
     const void* const* __restrict__ present, int E, int S, int max_mtiles, int nt_up, int nt_down,
-    int n_cu, int kt_down, TileSched* __restrict__ sched, const void* const* __restrict__ up_b0,
+    int n_cu, int kt_down, int nt_dh128, TileSched* __restrict__ sched, const void* const* __restrict__ up_b0,
     const void* const* __restrict__ up_b1, const void* const* __restrict__ down_b0,
     const void* const* __restrict__ down_b1, TileDesc* __restrict__ order_up,
     TileDesc* __restrict__ order_down) {
   __shared__ int32_t start[MOE_MAX_EXPERTS + 1];
-  __shared__ int bad;
+  __shared__ int bad, blocks128;
   const int tid = threadIdx.x;
   if (tid == 0) {
     start[0] = 0;
     bad = 0;
+    blocks128 = 0;
   }
   __syncthreads();
   // per-expert tile counts (E <= 256: one expert per thread), then an inclusive scan
@@ -67,7 +68,10 @@ __global__ __launch_bounds__(256) void mfma_sched_kernel(
   if (tid < E && present[tid] != nullptr) {
     const int n = counts[tid], o = offsets[tid];
     if (n < 0 || o < 0 || (long)o + n > (long)S) bad = 1;  // caller's arrays are inconsistent
-    else mine = (n + BM - 1) / BM;
+    else {
+      mine = (n + BM - 1) / BM;
+      atomicAdd(&blocks128, (n + 127) / 128);
+    }
   }
   start[tid + 1] = mine;
   __syncthreads();
@@ -91,6 +95,10 @@ __global__ __launch_bounds__(256) void mfma_sched_kernel(
     sched->down_split = split;
     sched->down_split_tiles = split > 1 ? tail : 0;
     sched->down_full = split > 1 ? total - tail : total;
+    // dH: a round of 128-row tiles (two blocks on a compute unit) takes 0.6 to 0.7 times as long as one of these
+    const int small_rounds = (blocks128 * nt_dh128 + 2 * n_cu - 1) / (2 * n_cu);
+    const int rounds = (total_m * nt_up + n_cu - 1) / n_cu;
+    sched->dh_small = total_m > 0 && nt_dh128 > 0 && 2 * small_rounds < 3 * rounds;
   }
   const int gsz = gridDim.x * blockDim.x;
   const int gid = blockIdx.x * blockDim.x + tid;
@@ -155,7 +163,8 @@ __device__ __forceinline__ Unit fetch_unit(const GemmArgs& p, int idx) {
   Unit u;
   u.valid = 0;
   u.ws_unit = -1;
-  const int total = p.sched->n_mtiles * p.n_tiles_n;
+  constexpr bool DH = MODE == MODE_DH || MODE == MODE_DH1;
+  const int total = DH && p.sched->dh_small ? 0 : p.sched->n_mtiles * p.n_tiles_n;
   const int n_full = MODE == MODE_DOWN ? p.sched->down_full : total;
   const int split = MODE == MODE_DOWN ? p.sched->down_split : 1;
   const int n_units = MODE == MODE_DOWN ? p.sched->down_split_tiles * split : 0;
@@ -617,11 +626,11 @@ extern "C" void moe_internal_split_tiles(int32_t tiles, int64_t tiles_max, int32
 }
 
 static int run_sched(moe_ctx* c, const int32_t* counts, const int32_t* offsets, int nt_a, int nt_b,
-                     int kt_b, const void* const* up_b0, const void* const* up_b1,
+                     int kt_b, int nt_dh128, const void* const* up_b0, const void* const* up_b1,
                      const void* const* down_b0, const void* const* down_b1, hipStream_t s) {
   hipLaunchKernelGGL(mfma_sched_kernel, dim3(32), dim3(256), 0, s, counts, offsets,
                      c->d_wtab + 0 * MOE_MAX_EXPERTS, c->cfg.E, c->S_call, c->max_mtiles[1], nt_a,
-                     nt_b, c->n_cu, kt_b, c->d_sched[1], up_b0, up_b1, down_b0, down_b1,
+                     nt_b, c->n_cu, kt_b, nt_dh128, c->d_sched[1], up_b0, up_b1, down_b0, down_b1,
                      c->d_order_up, c->d_order_down);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
@@ -680,7 +689,7 @@ int launch_ffn_mfma(moe_ctx* c, bool gated, const int32_t* counts, const int32_t
   const void* const* W3 = c->d_wtab + 1 * MOE_MAX_EXPERTS;
   const void* const* W2 = c->d_wtab + 2 * MOE_MAX_EXPERTS;
   prof_mark(c, 0, s);
-  int st = run_sched(c, counts, offsets, ceil_div(f, bn_up), ceil_div(d, 256), k_steps(f, 1), W1,
+  int st = run_sched(c, counts, offsets, ceil_div(f, bn_up), ceil_div(d, 256), k_steps(f, 1), 0, W1,
                      gated ? W3 : nullptr, W2, nullptr, s);
   if (st != MOE_OK) return st;
   prof_mark(c, 1, s);
@@ -712,11 +721,13 @@ int launch_ffn_bwd_mfma(moe_ctx* c, bool gated, const void* dy, const void* xp, 
   int st;
   // dH = dY W2 with the activation's derivative in the epilogue -> [dG|dU], H
   if (small) {
-    st = launch_ffn_tile128_dh(c, gated, dy, G, U, counts, offsets, s);
+    st = launch_ffn_tile128_dh(c, gated, dy, G, U, counts, offsets, false, s);
     if (st != MOE_OK) return st;
   } else {
-    st = run_sched(c, counts, offsets, ceil_div(f, 256), ceil_div(d, 256), k_steps(f, segs), W2,
-                   nullptr, W1, gated ? W3 : nullptr, s);
+    const bool offered = ffn_tile128_dh_offered(c);   // the 128-row tiles' dH as well
+    st = run_sched(c, counts, offsets, ceil_div(f, 256), ceil_div(d, 256), k_steps(f, segs),
+                   offered ? ceil_div(f, 128) : 0, W2, nullptr, W1, gated ? W3 : nullptr, s);
+    if (st == MOE_OK && offered) st = launch_ffn_tile128_dh(c, gated, dy, G, U, counts, offsets, true, s);
     if (st != MOE_OK) return st;
     GemmArgs dh = tiled_args(c, dy, d, c->d_order_up, 256, d, 1, f, f, c->d_dGU);
     dh.C2 = (uint16_t*)c->d_H;

@@ -287,7 +287,7 @@ __device__ __forceinline__ bool join_parts(f32x16 (&acc)[2][NI], float* slots, i
       int32_t* count = counters + first + (node >> 1);
       if (tid == 0) flag[2 * level] = join_get(count);
       __syncthreads();
-      if (flag[2 * level] == 0) {   // the neighbour is not there yet: publish
+      if (__builtin_amdgcn_readfirstlane(flag[2 * level]) == 0) {   // the neighbour is not there yet: publish
         join_word* mine = reinterpret_cast<join_word*>(slots + (size_t)(node << level) * (32 * NI * THREADS)) + tid;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -305,7 +305,7 @@ __device__ __forceinline__ bool join_parts(f32x16 (&acc)[2][NI], float* slots, i
         if (tid == 0)
           flag[2 * level + 1] = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        if (flag[2 * level + 1] == 0) return false;   // the neighbour goes on with it
+        if (__builtin_amdgcn_readfirstlane(flag[2 * level + 1]) == 0) return false;   // the neighbour goes on with it
       }
       if (tid == 0) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       join_word* theirs = reinterpret_cast<join_word*>(slots + (size_t)((node ^ 1) << level) * (32 * NI * THREADS)) + tid;

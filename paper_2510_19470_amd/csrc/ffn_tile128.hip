@@ -38,6 +38,7 @@ struct TileArgs {
   const void* const* b1;         // [E] gate/up: W3; k-major: the second segment's (may be nullptr)
   int E, S;
   TileSched* status;             // n_mtiles for the kernels after this one: 0 if counts do not fit
+  bool offered;                  // dH: status is the larger tiles' schedule, and says whose turn it is
 };
 
 // Row blocks of all experts, counted by every block for itself: start[e] is the first one of expert e.
@@ -158,11 +159,12 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
   // (dH, whose epilogue is long, is not cut: 1 % slower where it need not be.  Gate/up, 3 experts of 2048 x 2048, 100
   // tokens: pass 51.7 -> 46.2 us)
   constexpr bool CUT = MODE != MODE_DH && MODE != MODE_DH1;
+  if ((MODE == MODE_DH || MODE == MODE_DH1) && p.offered && p.status->dh_small == 0) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int total = count_tiles(p, map) * g.n_tiles_n;
   const int split = CUT ? parts_of(total, gridDim.x, g.kt) : 1;
-  if (blockIdx.x == 0 && threadIdx.x == 0) p.status->n_mtiles = total;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !p.offered) p.status->n_mtiles = total;
   const int units = total * split;
   // The idx-th unit of this block: rounds of gridDim.x units, a round in 8 chunks of consecutive ones
   // for the XCDs (blocks with index = x mod 8 are on XCD x), the last round in 8 equal chunks as well.
@@ -419,9 +421,10 @@ int launch_ffn_tile128(moe_ctx* c, bool gated, const int32_t* counts, const int3
 // The two halves of the data gradients (the weight gradients come between them, see
 // launch_ffn_bwd_mfma): dH = dY W2 with the activation's derivative, and dX.
 int launch_ffn_tile128_dh(moe_ctx* c, bool gated, const void* dy, const void* G, const void* U,
-                          const int32_t* counts, const int32_t* offsets, hipStream_t s) {
+                          const int32_t* counts, const int32_t* offsets, bool offered, hipStream_t s) {
   const int d = c->cfg.d, f = c->cfg.f;
   TileArgs dh = tile_args(c, counts, offsets, dy, d, TN, d, 1, f, f, c->d_dGU, 2, -1);
+  dh.offered = offered;
   dh.g.C2 = (uint16_t*)c->d_H;
   dh.g.Gs = (uint16_t*)const_cast<void*>(G);
   dh.g.Us = (uint16_t*)const_cast<void*>(U);
@@ -436,6 +439,11 @@ int launch_ffn_tile128_dx(moe_ctx* c, bool gated, const int32_t* counts, const i
   launch<MODE_DOWN, true>(c, tile_args(c, counts, offsets, c->d_dGU, segs * f, TN, f, segs, d, d, dxp, 0,
                                        gated ? 1 : -1), s);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+}
+
+static bool dh_offered(long long S, int f, int E, int n_res, int slots) {
+  const long long rows = (S + E - 1) / E;
+  return n_res > 0 && n_res * ((rows + TM - 1) / TM) * ceil_div(f, TN) <= slots;
 }
 
 // Time in us of a GEMM's launches with `rows` rows on each of `experts` experts and weights of `mb` MB: a
@@ -505,6 +513,21 @@ bool ffn_tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, 
   tile_us(n_res, rows, d, f, gated, backward, n_cu, large, small);
   tile_us(std::min(k, n_res), T, d, f, gated, backward, n_cu, large_hot, small_hot);
   return small < large && small_hot - large_hot <= 2 * (large - small) + 5;
+}
+
+// dH where the larger tiles take the call: its long epilogue (five arrays of S x f) runs under another block's main
+// loop in the smaller ones, so that these serve one round faster (kernel, larger -> smaller, us: 6 experts of 2048 x
+// 2048, 250 rows: 69 -> 38, 512 rows: 76 -> 54; 768 rows, where they are two rounds and the larger ones one: 73 -> 92).
+// How many rounds either takes shows on the device: where an even routing makes it one of the smaller tiles, both
+// kernels are launched, and the schedule says which of them works (dh_small); the other one ends at once (3 us).
+// Training step, us: 4096 tokens, 2048 x 2048, 6 of 32 experts: 512 -> 498; 1536 x 2048: 390 -> 373; 2048 x 1408, 12 of 64
+// with popularity rank^-1.2, where the larger tiles would begin a third round: 1404 -> 1385; 1024 x 2048, rank^-0.6,
+// two rounds against one: 427 -> 430.
+bool ffn_tile128_dh_offered(const moe_ctx* c) {
+  if (c->tile_rows != 0) return c->tile_rows == 256 + TM;
+  int n_res = 0;
+  for (int e = 0; e < c->cfg.E; ++e) n_res += c->h_wtab[0][e] != nullptr;
+  return dh_offered(c->S_call, c->cfg.f, c->cfg.E, n_res, slots(c));
 }
 
 bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {

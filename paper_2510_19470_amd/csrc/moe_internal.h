@@ -34,6 +34,7 @@ struct TileSched {
   int32_t down_full;
   int32_t down_split_tiles;
   int32_t down_split;
+  int32_t dh_small;     // dH: the 128-row tiles' kernel works, not the 256-row tiles'
 };
 
 // pointer-table rows: W1, W3, W2, dW1, dW3, dW2
@@ -46,7 +47,8 @@ struct moe_ctx {
   int device;
   int elem;               // bytes per stored element
   int ffn_path;           // MOE_FFN_AUTO / MOE_FFN_VALU
-  int tile_rows;          // tests: 128 or 256 takes the GEMMs with these tiles, 16 the few-rows kernel (0: the rules)
+  int tile_rows;          // tests: 128 or 256 takes the GEMMs with these tiles, 384 the latter and offers dH the former,
+                          // 16 the few-rows kernel (0: the rules)
   int wgrad_rows;         // ... 128 or 256 the weight gradients for few or for many rows per expert
   // placement
   int32_t* d_dest_rank;   // [E]
@@ -174,7 +176,8 @@ size_t ffn_join_counters(const moe_ctx* c);          // counters of the tiles th
 int launch_ffn_tile128(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
                        const void* x_packed, void* y_packed, void* G, void* U, hipStream_t s);
 int launch_ffn_tile128_dh(moe_ctx* c, bool gated, const void* dy, const void* G, const void* U,
-                          const int32_t* counts, const int32_t* offsets, hipStream_t s);
+                          const int32_t* counts, const int32_t* offsets, bool offered, hipStream_t s);
+bool ffn_tile128_dh_offered(const moe_ctx* c);
 int launch_ffn_tile128_dx(moe_ctx* c, bool gated, const int32_t* counts, const int32_t* offsets,
                           void* dxp, hipStream_t s);
 // bf16, few rows per expert (S_call rows in all): a kernel that streams the weights

@@ -41,6 +41,14 @@ def test_few_rows_match_oracle(d, f, rows, gated):
     _check_given_rows(d, f, rows, gated, 16)
 
 
+# The schedule gives dH to the 128-row tiles (one round of theirs against one; two against one:
+# the larger ones), whatever serves the other GEMMs.
+@pytest.mark.parametrize("gated", [True, False])
+@pytest.mark.parametrize("d,f,rows", [(264, 520, [130, 0, 65, 257]), (72, 4096, [2200, 0, 65]), (72, 4096, [17, 400])])
+def test_dh_in_either_tiles_matches_oracle(d, f, rows, gated):
+    _check_given_rows(d, f, rows, gated, 384)
+
+
 # A block's tiles follow one another without a stop: the next one's first copies are under way while the
 # outputs of the last are stored.  512 blocks serve the 128-row tiles, 256 the 256-row ones (here 816 and 264
 # tiles or more in each of the four GEMMs), and tiles that follow one another differ in the rows they hold.
