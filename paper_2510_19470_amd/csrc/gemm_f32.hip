@@ -5,8 +5,8 @@
 //
 // Block = 256 threads = 4 wavefronts (2 x 2) on a tile of TM token rows x TN output columns;
 // weights are the MFMA "A" operand and tokens the "B" operand, so a lane ends up with 4
-// consecutive columns of one token (one 16-byte store).  Contraction steps of 32 through three
-// LDS stages filled by asynchronous copies, two steps in flight, one barrier per step.  (Loads
+// consecutive columns of one token (one 16-byte store).  Contraction steps of 32 through two or three
+// LDS stages filled by asynchronous copies, one or two steps in flight, one barrier per step.  (Loads
 // through registers, three steps ahead: the compiler waited for all of them at the head of every
 // step, 15-30 % slower.)  A lane takes 4 consecutive k of its row per fragment (the four MFMAs
 // of 16 k use the elements 0..3 of both operands: the order of k inside a group of 16 does not
@@ -32,8 +32,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 32;
 constexpr int NTHR = 256;
-constexpr int STAGES = 3;   // LDS stages, all but one in flight from memory (4: fewer blocks per
-                            // compute unit, 3-10 % slower)
 
 struct Tile {
   int expert, row0, rows;   // rows == 0: nothing to do
@@ -155,7 +153,7 @@ __device__ __forceinline__ void wait_barrier() {
 
 // acc[b][j][i] += tokens x weights over one segment of length K; b: weight matrix (two for gate
 // and up), j / i: 16-column / 16-token block of the wavefront's tile.
-template <int TM, int TN, int NB, bool XK, bool WK>
+template <int TM, int TN, int NB, bool XK, bool WK, int STAGES>
 struct Mma {
   static constexpr int MI = TM / 32, NJ = TN / 32;   // 16-blocks per wavefront (2 x 2 wavefronts)
   typedef Operand<TM, XK> X;
@@ -266,7 +264,12 @@ template <int MODE, int TM, int TN>
 __global__ __launch_bounds__(NTHR) void ffn_f32_kernel(const F32Args p) {
   constexpr bool WK = MODE == F_UP || MODE == F_UP1 || MODE == F_DOWN;   // weights contiguous in k
   constexpr int NB = MODE == F_UP ? 2 : 1;
-  typedef Mma<TM, TN, NB, true, WK> M;
+  // LDS stages, all but one in flight from memory.  64x64 tiles: two, so that five blocks share a compute unit's LDS
+  // instead of three and cover each other's waits (2048 tokens, d = 1024, f = 2048, 6 of 8 experts, step: 1408 -> 1346
+  // us; forward, 2000 tokens, 1000 x 1800: 391 -> 385).  32x32 tiles have six blocks with three of them (two: 194 ->
+  // 196.5, 1024 tokens, 512 x 1024; four: 3-10 % slower).
+  constexpr int STAGES = TM == 64 ? 2 : 3;
+  typedef Mma<TM, TN, NB, true, WK, STAGES> M;
   __shared__ __align__(16) float lds[STAGES * M::STAGE];
   const Tile tl = find_tile(blockIdx.x, TM, p.counts, p.offsets, p.present, p.E, p.S);
   if (tl.rows == 0) return;
@@ -344,9 +347,10 @@ struct DwArgs {
   const void* const* present;
 };
 
+template <int STAGES>
 __global__ __launch_bounds__(NTHR) void ffn_f32_dw_kernel(const DwArgs p) {
   constexpr int TS = 64;
-  typedef Mma<TS, TS, 1, false, false> M;
+  typedef Mma<TS, TS, 1, false, false, STAGES> M;
   __shared__ __align__(16) float lds[STAGES * M::STAGE];
   const int e = blockIdx.y / p.n_jobs;
   const DwArgs::Job& J = p.job[blockIdx.y % p.n_jobs];
@@ -473,6 +477,10 @@ int launch_ffn_bwd_f32(moe_ctx* c, bool gated, const void* dy, const void* xp, c
   a.offsets = offsets;
   a.present = c->d_wtab;
   const dim3 grid(ceil_div(d, 64) * ceil_div(f, 64), a.E * a.n_jobs);
-  hipLaunchKernelGGL(ffn_f32_dw_kernel, grid, dim3(NTHR), 0, s, a);
+  // Two stages where there are two steps or fewer on average: what counts then is blocks that start and store beside
+  // each other (step, us: 37 rows per expert 466 -> 450, 12 rows 130 -> 128; 131 rows 327 -> 326, 187 rows 288 -> 289.5,
+  // 256 rows 193.7 -> 198.6)
+  if (a.S <= 64 * a.E) hipLaunchKernelGGL((ffn_f32_dw_kernel<2>), grid, dim3(NTHR), 0, s, a);
+  else hipLaunchKernelGGL((ffn_f32_dw_kernel<3>), grid, dim3(NTHR), 0, s, a);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
