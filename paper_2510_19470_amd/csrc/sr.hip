@@ -40,11 +40,12 @@
 //
 // What bounds it, n = 14336 x 4096 bf16: the pass over both matrices (235 MB).  Encode 157 -> 95 us
 // against the version that streamed both matrices twice (histogram, then list) and picked bins in
-// one-block launches (matrices not in the last-level cache); of it the pass takes 58 us (4.1 TB/s; 50 us
-// with non-temporal loads, which the next reader of the shared expert pays back), the five short
-// launches 4.6-12 us each.  Half of the pass is vector instructions (selecting the residual by a tree of
-// moves instead of one comparison per word made it 80 us, reading it again from memory 64).  Decode 60 -> 46 us (5.1 TB/s): the shared expert is requested before the
-// search, 1 KB per load instruction, and the LDS of a block went from 40 to 17 KB.
+// one-block launches (matrices not in the last-level cache); of it the pass takes 58 us (4.1 TB/s; 46 us
+// with non-temporal loads, see sr_once), the five short launches 4.6-12 us each.  Half of the pass is
+// vector instructions (selecting the residual by a tree of moves instead of one comparison per word
+// made it 80 us, reading it again from memory 64; two chunks ahead instead of one: no faster).  Decode
+// 60 -> 46 us (5.1 TB/s): the shared expert is requested before the search, 1 KB per load instruction,
+// and the LDS of a block went from 40 to 17 KB.
 #include "moe_internal.h"
 #include "numeric.h"
 
