@@ -168,3 +168,35 @@ def test_weight_gradients_wherever_they_lie(d, f, few):
     for a, b in zip(grads(0), grads(4)):
         assert torch.equal(a, b)
     lay.close()
+
+
+@pytest.mark.parametrize("d,f,rows,parts", [
+    (128, 4096, [40], 8), (1024, 1408, [64], 4), (1024, 4096, [128] * 10, 3), (2048, 2048, [100] * 8, 2),
+])
+def test_joined_parts_are_the_same_bits_every_time(d, f, rows, parts):
+    """Which of two neighbouring parts is added by which block depends on who comes first; the sum and the counters
+    for the next call do not."""
+    from gpu_common import DEV, moe
+    lib, n, T = moe.load_library(), len(rows), sum(rows)
+    slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
+    assert lib.moe_internal_tile128_parts(sum(-(-r // 128) for r in rows) * -(-d // 128), slots, -(-f // 64)) == parts
+    ctx = moe.moe_create(T_max=T, d=d, E=n, k=1, f=f, R=1, dtype=moe.MOE_BF16)
+    lib.moe_internal_ffn_tile_rows(ctx.handle, 128)
+    g = torch.Generator(device=DEV).manual_seed(d + f)
+    W = lambda r, c: [(torch.randn(r, c, device=DEV, generator=g) * c ** -0.5).bfloat16() for _ in rows]
+    W1, W2 = W(f, d), W(d, f)
+    x = torch.randn(T, d, device=DEV, generator=g).bfloat16()
+    cnt = torch.tensor(rows, dtype=torch.int32, device=DEV)
+    off = (torch.cumsum(cnt, 0) - cnt).int()
+    first = None
+    for _ in range(20):
+        y, _, _ = moe.moe_expert_ffn(ctx, x, cnt, off, W1, None, W2)
+        torch.cuda.synchronize()
+        first = y if first is None else first
+        assert torch.equal(y, first)
+    for e, r in enumerate(rows):
+        s = slice(int(off[e]), int(off[e]) + r)
+        h = torch.relu(x[s].float() @ W1[e].float().t().contiguous())
+        want = h.bfloat16().float() @ W2[e].float().t().contiguous()
+        assert float((first[s].float() - want).norm() / want.norm()) <= 1e-2   # bf16 output and H: 2^-8 each
+    moe.moe_destroy(ctx)
