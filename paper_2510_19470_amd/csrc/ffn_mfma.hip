@@ -95,10 +95,11 @@ __global__ __launch_bounds__(256) void mfma_sched_kernel(
     sched->down_split = split;
     sched->down_split_tiles = split > 1 ? tail : 0;
     sched->down_full = split > 1 ? total - tail : total;
-    // dH: a round of 128-row tiles (two blocks on a compute unit) takes 0.6 to 0.7 times as long as one of these
+    // dH: a round of 128-row tiles (two blocks on a compute unit) takes 0.6 to 0.7 times as long as one of these.
+    // (Segments that overlap may have more row blocks than the smaller tiles' kernel takes.)
     const int small_rounds = (blocks128 * nt_dh128 + 2 * n_cu - 1) / (2 * n_cu);
     const int rounds = (total_m * nt_up + n_cu - 1) / n_cu;
-    sched->dh_small = total_m > 0 && nt_dh128 > 0 && 2 * small_rounds < 3 * rounds;
+    sched->dh_small = total_m > 0 && nt_dh128 > 0 && blocks128 <= S / 128 + E && 2 * small_rounds < 3 * rounds;
   }
   const int gsz = gridDim.x * blockDim.x;
   const int gid = blockIdx.x * blockDim.x + tid;

@@ -112,7 +112,7 @@ def _check_given_rows(d, f, rows, gated, tile):
     lay.close()
 
 
-@pytest.mark.parametrize("tile", [128, 256])
+@pytest.mark.parametrize("tile", [128, 256, 384])
 def test_counts_that_do_not_fit_compute_nothing(tile):
     """A segment outside the buffers, a negative count, a negative offset: no output is written, the weight
     gradients are zero."""
@@ -137,6 +137,35 @@ def test_counts_that_do_not_fit_compute_nothing(tile):
         assert torch.all(y == 3.0) and torch.all(dxp == 5.0)
         assert all(torch.all(w == 0) for w in dW1 + dW2)
     lay.close()
+
+
+def test_dh_is_computed_by_either_tiles_where_segments_overlap():
+    """Experts that share their rows: more 128-row blocks than a call of these tokens can have, not more 256-row
+    ones.  The schedule offers dH to the smaller tiles only where they take it.  (All experts have the same weights:
+    whoever writes a shared row writes the same.)"""
+    from gpu_common import DEV, moe
+    E, k, T, d, f = 4, 2, 128, 136, 264
+    g = torch.Generator(device=DEV).manual_seed(5)
+    one = lambda r, c: [(torch.randn(r, c, device=DEV, generator=g) * c ** -0.5).bfloat16()] * E
+    W1, W3, W2 = one(f, d), one(f, d), one(d, f)
+    x, dy = (torch.randn(T * k, d, device=DEV, generator=g).bfloat16() for _ in range(2))
+    G, U = (torch.randn(T * k, f, device=DEV, generator=g).bfloat16() for _ in range(2))
+    cnt = torch.full((E,), T * k, dtype=torch.int32, device=DEV)
+    off = torch.zeros(E, dtype=torch.int32, device=DEV)
+    got = {}
+    for tile in (256, 384):
+        ctx = moe.moe_create(T_max=T, d=d, E=E, k=k, f=f, R=1, dtype=moe.MOE_BF16)
+        moe.load_library().moe_internal_ffn_tile_rows(ctx.handle, tile)
+        # other rows first: what a dH that is left out would leave behind
+        moe.moe_expert_ffn_bwd(ctx, x, dy, U, G, torch.full_like(cnt, 64), off + 64 * torch.arange(E, device=DEV).int(),
+                               W1, W3, W2)
+        dxp, dW1, dW3, dW2 = moe.moe_expert_ffn_bwd(ctx, dy, x, G, U, cnt, off, W1, W3, W2)
+        torch.cuda.synchronize()
+        got[tile] = [dxp] + dW1 + dW3 + dW2
+        moe.moe_destroy(ctx)
+    assert float(got[256][0].abs().sum()) > 0
+    for a, b in zip(got[256], got[384]):
+        assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("few", [128, 256])
