@@ -203,11 +203,12 @@ __device__ __forceinline__ void dwg_partial(const TokenArgs& t, const DwgArgs& p
   if (OWN) {
     if (threadIdx.x < RB_TOK) {
       float* row = lds.dl[threadIdx.x];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) row[i] = 0.f;
       const size_t s0 = (size_t)min(chunk * RB_TOK + (int)threadIdx.x, Tn - 1) * t.k;
       float inner = 0.f;
       for (int j = 0; j < t.k; ++j) inner += t.dtopk_w[s0 + j] * t.topk_w[s0 + j];
+      const float none = 0.f * (0.f - inner);   // of experts not selected: as in dlogits, where a NaN shows for all
+#pragma unroll
+      for (int i = 0; i < 16; ++i) row[i] = none;
       for (int j = 0; j < t.k; ++j) {
         const int e = t.topk_idx[s0 + j] - e0;
         if ((unsigned)e < 16u) row[e] = t.topk_w[s0 + j] * (t.dtopk_w[s0 + j] - inner);

@@ -113,3 +113,21 @@ def test_x_aligned_to_its_elements_only(dtype):
     torch.cuda.synchronize()
     assert off.data_ptr() % 16 != 0 and torch.equal(a[1], b[1])
     moe.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("renorm", [1, 0])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_gradients_that_are_not_finite_show_in_both_outputs(bad, renorm):
+    """dWg = dlogits^T x for what is no number, too: a token whose dtopk_w is not finite has no finite logit gradient."""
+    T, d, E, k = 200, 136, 40, 2
+    ctx = moe.moe_create(T_max=T, d=d, E=E, k=k, f=8, R=1, dtype=moe.MOE_BF16, renormalize=renorm)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x, Wg = (torch.randn(n, d, device="cuda", generator=g).bfloat16() for n in (T, E))
+    idx, w, logits = moe.moe_route(ctx, x, Wg, None, want_logits=True)
+    dw = torch.randn(T, k, device="cuda", generator=g)
+    dw[150, 0] = bad
+    dl, dWg, _ = moe.moe_route_bwd(ctx, x, Wg, idx, w, dw, logits=logits)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(dl[150]).any() and torch.isfinite(dl[:150]).all() and torch.isfinite(dl[151:]).all()
+    assert not torch.isfinite(dWg).any()
+    moe.moe_destroy(ctx)
