@@ -50,6 +50,7 @@ struct moe_ctx {
   int tile_rows;          // tests: 128 or 256 takes the GEMMs with these tiles, 384 the latter and offers dH the former,
                           // 16 the few-rows kernel (0: the rules)
   int wgrad_rows;         // ... 128 or 256 the weight gradients for few or for many rows per expert
+  int gate_joint;         // ... 1 or 2 the gate backward's logit and weight gradients in one launch or in two
   // placement
   int32_t* d_dest_rank;   // [E]
   int32_t* d_seg_pos;     // [E] position of every expert in (dest_rank, id) order

@@ -4,13 +4,12 @@
 //   p = softmax of the logits over the selected experts (renormalize) or over all E,
 //   dlogits[t,e] = p_e * ( [e selected] dw_e - sum_j dw_j w_j ),   w_j = p[idx_j] = topk_w,
 //   dWg = dlogits^T x,  dbias = sum_t dlogits[t],  dx += dlogits Wg.
-// Two launches: the logit gradients and the input gradient (one wavefront per token, added to the dx
-// the dispatch backward has written) beside the weight gradient as per-chunk partial sums over 128
-// tokens, and the fixed-order sum of those over the chunks together with dbias (deterministic, no
-// floating-point atomics).  Without renormalising the partial sums are a launch of their own.
+// Three launches: the logit gradients and the input gradient (one wavefront per token, added to the dx
+// the dispatch backward has written), the weight gradient as per-chunk partial sums over 128 tokens,
+// and the fixed-order sum of those over the chunks together with dbias (deterministic, no
+// floating-point atomics).  Where the weights are renormalised, small calls make the first two one.
 #include "moe_internal.h"
 #include "numeric.h"
-#include <type_traits>
 
 namespace {
 
@@ -38,14 +37,123 @@ struct TokenArgs {
   void* dx;
 };
 
-// One wavefront per token; lane e, e+64, ... own the experts.  dlogits[t] stays in registers for
+// One wavefront per token; lane e, e+64, ... own the experts (NE: how many a lane has, at most).  dlogits[t]
+// stays in registers for
 //   dx[t] += sum_e dlogits[t][e] * Wg[e]   (16 bytes per lane; left out without dx),
 // in which only the k selected experts have a non-zero logit gradient when renormalising.  Bound by reading
-// and writing dx; the k rows of Wg come from L2, all requested together with the piece of dx (one at a time,
-// every term waited for its own: 8192 tokens, d = 2048, E = 32, k = 4, dx in the last-level cache: call without dWg
-// 18.0 -> 15.0 us).
-template <typename T, int K_MAX>
+// and writing dx, with the full softmax by reading all of Wg from L2.  Four rows of Wg are requested together
+// (one at a time, every term waited for its own), two pieces of them where there are more terms than that, and the
+// first piece of dx before anything else; 6 to 8 wavefronts per SIMD cover the rest of the wait.  Call, us, a term at
+// a time -> this: 8192 tokens, d = 2048, E = 32, k = 4: 47 -> 44; 4096 tokens, d = 2048, E = 64, k = 12: 51 -> 40; full
+// softmax: 8192 x 2048, E = 32: 108 -> 77; 4096 x 2048, E = 64: 155 -> 73; 8192 x 2048, E = 256: 709 -> 459.
+template <typename T, int NE, int P>
 __device__ __forceinline__ void token_grads(const TokenArgs& p, int block) {
+  constexpr int V = Vec16<T>::N;
+  constexpr int TERMS = 4;
+  const int E = p.E, k = p.k, d = p.d;
+  const int lane = threadIdx.x & 63;
+  const int t = block * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (t >= p.Tn) return;
+  const T* Wg = static_cast<const T*>(p.Wg);
+  T* dx = static_cast<T*>(p.dx) + (size_t)t * d;
+  uint4 own[P];   // of dx, requested first: nothing has to be known for it
+  auto load_own = [&](int c) {
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+      if (c + q * 64 * V < d) own[q] = Vec16<T>::load_raw(dx + c + q * 64 * V);
+  };
+  if (p.dx != nullptr) load_own(lane * V);
+  // lane j < k: selected expert j
+  static_assert(MOE_MAX_TOPK <= 64, "a lane per selected expert");
+  const size_t sel = (size_t)t * k + min(lane, k - 1);
+  const int idx = p.topk_idx[sel];
+  const float tw = p.topk_w[sel], dw = p.dtopk_w[sel];
+  auto of_lane = [](float v, int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j)); };
+  float inner = 0.f;
+  for (int j = 0; j < k; ++j) inner += of_lane(dw, j) * of_lane(tw, j);
+  const float* logits = p.logits + (size_t)t * E;
+  float mx = -INFINITY, den = 1.f;
+  if (!p.renormalize) {   // full softmax of the row
+    for (int e = lane; e < E; e += 64) mx = fmaxf(mx, logits[e]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float s = 0.f;
+    for (int e = lane; e < E; e += 64) s += expf(logits[e] - mx);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    den = s;
+  }
+  float dl[NE];   // of experts lane, lane + 64, ...
+#pragma unroll
+  for (int i = 0; i < NE; ++i) {
+    const int e = lane + 64 * i;
+    float sel_dw = 0.f, w = 0.f;
+    bool selected = false;
+    for (int j = 0; j < k; ++j)
+      if (__builtin_amdgcn_readlane(idx, j) == e) {
+        selected = true;
+        sel_dw = of_lane(dw, j);
+        w = of_lane(tw, j);
+      }
+    dl[i] = 0.f;
+    if (e < E) {
+      float pe;
+      if (p.renormalize) pe = selected ? w : 0.f;
+      else pe = expf(logits[e] - mx) / den;
+      dl[i] = pe * ((selected ? sel_dw : 0.f) - inner);
+      p.dlogits[(size_t)t * E + e] = dl[i];
+    }
+  }
+  if (p.dx == nullptr) return;
+  const int n_terms = p.renormalize ? k : E;
+  // (wave-uniform loops: a lane past the row's columns neither loads nor stores, but the others read its dl)
+  for (int c0 = 0; c0 < d; c0 += P * 64 * V) {
+    const int c = c0 + lane * V;
+    float acc[P][V];
+    for (int j0 = 0; j0 < n_terms; j0 += TERMS) {
+      uint4 raw[TERMS][P];
+      int e[TERMS];
+#pragma unroll
+      for (int u = 0; u < TERMS; ++u) {
+        e[u] = -1;
+        if (j0 + u < n_terms) e[u] = p.renormalize ? __builtin_amdgcn_readlane(idx, j0 + u) : j0 + u;
+        if ((unsigned)e[u] >= (unsigned)E) continue;   // the routing is the caller's: stay inside Wg
+#pragma unroll
+        for (int q = 0; q < P; ++q)
+          if (c + q * 64 * V < d) raw[u][q] = Vec16<T>::load_raw(Wg + (size_t)e[u] * d + c + q * 64 * V);
+      }
+      if (j0 == 0) {
+#pragma unroll
+        for (int q = 0; q < P; ++q) Vec16<T>::unpack(own[q], acc[q]);
+        load_own(c + P * 64 * V);
+      }
+#pragma unroll
+      for (int u = 0; u < TERMS; ++u) {
+        if ((unsigned)e[u] >= (unsigned)E) continue;
+        float v = dl[0];
+#pragma unroll
+        for (int i = 1; i < NE; ++i) v = (e[u] >> 6) == i ? dl[i] : v;
+        const float g = of_lane(v, e[u] & 63);
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+          float w[V];
+          Vec16<T>::unpack(raw[u][q], w);
+#pragma unroll
+          for (int i = 0; i < V; ++i) acc[q][i] = fmaf(g, w[i], acc[q][i]);
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+      if (c + q * 64 * V < d) Vec16<T>::store(dx + c + q * 64 * V, acc[q]);
+  }
+}
+
+// The same for renormalised weights of up to K_MAX experts, beside blocks that leave it half as many wavefronts
+// (route_bwd_joint_kernel): what a wavefront needs is in registers and requested without a branch between, two
+// pieces of the row at a time where they fit.
+template <typename T, int K_MAX>
+__device__ __forceinline__ void token_grads_selected(const TokenArgs& p, int block) {
   constexpr int V = Vec16<T>::N;
   constexpr int NE = MOE_MAX_EXPERTS / 64;
   const int E = p.E, k = p.k, d = p.d;
@@ -66,92 +174,53 @@ __device__ __forceinline__ void token_grads(const TokenArgs& p, int block) {
 #pragma unroll
   for (int j = 0; j < K_MAX; ++j)
     if (j < k) inner += dw[j] * tw[j];
-  const float* logits = p.logits + (size_t)t * E;
-  float mx = -INFINITY, den = 1.f;
-  if (!p.renormalize) {   // full softmax of the row
-    for (int e = lane; e < E; e += 64) mx = fmaxf(mx, logits[e]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    float s = 0.f;
-    for (int e = lane; e < E; e += 64) s += expf(logits[e] - mx);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    den = s;
-  }
-  float dl[NE];
+  float dl[NE];   // of experts lane, lane + 64, ...
 #pragma unroll
   for (int i = 0; i < NE; ++i) {
     const int e = lane + 64 * i;
     dl[i] = 0.f;
     if (e >= E) continue;
     float sel_dw = 0.f, w = 0.f;
-    bool selected = false;
 #pragma unroll
     for (int j = 0; j < K_MAX; ++j)
       if (idx[j] == e) {
-        selected = true;
         sel_dw = dw[j];
         w = tw[j];
       }
-    float pe;
-    if (p.renormalize) pe = selected ? w : 0.f;
-    else pe = expf(logits[e] - mx) / den;
-    dl[i] = pe * ((selected ? sel_dw : 0.f) - inner);
+    dl[i] = w * (sel_dw - inner);
     p.dlogits[(size_t)t * E + e] = dl[i];
   }
   if (p.dx == nullptr) return;
   T* dx = static_cast<T*>(p.dx) + (size_t)t * d;
-  auto of_expert = [&](int e) {   // dlogits[t][e], e wave-uniform
+  float g[K_MAX];
+  const T* row[K_MAX];
+  bool ok[K_MAX];
+#pragma unroll
+  for (int j = 0; j < K_MAX; ++j) {
+    ok[j] = (unsigned)idx[j] < (unsigned)E;   // the routing is the caller's: stay inside Wg
+    const int e = __builtin_amdgcn_readfirstlane(ok[j] ? idx[j] : 0);
     float v = dl[0];
 #pragma unroll
     for (int i = 1; i < NE; ++i) v = (e >> 6) == i ? dl[i] : v;
-    return __shfl(v, e & 63, 64);
-  };
-  // every lane takes part in every exchange: columns past the row are not loaded or stored
-  if (p.renormalize) {
-    float g[K_MAX];
-    const T* row[K_MAX];
-    bool ok[K_MAX];
+    g[j] = __shfl(v, e & 63, 64);   // (every lane takes part)
+    row[j] = Wg + (size_t)e * d;
+  }
+#pragma unroll(K_MAX <= 4 ? 2 : 1)
+  for (int c = lane * V; c < d; c += 64 * V) {
+    float acc[V];
+    const uint4 own = Vec16<T>::load_raw(dx + c);
+    uint4 raw[K_MAX];
+#pragma unroll
+    for (int j = 0; j < K_MAX; ++j) raw[j] = Vec16<T>::load_raw(row[j] + c);
+    Vec16<T>::unpack(own, acc);
 #pragma unroll
     for (int j = 0; j < K_MAX; ++j) {
-      ok[j] = (unsigned)idx[j] < (unsigned)E;   // the routing is the caller's: stay inside Wg
-      const int e = __builtin_amdgcn_readfirstlane(ok[j] ? idx[j] : 0);
-      g[j] = of_expert(e);
-      row[j] = Wg + (size_t)e * d;
+      float w[V];
+      Vec16<T>::unpack(raw[j], w);
+#pragma unroll
+      for (int i = 0; i < V; ++i) acc[i] = ok[j] ? fmaf(g[j], w[i], acc[i]) : acc[i];
     }
-#pragma unroll(K_MAX <= 4 ? 2 : 1)
-    for (int c = lane * V; c < d; c += 64 * V) {
-      float acc[V];
-      const uint4 own = Vec16<T>::load_raw(dx + c);
-      uint4 raw[K_MAX];
-#pragma unroll
-      for (int j = 0; j < K_MAX; ++j) raw[j] = Vec16<T>::load_raw(row[j] + c);
-      Vec16<T>::unpack(own, acc);
-#pragma unroll
-      for (int j = 0; j < K_MAX; ++j) {
-        float w[V];
-        Vec16<T>::unpack(raw[j], w);
-#pragma unroll
-        for (int i = 0; i < V; ++i) acc[i] = ok[j] ? fmaf(g[j], w[i], acc[i]) : acc[i];
-      }
-      Vec16<T>::store(dx + c, acc);
-    }
-    return;
-  }
-  for (int c0 = 0; c0 < d; c0 += 64 * V) {
-    const int c = c0 + lane * V;
-    const bool in = c < d;
-    float acc[V] = {};
-    if (in) Vec16<T>::load(dx + c, acc);
-#pragma unroll 4
-    for (int e = 0; e < E; ++e) {
-      const float g = of_expert(e);
-      float w[V] = {};
-      if (in) Vec16<T>::load(Wg + (size_t)e * d + c, w);
-#pragma unroll
-      for (int i = 0; i < V; ++i) acc[i] = fmaf(g, w[i], acc[i]);
-    }
-    if (in) Vec16<T>::store(dx + c, acc);
+    Vec16<T>::store(dx + c, acc);
   }
 }
 
@@ -256,22 +325,23 @@ __device__ __forceinline__ void dwg_partial(const TokenArgs& t, const DwgArgs& p
   }
 }
 
-// Both in one launch where neither needs the other (renormalising): the first n_dwg blocks make partial sums,
-// the others serve tokens.  Training step, two launches -> one: 1024 tokens, d = 1024, E = 32: 189 -> 185 us; fp32,
-// 1024 tokens, d = 512, E = 8: 197 -> 192; 8192 tokens, d = 2048: 768 -> 766; 8192 tokens, d = 1024, k = 8: 567 ->
-// 562: with many tokens the fp32 products of the partial sums (7 us at d = 2048) and 100 MB of memory share the time.
-// (Token blocks first, or both in turn: no difference.)  Without renormalising the partial sums take the logit
-// gradients from the launch before (n_dwg = 0 there).
-template <typename T, int K_MAX, bool ALIGNED>
-__global__ __launch_bounds__(256) void route_bwd_token_kernel(const TokenArgs t, const DwgArgs p, int n_dwg) {
-  __shared__ DwgShared<T> lds;
-  if ((int)blockIdx.x < n_dwg) dwg_partial<T, ALIGNED, true>(t, p, lds, (int)blockIdx.x);
-  else token_grads<T, K_MAX>(t, (int)blockIdx.x - n_dwg);
+template <typename T, int NE, int P>
+__global__ __launch_bounds__(256) void route_bwd_token_kernel(const TokenArgs t) {
+  token_grads<T, NE, P>(t, (int)blockIdx.x);
 }
 template <typename T, bool ALIGNED>
 __global__ __launch_bounds__(256) void route_bwd_dwg_partial_kernel(const TokenArgs t, const DwgArgs p) {
   __shared__ DwgShared<T> lds;
   dwg_partial<T, ALIGNED, false>(t, p, lds, (int)blockIdx.x);
+}
+// Both in one launch (renormalising, where neither needs the other): the first n_dwg blocks make partial sums,
+// the others serve tokens.
+template <typename T, int K_MAX, bool ALIGNED>
+__global__ __launch_bounds__(256) void route_bwd_joint_kernel(const TokenArgs t, const DwgArgs p, int n_dwg) {
+  __shared__ DwgShared<T> lds;
+  const int block = (int)blockIdx.x - n_dwg;
+  if (block < 0) dwg_partial<T, ALIGNED, true>(t, p, lds, (int)blockIdx.x);
+  else token_grads_selected<T, K_MAX>(t, block);
 }
 
 // Blocks 0 .. n_bias-1: dbias[e] = sum_t dlogits[t][e], a fixed reduction tree per expert.  The
@@ -325,24 +395,40 @@ __global__ void route_bwd_zero_kernel(float* __restrict__ p, size_t n) {
     p[i] = 0.f;
 }
 
-template <typename T, int K_MAX, bool ALIGNED>
-void launch_parts_as(const TokenArgs& t, const DwgArgs& w, int n_dwg, hipStream_t s) {
-  const int n_tok = (t.Tn + 3) / 4, first = t.renormalize ? n_dwg : 0;
-  hipLaunchKernelGGL((route_bwd_token_kernel<T, K_MAX, ALIGNED>), dim3(first + n_tok), dim3(256), 0, s, t, w, first);
-  if (n_dwg > first)
+template <typename T, bool ALIGNED>
+void launch_parts(const TokenArgs& t, const DwgArgs& w, int n_dwg, bool joint, hipStream_t s) {
+  const int n_tok = (t.Tn + 3) / 4;
+  if (joint) {
+    auto kern = t.k <= 2   ? route_bwd_joint_kernel<T, 2, ALIGNED>
+                : t.k <= 4 ? route_bwd_joint_kernel<T, 4, ALIGNED>
+                : t.k <= 8 ? route_bwd_joint_kernel<T, 8, ALIGNED>
+                           : route_bwd_joint_kernel<T, MOE_MAX_TOPK, ALIGNED>;
+    hipLaunchKernelGGL(kern, dim3(n_dwg + n_tok), dim3(256), 0, s, t, w, n_dwg);
+    return;
+  }
+  constexpr int MANY = MOE_MAX_EXPERTS / 64;
+  const bool two = t.d > 64 * Vec16<T>::N && (!t.renormalize || t.k > 4);   // pieces of a row at a time
+  auto token = t.E <= 64 ? (two ? route_bwd_token_kernel<T, 1, 2> : route_bwd_token_kernel<T, 1, 1>)
+                         : (two ? route_bwd_token_kernel<T, MANY, 2> : route_bwd_token_kernel<T, MANY, 1>);
+  hipLaunchKernelGGL(token, dim3(n_tok), dim3(256), 0, s, t);
+  if (n_dwg > 0)
     hipLaunchKernelGGL((route_bwd_dwg_partial_kernel<T, ALIGNED>), dim3(n_dwg), dim3(256), 0, s, t, w);
 }
-template <typename T>
-void launch_parts(const TokenArgs& t, const DwgArgs& w, int n_dwg, bool aligned, hipStream_t s) {
-  auto run = [&](auto al) {
-    constexpr bool AL = decltype(al)::value;
-    if (t.k <= 2) launch_parts_as<T, 2, AL>(t, w, n_dwg, s);
-    else if (t.k <= 4) launch_parts_as<T, 4, AL>(t, w, n_dwg, s);
-    else if (t.k <= 8) launch_parts_as<T, 8, AL>(t, w, n_dwg, s);
-    else launch_parts_as<T, MOE_MAX_TOPK, AL>(t, w, n_dwg, s);
-  };
-  if (aligned) run(std::true_type{});
-  else run(std::false_type{});
+
+// One launch or two where one is possible.  One saves 2 to 3 us of start and gap, but its token blocks get half as
+// many wavefronts, and its weight-gradient blocks make the logit gradients again, once per 16 experts and 128 (64)
+// columns.  Call, us, two launches -> one (n_dwg: blocks of the weight gradient):
+//   512 blocks or less: 1024 tokens, d = 1024, E = 32, k = 2: 11.9 -> 9.8; 2048, 2048, 32, 4: 18.0 -> 15.2; 8192, 1024, 8,
+//   2: 22.0 -> 19.2; 2048, 1024, 64, 8: 16.9 -> 15.6
+//   768: 2048, 1536, 64, 8: 21.5 -> 20.1; 3072, 1024, 64, 8: 20.5 -> 21.3; 1024: 2048, 2048, 64, 6: 23.7 -> 22.1, k = 8: 24.7 ->
+//   25.3; 4096, 2048, 32, 4: 24.9 -> 26.2; 1536: 3072, 2048, 64, 6: 28.4 -> 30.1, k = 8: 29.6 -> 33.7; few tokens: 700, 4096,
+//   128, 6: 32.7 -> 27.1
+//   2048: 8192, 2048, 32, 4: 44.4 -> 48.5; 4096, 2048, 64, 6: 38.2 -> 45.0; 8192: 8192, 4096, 64, 7: 117 -> 153
+//   more than eight selected experts (three wavefronts per SIMD): 1024, 4096, 32, 12: 25.5 -> 22.5; 4096, 136, 32, 12: 15.4 ->
+//   15.2; 8192, 512, 16, 9: 21.1 -> 25
+bool joint_wanted(int T, int n_dwg, int k, int n_cu) {
+  if (k > 8) return n_dwg <= 2 * n_cu && T <= 16 * n_cu;
+  return n_dwg <= (k > 6 ? 3 : T > 4 * n_cu ? 5 : 8) * n_cu;
 }
 
 }  // namespace
@@ -370,8 +456,9 @@ int launch_route_bwd(moe_ctx* c, const void* x, const void* Wg, const float* log
   const DwgArgs w = {x, n_cb, n_eg, chunks * n_cb, c->d_rbwd_ws};
   const int n_dwg = dWg != nullptr ? (w.n_tiles + 7) / 8 * 8 * n_eg : 0;
   const bool al = ((uintptr_t)x & 15) == 0;
-  if (c->cfg.dtype == MOE_BF16) launch_parts<uint16_t>(t, w, n_dwg, al, s);
-  else launch_parts<float>(t, w, n_dwg, al, s);
+  const bool joint = rn && n_dwg > 0 && (c->gate_joint != 0 ? c->gate_joint == 1 : joint_wanted(T, n_dwg, k, c->n_cu));
+  if (c->cfg.dtype == MOE_BF16) (al ? launch_parts<uint16_t, true> : launch_parts<uint16_t, false>)(t, w, n_dwg, joint, s);
+  else (al ? launch_parts<float, true> : launch_parts<float, false>)(t, w, n_dwg, joint, s);
   const size_t ed = dWg != nullptr ? (size_t)E * d : 0;
   const int n_bias = dbias != nullptr ? E : 0;
   if (ed > 0 || n_bias > 0)
@@ -379,3 +466,6 @@ int launch_route_bwd(moe_ctx* c, const void* x, const void* Wg, const float* log
                        s, c->d_rbwd_ws, chunks, ed, dWg, dlogits, T, E, n_bias, dbias);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
+
+// Not part of the interface, for tests: one launch (1) or two (2) for the logit and the weight gradients (0: the rule).
+extern "C" void moe_internal_gate_joint(moe_ctx* c, int32_t joint) { c->gate_joint = joint; }

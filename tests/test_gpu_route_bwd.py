@@ -131,3 +131,32 @@ def test_gradients_that_are_not_finite_show_in_both_outputs(bad, renorm):
     assert not torch.isfinite(dl[150]).any() and torch.isfinite(dl[:150]).all() and torch.isfinite(dl[151:]).all()
     assert not torch.isfinite(dWg).any()
     moe.moe_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T,d,E,k", [
+    (131, 136, 17, 1), (260, 520, 64, 2),   # one piece of a row or a bit of it (f32: two and a bit)
+    (77, 1160, 65, 4), (64, 2056, 40, 7), (33, 1032, 256, 16),
+])
+def test_one_launch_and_two_give_the_same(dtype, T, d, E, k):
+    """The logit gradients beside the weight gradient's sums or before them, with and without dx; and a routing that
+    names experts that do not exist."""
+    ctx = moe.moe_create(T_max=T, d=d, E=E, k=k, f=8, R=1, renormalize=1,
+                         dtype=moe.MOE_BF16 if dtype == torch.bfloat16 else moe.MOE_F32)
+    g = torch.Generator(device="cuda").manual_seed(7 + T)
+    x, Wg, dx = (torch.randn(n, d, device="cuda", generator=g).to(dtype) for n in (T, E, T))
+    idx, w, _ = moe.moe_route(ctx, x, Wg, None)
+    idx[T // 2, 0], idx[T // 3, k - 1] = E, -1
+    dw = torch.randn(T, k, device="cuda", generator=g)
+    got = {}
+    for joint in (1, 2):
+        moe.load_library().moe_internal_gate_joint(ctx.handle, joint)
+        out = dx.clone()
+        dl, dWg, db = moe.moe_route_bwd(ctx, x, Wg, idx, w, dw, dx=out, want_dbias=True)
+        only = moe.moe_route_bwd(ctx, x, Wg, idx, w, dw)
+        torch.cuda.synchronize()
+        assert torch.equal(only[0], dl) and torch.equal(only[1], dWg)
+        got[joint] = (dl, dWg, db, out)
+    for a, b in zip(got[1], got[2]):
+        assert torch.equal(a, b)
+    moe.moe_destroy(ctx)
