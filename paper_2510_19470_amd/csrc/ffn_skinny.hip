@@ -3,8 +3,8 @@
 // What bounds it is reading every weight of the used experts once.  The 256-row tiles of
 // ffn_mfma_kernel serve that badly where few experts are used: one block per 128 to 256 weight
 // rows leaves compute units idle and needs a K-split with partial sums through memory, and a
-// tile list has to be built first.  Here a block takes 16 or 32 weight rows (of W1 and the same ones
-// of W3 for gate/up), its 8 wavefronts cut the contraction among themselves in units of 64 (one
+// tile list has to be built first.  Here a block takes 16 weight rows (of W1 and the same ones
+// of W3 for gate/up; of a single matrix 32 in small calls), its 8 wavefronts cut the contraction among themselves in units of 64 (one
 // 128-byte line per weight row), and nothing is staged: a weight fragment is one 16-byte load per
 // lane, used for all of the expert's rows, and the wavefronts' sums meet in LDS (added in
 // wavefront order: deterministic).  No schedule launch, no partial sums in memory.  The token rows
@@ -197,16 +197,19 @@ __global__ __launch_bounds__(NT, 4) void ffn_skinny_kernel(const SkinnyArgs p) {
 
 template <int MODE>
 int launch(const SkinnyArgs& a, int T, hipStream_t s) {
-  // A wavefront has K / 512 units: with four or less it asks for all of them at once, and a block that takes 32
-  // weight rows has twice as much in flight behind one start (kernel arguments, counts, sums).  16 rows -> 32,
-  // pass, us: d = 1024, f = 4096, T = 8: 38.5 -> 37.2, T = 16 on 16 experts: 97.2 -> 93.3; d = 2048, f = 1408, T = 16:
-  // 75.1 -> 72.7; two-matrix, 1536 x 3072: 47.2 -> 45.7.  With longer rows there are too few blocks (up to K =
-  // 4096: 38.6 -> 40.4, 78 -> 86), and with more token rows too few registers.
-  if (T <= 16 && a.K <= 2048) {
-    const dim3 grid((a.N + 2 * WROWS - 1) / (2 * WROWS), a.n_list);
-    hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 2>), grid, dim3(NT), 0, s, a);
-    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
-  }
+  // One matrix: a wavefront has K / 512 units, with four or less it asks for all of them at once (16 registers a unit
+  // and row group; with two matrices only half of them would fit), and a block that takes 32 weight rows has twice as
+  // much in flight behind one start (kernel arguments, counts, sums).  16 rows -> 32, both GEMMs, us: 2048 x 1408, 12 of 64
+  // experts, T = 8: 57.8 -> 54.4, T = 16: 57.2 -> 53.5; 4096 x 2048, 16 experts, T = 16: 161 -> 152; two-matrix, 2048 x
+  // 14336, T = 8: 201 -> 183.  For gate/up as well: 2048 x 4096, 16 experts, T = 12: 159 -> 167 to 176; 1024 x 4096, 6 of 16,
+  // T = 8: 40.5 -> 43.0.  Rows up to 4096: 2048 x 4096, T = 12: 159 -> 164; one token on 1024 x 4096: 18.2 -> 21.5; two-matrix
+  // 3072 x 3072, T = 8: 71 -> 65.  With more token rows there are too few registers.
+  if constexpr (MODE != SK_UP)
+    if (T <= 16 && a.K <= 2048) {
+      const dim3 grid((a.N + 2 * WROWS - 1) / (2 * WROWS), a.n_list);
+      hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 2>), grid, dim3(NT), 0, s, a);
+      return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+    }
   const dim3 grid((a.N + WROWS - 1) / WROWS, a.n_list);
   hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 1>), grid, dim3(NT), 0, s, a);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
