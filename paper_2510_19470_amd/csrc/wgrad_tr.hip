@@ -76,7 +76,7 @@ struct WgradArgs {
 // a 128-byte line: pieces of lines lose (1160 x 2888: 291 -> 296; 648 x 1400: 243 -> 248).
 template <bool RAG, bool LINES, int NI = 4, int NJ = 2>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][4], float* dW, int m0, int n0, int Mo, int No,
-                                              int lane) {
+                                           int lane) {
   const int col = lane & 31, half = lane >> 5;
 #pragma unroll
   for (int i = 0; i < NI; ++i)
@@ -94,6 +94,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][4], float* dW,
         }
       }
 }
+
 // RAG: some last block is not whole (d or f no multiple of 256): columns are clamped and guarded.
 // A kernel of its own, so that whole sizes do not pay for the guards of the stores.  LINES: see store_tile
 // (a template argument: of two ways to store in one kernel the compiler makes one, the plain one).
