@@ -196,6 +196,7 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
   const int lc = (lane & 7) ^ swz(8 * wave + (lane >> 3));   // the lane's chunk of a row-major step
   uint32_t a_off[4], b_off[4];
   const char *a_base, *b_base0, *b_base1;
+  bool once;
   auto open = [&](const Unit128& u) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -215,6 +216,7 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
                            : (size_t)u.nblk * (MODE == MODE_UP ? 64 : TN) * b_pitch;
     b_base0 = uniform_ptr((const char*)map.b0[u.expert] + ofs);
     b_base1 = uniform_ptr((const char*)map.b1[u.expert] + ofs);
+    once = u.once && (BKM || (((uintptr_t)b_base0 | (uintptr_t)b_base1 | b_pitch) & 127) == 0);
   };
   // copies of step t into stage t & 1: weight rows, then the token rows' na blocks
   auto issue = [&](const Unit128& u, int na, int t) {
@@ -240,11 +242,14 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
       if (i < na) dma16(a_off[i], a, dst + OPERAND + i * 4096);
     // Weights that one tile alone reads are copied past the last-level cache, where they would displace
     // activations and weights that are read again.  64 tokens, 8 experts of 4096 x 14336: pass 518 -> 465 us (gate/up
-    // 5.8 -> 6.5 TB/s); two-matrix training, 64 rows per expert of 1024 x 4096: 225 -> 200.  It pays on layers that
-    // fit the cache as well, as long as other layers run in between (100 tokens, 8 experts of 1024 x 2048, 101 MB
-    // of weights: 54 -> 47); a layer that runs alone again and again with 150 to 200 MB of weights loses (49 -> 52).  With
-    // two row blocks the second one finds the weights in L2 less often: 250 rows per expert, 1160 x 2888: 117 -> 133.
-    if (u.once) {
+    // 5.8 -> 6.5 TB/s); two-matrix training, 64 rows per expert of 1024 x 4096: 225 -> 200.  Rows in pieces of 128 bytes only
+    // where those are lines (177 tokens, 1880 x 3928: 243 -> 283; 2858 tokens, 1528 x 2592: 156 -> 173; k-major ones in pieces of
+    // 256 anywhere: backward, 584 tokens, 1888 x 2256: 176 -> 156).  It pays on
+    // layers that fit the cache as well, as long as other layers run in between (four in turn, 151 MB of weights:
+    // 50 -> 45, 208 MB: 59 -> 55); one that runs alone again and again loses (101 MB: 28 -> 31, 151: 37 to 40 -> 44,
+    // 208: 43 -> 58, 302: 65 -> 67).  With two row blocks the second one finds the weights in L2 less often: 250
+    // rows per expert, 1160 x 2888: 117 -> 133.
+    if (once) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) dma16_once(b_off[i], b[i >> 1], dst + i * 4096);
     } else {
