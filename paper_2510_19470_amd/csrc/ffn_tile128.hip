@@ -39,6 +39,7 @@ struct TileArgs {
   int E, S;
   TileSched* status;             // n_mtiles for the kernels after this one: 0 if counts do not fit
   bool offered;                  // dH: status is the larger tiles' schedule, and says whose turn it is
+  bool again;                    // forward: the pass reads the weights again
 };
 
 // Row blocks of all experts, counted by every block for itself: start[e] is the first one of expert e.
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
                            : (size_t)u.nblk * (MODE == MODE_UP ? 64 : TN) * b_pitch;
     b_base0 = uniform_ptr((const char*)map.b0[u.expert] + ofs);
     b_base1 = uniform_ptr((const char*)map.b1[u.expert] + ofs);
-    once = u.once && (BKM || (((uintptr_t)b_base0 | (uintptr_t)b_base1 | b_pitch) & 127) == 0);
+    once = u.once && (BKM || (!p.again && (((uintptr_t)b_base0 | (uintptr_t)b_base1 | b_pitch) & 127) == 0));
   };
   // copies of step t into stage t & 1: weight rows, then the token rows' na blocks
   auto issue = [&](const Unit128& u, int na, int t) {
@@ -244,7 +245,8 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
     // activations and weights that are read again.  64 tokens, 8 experts of 4096 x 14336: pass 518 -> 465 us (gate/up
     // 5.8 -> 6.5 TB/s); two-matrix training, 64 rows per expert of 1024 x 4096: 225 -> 200.  Rows in pieces of 128 bytes only
     // where those are lines (177 tokens, 1880 x 3928: 243 -> 283; 2858 tokens, 1528 x 2592: 156 -> 173; k-major ones in pieces of
-    // 256 anywhere: backward, 584 tokens, 1888 x 2256: 176 -> 156).  It pays on
+    // 256 anywhere: backward, 584 tokens, 1888 x 2256: 176 -> 156), and not where the pass itself
+    // reads them again (chunks of a pipeline: 2048 tokens in four, 12 of 64 experts of 2048 x 1408: 271 -> 310).  It pays on
     // layers that fit the cache as well, as long as other layers run in between (four in turn, 151 MB of weights:
     // 50 -> 45, 208 MB: 59 -> 55); one that runs alone again and again loses (101 MB: 28 -> 31, 151: 37 to 40 -> 44,
     // 208: 43 -> 58, 302: 65 -> 67).  With two row blocks the second one finds the weights in L2 less often: 250
@@ -375,6 +377,7 @@ TileArgs tile_args(const moe_ctx* c, const int32_t* counts, const int32_t* offse
   a.E = c->cfg.E;
   a.S = c->S_call;
   a.status = c->d_sched[1];
+  a.again = c->weights_again;
   return a;
 }
 

@@ -51,6 +51,7 @@ struct moe_ctx {
                           // 16 the few-rows kernel (0: the rules)
   int wgrad_rows;         // ... 128 or 256 the weight gradients for few or for many rows per expert
   int gate_joint;         // ... 1 or 2 the gate backward's logit and weight gradients in one launch or in two
+  bool weights_again;     // other calls of the same pass read the weights too (a pipeline's chunks)
   // placement
   int32_t* d_dest_rank;   // [E]
   int32_t* d_seg_pos;     // [E] position of every expert in (dest_rank, id) order

@@ -71,6 +71,7 @@ int moe_pipeline_create(moe_pipeline** out, const moe_config* cfg, int32_t n_chu
       destroy(p);
       return st;
     }
+    c->weights_again = n_chunks > 1;
     p->ctx.push_back(c);
     hipStream_t s = nullptr;
     hipEvent_t e = nullptr;
