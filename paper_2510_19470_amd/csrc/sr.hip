@@ -205,13 +205,13 @@ struct SrLane {
     __builtin_memcpy(&q, e, 16);
     return q;
   }
-  template <bool ONCE = false>
+  template <bool ONCE = false>   // of W
   __device__ __forceinline__ void load(const T* __restrict__ W, const T* __restrict__ S, int64_t c,
                                        int64_t n) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) w[v] = load_vec<ONCE>(W, first(c, v), n);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) s[v] = load_vec<ONCE>(S, first(c, v), n);
+    for (int v = 0; v < NV; ++v) s[v] = load_vec(S, first(c, v), n);
   }
   __device__ __forceinline__ void residual(int v, float (&r)[V]) const {
     float a[V], b[V];
@@ -837,7 +837,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
   const int64_t c = blockIdx.x, start = c * SR_CHUNK, end = min(n, start + SR_CHUNK);
   uint4 q[NV];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) q[v] = Lane::template load_vec<ONCE>(S, Lane::first(c, v), n);
+  for (int v = 0; v < NV; ++v) q[v] = Lane::load_vec(S, Lane::first(c, v), n);
   if (threadIdx.x < 128) {   // lower_bound of start (wavefront 0) / end (wavefront 1), 64 probes
                              // per round (4 rounds for a million entries)
     const int lane = threadIdx.x & 63;
@@ -893,10 +893,16 @@ __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
   }
 }
 
-// Matrices that are read and written past the last-level cache (256 MB): where the encode's two do not leave
-// room in it for anything else, their next reader does not find them there either.  Encode and decode, us,
-// plain -> past the cache: 117 MB a matrix 139.5 -> 129.7, 235 MB (fp32, k = n / 10) 474 -> 451, 42 MB 80.1 -> 76.9;
-// 17 MB, three matrices in turn, which the cache holds: 41.7 -> 42.0.
+// From two matrices of 64 MB on, the expert's is read past the last-level cache (256 MB) and the rebuilt one written
+// past it; the shared one, which the next expert's encode or decode reads again, is not.  Plain -> all three past the
+// cache -> this, us:
+//   one of eight experts encoded in a row, 42, 64, 117 MB a matrix: 47.0, 58.0, 77.5 -> 47.7, 59.2, 81.1 -> 46.1, 56.7, 76.0;
+//   fp32, 235 MB: 195 -> 182 -> 173
+//   decoded in a row, 42, 64, 117 MB: 24.4, 33.3, 55.3 -> 21.2, 28.9, 49.4 -> 20.3, 28.7, 49.3
+//   an expert's three matrices decoded and the expert computed for 8 tokens, 34, 42, 67, 117 MB: 87, 112, 156, 261 -> 84, 111,
+//   151, 244 -> 83, 109, 152, 245; four experts decoded, then computed: 92, 118, 161, 257 -> 80, 111, 151, 243 -> 84, 109, 148,
+//   245.  (Where nothing but a copy of it follows a decode, 42 to 64 MB lose 1 %.)
+//   17 MB, plain -> past the cache, three matrices in turn, which it holds: 41.7 -> 42.0
 bool sr_once(int64_t n, size_t elem) { return 2 * n * (int64_t)elem >= (int64_t)64 << 20; }
 
 // blocks of the launches that deal chunks out: two per compute unit
