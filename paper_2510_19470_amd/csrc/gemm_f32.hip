@@ -265,9 +265,9 @@ __global__ __launch_bounds__(NTHR) void ffn_f32_kernel(const F32Args p) {
   constexpr bool WK = MODE == F_UP || MODE == F_UP1 || MODE == F_DOWN;   // weights contiguous in k
   constexpr int NB = MODE == F_UP ? 2 : 1;
   // LDS stages, all but one in flight from memory.  64x64 tiles: two, so that five blocks share a compute unit's LDS
-  // instead of three and cover each other's waits (2048 tokens, d = 1024, f = 2048, 6 of 8 experts, step: 1408 -> 1346
-  // us; forward, 2000 tokens, 1000 x 1800: 391 -> 385).  32x32 tiles have six blocks with three of them (two: 194 ->
-  // 196.5, 1024 tokens, 512 x 1024; four: 3-10 % slower).
+  // instead of three (with two weight matrices three instead of two) and cover each other's waits (2048 tokens, d =
+  // 1024, f = 2048, 6 of 8 experts, step: 1408 -> 1346 us; forward, 2000 tokens, 1000 x 1800: 391 -> 385).  32x32 tiles
+  // have six blocks (four) with three of them (two: 194 -> 196.5, 1024 tokens, 512 x 1024; four: 3-10 % slower).
   constexpr int STAGES = TM == 64 ? 2 : 3;
   typedef Mma<TM, TN, NB, true, WK, STAGES> M;
   __shared__ __align__(16) float lds[STAGES * M::STAGE];
@@ -381,11 +381,13 @@ void launch_tile(const moe_ctx* c, const F32Args& a, hipStream_t s) {
   hipLaunchKernelGGL((ffn_f32_kernel<MODE, TM, TN>), grid, dim3(NTHR), 0, s, a);
 }
 
-// 64x64 tiles while they give every compute unit the three blocks its LDS holds, else 32x32: few
-// large tiles leave units idle or put two blocks on one (measured, us, 64x64 | 32x32; gate/up,
-// down, dH, dX): 1024 rows, d = 512, f = 1024, 130-270 tiles of 64x64: 45, 41, 29, 82 | 39, 22, 26,
-// 43; 8192 rows, d = 1024, f = 2048, 2100-4200 tiles: 619, 333, 357, 677 | 704, 424, 391, 803
-// (the 32x32 tile reads twice as much from L2 per flop).
+// 64x64 tiles from three of them per compute unit on, else 32x32: few large tiles leave units idle or make a round of
+// a few; the 32x32 tile reads twice as much from L2 per flop.  64x64 against 32x32, us a GEMM, in the mean over 70 layers
+// of 512 to 2048 tokens with an even routing, by the expected number of 64x64 tiles (gate/up, down, dH, dX; three blocks
+// of 64x64 fit a unit in gate/up, five in the others):
+//   300 to 400: +22, +30, +8, +61; 512 to 640: +18, +7, +7, +6; 640 to 768: +18, +6, +2, -9; 768 to 900: -12, -15, -18, -38;
+//   2000 and more: -89, -156, -74, -332.  Popularity as rank^-1 makes more tiles than expected: down and dX gain from 400 on
+//   (-20, -58), gate/up and dH from 770.
 template <int MODE>
 void launch_mode(const moe_ctx* c, const F32Args& a, hipStream_t s) {
   int present = 0;
