@@ -47,13 +47,13 @@ struct TileArgs {
 // cold loads otherwise, 1 to 2 us each).
 struct TileMap {
   int32_t start[MOE_MAX_EXPERTS + 1];
-  int32_t wave_sum[NT / 64];
+  int32_t wave_sum[NT / 64], wave_used[NT / 64];
   int32_t rows[MOE_MAX_EXPERTS], row0[MOE_MAX_EXPERTS];
   const void *b0[MOE_MAX_EXPERTS], *b1[MOE_MAX_EXPERTS];
 };
 // Called by all threads; returns the number of row blocks (0 when a segment of a present expert does not
-// lie inside the S rows of the buffers, or they are more than S rows can have).
-__device__ __forceinline__ int count_tiles(const TileArgs& p, TileMap& m) {
+// lie inside the S rows of the buffers, or they are more than S rows can have) and the experts that have any.
+__device__ __forceinline__ int count_tiles(const TileArgs& p, TileMap& m, int& used) {
   static_assert(NT == MOE_MAX_EXPERTS, "one expert per thread");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int mine = 0;
@@ -78,37 +78,43 @@ __device__ __forceinline__ int count_tiles(const TileArgs& p, TileMap& m) {
     const int v = __shfl_up(incl, off, 64);
     if (lane >= off) incl += v;
   }
-  if (lane == 63) m.wave_sum[wave] = incl;
+  const int some = __popcll(__ballot(mine > 0));
+  if (lane == 63) m.wave_sum[wave] = incl, m.wave_used[wave] = some;
   const int any_bad = __syncthreads_or(bad);
   for (int w = 0; w < wave; ++w) incl += m.wave_sum[w];
   m.start[tid + 1] = incl;
   if (tid == 0) m.start[0] = 0;
   __syncthreads();
+  used = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) used += __builtin_amdgcn_readfirstlane(m.wave_used[w]);
   const int total = __builtin_amdgcn_readfirstlane(m.start[MOE_MAX_EXPERTS]);
   return any_bad || total > p.S / TM + p.E ? 0 : total;   // (segments that overlap)
 }
 
 // Parts of every contraction of a launch of `tiles` tiles on `slots` resident blocks, two on a compute unit: the
-// number that is done first by its k-steps, each 2.3 times as long where there are units with two blocks, and a
-// level of neighbours that add their sums (join_parts) counted as 3.5 of them.  Kernel time, us, 1, 2, 3, 4 ... 8
-// parts (behind the semicolon units have two blocks): 64 tiles of 64 steps 44, 28, 23, 22; 28, 28, 29, 29; 48 of 32:
-// 24, 18, 17, 16, 18; 20, 21, 22; 96 of 16: 16, 15; 17, 21; 120 of 46: 44, 31; 40, 41; 140 of 46: 44; 49, 41; 168 of 64:
-// 52; 52, 43; 192 of 22: 24; 29, of 64: 56; 57.  Pass, us, as many parts as there are blocks for -> these: two-matrix
-// step, 64 rows, 1024 x 4096: 195 -> 179; step of 2048 tokens, 1024 x 1024: 172 -> 155; step, 125 rows, 1160 x 2888:
-// 294 -> 270.
+// number that is done first by its k-steps and the levels of neighbours that add their sums (join_parts), 3.9 steps each.
+// Where there are units with two blocks, a step is 2.3 times as long if every tile has weights of its own, which one
+// block on every unit streams as fast as they come, and 1.8 times if tiles share them (one_block: experts have
+// one row block, or three in two of them at most).  From 482 GEMMs of 2 to 256 tiles, 8 to 256 steps, 5 to 1000 rows
+// per expert, forward and backward, weights from HBM, with every number of parts; from the fastest one, mean and
+// most: one row block 0.2 us, 5 us (1.8: 0.6, 14 us); more of them 0.3, 9 us (2.3: 2.1, 60 us or 24 %); as many parts as
+// there are blocks for 2.8 us, 29 %.  Both GEMMs, us, 1, 2, 3, 4 ... parts of the second: one row block: 12 tiles of 46
+// steps 55, 41, 38, 36, 37, 35, 34, 35; 48 of 64: 67, 50, 46, 44, 45, 49; 128 of 16: 42, 42, 45, 47; 240 of 112: 163, 174; more: 96
+// of 128: 141, 98, 88, 86, 85; 216 of 94: 206, 181; 192 of 256: 310, 250.
 __host__ __device__ inline int join_levels(int parts) { return parts > 4 ? 3 : parts > 2 ? 2 : parts - 1; }
-__host__ __device__ inline int parts_of(int tiles, int slots, int kt) {
+__host__ __device__ inline int parts_of(int tiles, int slots, int kt, bool one_block) {
   auto best = [&](int most, float two) {
     const int one_each = slots / 2 > SPLIT_MAX ? slots / 2 : SPLIT_MAX;
     int parts = 1;
     float least = (float)kt;
     for (int n = 2; n <= most && tiles * n <= slots && kt / n >= SPLIT_STEPS; ++n) {
-      const float t = (float)((kt + n - 1) / n) * (tiles * n <= one_each ? 1.f : two) + 3.5f * join_levels(n);
+      const float t = (float)((kt + n - 1) / n) * (tiles * n <= one_each ? 1.f : two) + 3.9f * join_levels(n);
       if (t < least) least = t, parts = n;
     }
     return parts;
   };
-  return best(best(SPLIT_MAX, 1.f), 2.3f);   // no more than of one tile alone: the workspace is sized for those
+  return best(best(SPLIT_MAX, 1.f), one_block ? 2.3f : 1.8f);   // no more than of one tile alone: the workspace is sized for those
 }
 
 // One tile, or one part of its contraction (all fields wave-uniform).
@@ -163,8 +169,9 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
   if ((MODE == MODE_DH || MODE == MODE_DH1) && p.offered && p.status->dh_small == 0) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int total = count_tiles(p, map) * g.n_tiles_n;
-  const int split = CUT ? parts_of(total, gridDim.x, g.kt) : 1;
+  int used;
+  const int blocks128 = count_tiles(p, map, used), total = blocks128 * g.n_tiles_n;
+  const int split = CUT ? parts_of(total, gridDim.x, g.kt, 2 * blocks128 < 3 * used) : 1;
   if (blockIdx.x == 0 && threadIdx.x == 0 && !p.offered) p.status->n_mtiles = total;
   const int units = total * split;
   // The idx-th unit of this block: rounds of gridDim.x units, a round in 8 chunks of consecutive ones
@@ -389,7 +396,7 @@ int slots(const moe_ctx* c) { return slots_of(c->n_cu); }
 size_t split_floats(int S, int E, int d, int f, int n_cu) {
   const long long blocks = (long long)S / TM + E;
   auto tiles = [&](int kt, int cols) {
-    const int most = parts_of(1, SPLIT_MAX, kt);
+    const int most = parts_of(1, SPLIT_MAX, kt, true);
     return most == 1 ? 0 : std::min<long long>(slots_of(n_cu), blocks * cols * most);
   };
   return (size_t)std::max(tiles(2 * ceil_div(f, BK), ceil_div(d, TN)) /* dX */,
@@ -471,7 +478,7 @@ static double us_256(int experts, int rows, int N, int bn, int K, int kt, bool d
 }
 static double us_128(int experts, int rows, int N, int bn, int kt, bool down, bool bwd, double mb, int n_cu) {
   const int blocks = ceil_div(rows, TM), tiles = experts * blocks * ceil_div(N, bn), slots = 2 * n_cu;
-  const int split = down ? parts_of(tiles, slots, kt) : 1, units = tiles * split, tail = units % slots;
+  const int split = down ? parts_of(tiles, slots, kt, blocks == 1) : 1, units = tiles * split, tail = units % slots;
   const double steps = (double)kt / split, full = 0.77 * rows / ((double)TM * blocks);
   const double loop = units / slots * (steps * (0.67 + full) + 1.26) +
                       (tail > 0 ? steps * (0.67 + full * tail / slots) + 1.26 : 0);
@@ -558,7 +565,10 @@ extern "C" void moe_internal_ffn_tile_us(int32_t experts, int32_t rows, int32_t 
   tile_us(experts, rows, d, f, gated != 0, backward != 0, n_cu, us[0], us[1]);
 }
 extern "C" int moe_internal_tile128_parts(int32_t tiles, int32_t slots, int32_t kt) {
-  return parts_of(tiles, slots, kt);
+  return parts_of(tiles, slots, kt, true);
+}
+extern "C" int moe_internal_tile128_parts_shared(int32_t tiles, int32_t slots, int32_t kt) {
+  return parts_of(tiles, slots, kt, false);
 }
 extern "C" int64_t moe_internal_tile128_split_floats(int32_t S, int32_t E, int32_t d, int32_t f, int32_t n_cu) {
   return (int64_t)split_floats(S, E, d, f, n_cu);

@@ -202,6 +202,7 @@ def test_weight_gradients_wherever_they_lie(d, f, few):
 
 @pytest.mark.parametrize("d,f,rows,parts", [
     (128, 4096, [40], 8), (1024, 1408, [64], 4), (1024, 4096, [128] * 10, 3), (2048, 2048, [100] * 8, 2),
+    (1536, 5888, [100] * 4, 5), (1280, 5888, [70] * 4, 6), (1152, 5888, [40] * 4, 7),   # a node without a neighbour
 ])
 def test_joined_parts_are_the_same_bits_every_time(d, f, rows, parts):
     """Which of two neighbouring parts is added by which block depends on who comes first; the sum and the counters
@@ -229,4 +230,33 @@ def test_joined_parts_are_the_same_bits_every_time(d, f, rows, parts):
         h = torch.relu(x[s].float() @ W1[e].float().t().contiguous())
         want = h.bfloat16().float() @ W2[e].float().t().contiguous()
         assert float((first[s].float() - want).norm() / want.norm()) <= 1e-2   # bf16 output and H: 2^-8 each
+    moe.moe_destroy(ctx)
+
+
+def test_cut_gate_up_saves_the_same_bits_every_time():
+    """The gated expert's first GEMM in four parts, two accumulator halves of 32 rows and a bit: H, G and U."""
+    from gpu_common import DEV, moe
+    lib, d, f, T = moe.load_library(), 2048, 512, 65
+    slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
+    assert lib.moe_internal_tile128_parts(-(-f // 64), slots, -(-d // 64)) >= 4
+    ctx = moe.moe_create(T_max=T, d=d, E=1, k=1, f=f, R=1, dtype=moe.MOE_BF16)
+    lib.moe_internal_ffn_tile_rows(ctx.handle, 128)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    W1, W3 = ([(torch.randn(f, d, device=DEV, generator=g) * d ** -0.5).bfloat16()] for _ in range(2))
+    W2 = [(torch.randn(d, f, device=DEV, generator=g) * f ** -0.5).bfloat16()]
+    x = torch.randn(T, d, device=DEV, generator=g).bfloat16()
+    cnt, off = torch.tensor([T], dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    first = None
+    for _ in range(20):
+        got = moe.moe_expert_ffn(ctx, x, cnt, off, W1, W3, W2, save=True)
+        torch.cuda.synchronize()
+        first = got if first is None else first
+        assert all(torch.equal(a, b) for a, b in zip(got, first))
+    y, G, U = first
+    for got, w in ((G, W1[0]), (U, W3[0])):
+        want = x.float() @ w.float().t().contiguous()
+        assert float((got.float() - want).norm() / want.norm()) <= 4e-3      # bf16 output: 2^-8 at most
+    h = (torch.nn.functional.silu(G.float()) * U.float()).bfloat16().float()
+    want = h @ W2[0].float().t().contiguous()
+    assert float((y.float() - want).norm() / want.norm()) <= 1e-2   # bf16 output, H, G and U: 2^-8 each
     moe.moe_destroy(ctx)

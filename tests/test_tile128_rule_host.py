@@ -118,3 +118,32 @@ def test_partial_sums_fit_the_workspace(n_cu):
                                 cut += 1
                     assert have <= slots * 128 * 128
     assert cut > 1000
+
+
+@pytest.mark.parametrize("n_cu", [8, 256, 304])
+def test_every_cut_gemm_fits_the_workspace_and_the_counters(n_cu):
+    """Gate/up of the gated expert (64 columns a tile) and of the two-matrix one, down and both dX contractions, with
+    tiles that share their weights or not: the partial tiles fit what moe_create allocates, and there are counters
+    for slots / 2 tiles."""
+    lib = moe.load_library()
+    lib.moe_internal_tile128_split_floats.restype = ctypes.c_int64
+    slots, cut = max(8, 2 * n_cu // 8 * 8), set()
+    for S in (0, 1, 127, 128, 1000, 20000):
+        for E in (1, 3, 40, 256):
+            for d in (8, 136, 512, 1160, 4096, 14336):
+                for f in (8, 64, 200, 512, 2888, 14336):
+                    have = lib.moe_internal_tile128_split_floats(S, E, d, f, n_cu)
+                    kd, kf = -(-d // 64), -(-f // 64)
+                    for name, kt, cols in (("gate/up", kd, kf), ("up", kd, -(-f // 128)), ("down", kf, -(-d // 128)),
+                                           ("dX", 2 * kf, -(-d // 128))):
+                        most = S // 128 + E                      # row blocks that the kernel counts up to
+                        for blocks in {1, 2, 3, 5, E, most // 2, most}:
+                            if not 1 <= blocks <= most:
+                                continue
+                            for parts_of in (lib.moe_internal_tile128_parts, lib.moe_internal_tile128_parts_shared):
+                                parts = parts_of(blocks * cols, slots, kt)
+                                if parts > 1:
+                                    assert blocks * cols * parts * 128 * 128 <= have
+                                    assert blocks * cols <= slots // 2 and parts <= 8
+                                    cut.add((name, parts))
+    assert {name for name, _ in cut} == {"gate/up", "up", "down", "dX"} and {n for _, n in cut} >= {2, 3, 4, 5, 6, 7, 8}
