@@ -456,68 +456,76 @@ int launch_ffn_tile128_dx(moe_ctx* c, bool gated, const int32_t* counts, const i
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
 }
 
-static bool dh_offered(long long S, int f, int E, int n_res, int slots) {
-  const long long rows = (S + E - 1) / E;
-  return n_res > 0 && n_res * ((rows + TM - 1) / TM) * ceil_div(f, TN) <= slots;
+// One round of 128-row tiles in dH, with `rows` rows on each of `experts` experts.
+static bool dh_one_round(int experts, long long rows, int f, int slots) {
+  return experts > 0 && experts * ((rows + TM - 1) / TM) * ceil_div(f, TN) <= slots;
 }
 
-// Time in us of a GEMM's launches with `rows` rows on each of `experts` experts and weights of `mb` MB: a
-// constant, and the rounds of tiles, or the weights from HBM where those take longer.  A k-step of a round
-// costs more the more of the chip has tiles, the more rows these hold and, in the larger tiles, where the
-// sizes are not multiples of theirs.  bwd: k-major weights, which the smaller tiles read in pieces of 256
-// bytes.  (Constants: least squares over 181 calls of 1 to 8400 tokens, forward or backward, with up to three
-// routings each and weights that are not in the last-level cache.  On 120 other calls either side is within
-// 15 % of what was measured in the mean square, their ratio within 9 %.)
+// Time in us of a GEMM's launch with `rows` rows on each of `experts` experts and weights of `mb` MB: a
+// constant, and the rounds of tiles, or the weights from HBM where those take longer; contractions are cut as the
+// kernels cut them.  A k-step of a round costs more the more of the chip has tiles, the more rows these hold and,
+// in the larger tiles, where the sizes are not multiples of theirs.  (Constants: least squares of the logarithms over
+// 331 calls of 1 to 8400 tokens, forward and backward, evenly routed and with all tokens on the same experts,
+// weights that are not in the last-level cache; three of them, at which the choice had been wrong, counted 20 times.
+// Either side is within 13 % of what was measured in the mean square, their ratio within 8 %; on 110 other calls
+// 15 % and 9 %.)
 static double us_256(int experts, int rows, int N, int bn, int K, int kt, bool down, bool bwd, double mb, int n_cu) {
   const int blocks = ceil_div(rows, 256), tiles = experts * blocks * ceil_div(N, bn), tail = tiles % n_cu;
   const int split = down ? split_parts(tail, n_cu, kt) : 1;
-  const double full = 1.21 * rows / (256.0 * blocks) + (K % 128 != 0 || N % bn != 0 ? 0.32 : 0);
-  const double loop = tiles / n_cu * (kt * (0.77 + full) + 2.35) +
-                      (tail > 0 ? (double)kt / split * (0.77 + full * tail * split / n_cu) + 2.35 : 0);
-  return (bwd ? 11.3 : 11.8) /* half of the schedule in it */ + (split > 1 ? 4.4 : 0) + std::max(loop, mb / (bwd ? 5.4 : 5.2));
+  const double full = 1.102 * rows / (256.0 * blocks) + (K % 128 != 0 || N % bn != 0 ? 0.234 : 0);
+  const double loop = tiles / n_cu * (kt * (0.729 + full) + 8.01) +
+                      (tail > 0 ? (double)kt / split * (0.729 + full * tail * split / n_cu) + 8.01 : 0);
+  return 6.3 /* half of the schedule in it */ + (split > 1 ? 8.73 : 0) + std::max(loop, mb / (bwd ? 5.59 : 4.87));
 }
-static double us_128(int experts, int rows, int N, int bn, int kt, bool down, bool bwd, double mb, int n_cu) {
+static double us_128(int experts, int rows, int N, int bn, int kt, bool cut, double mb, int n_cu) {
   const int blocks = ceil_div(rows, TM), tiles = experts * blocks * ceil_div(N, bn), slots = 2 * n_cu;
-  const int split = down ? parts_of(tiles, slots, kt, blocks == 1) : 1, units = tiles * split, tail = units % slots;
-  const double steps = (double)kt / split, full = 0.77 * rows / ((double)TM * blocks);
-  const double loop = units / slots * (steps * (0.67 + full) + 1.26) +
-                      (tail > 0 ? steps * (0.67 + full * tail / slots) + 1.26 : 0);
-  return 4.65 + (split > 1 ? 2.2 * join_levels(split) - 1 : 0) + std::max(loop, mb / (bwd ? 4.5 : 5.3));
+  const int split = cut ? parts_of(tiles, slots, kt, blocks == 1) : 1, units = tiles * split, tail = units % slots;
+  const double steps = (double)kt / split, full = 0.78 * rows / ((double)TM * blocks);
+  const double loop = units / slots * (steps * (0.577 + full) + 3.74) +
+                      (tail > 0 ? steps * (0.577 + full * tail / slots) + 3.74 : 0);
+  return 2.12 + 3.77 * join_levels(split) + std::max(loop, mb / 5.56);
 }
-// Both GEMMs of a call, larger and smaller tiles.
+// Both GEMMs of a call, larger and smaller tiles.  (dH: with its epilogue; beside the larger tiles it is offered to the
+// smaller ones, see ffn_tile128_dh_offered, and taken by the rounds of both as in mfma_sched_kernel.)
 static void tile_us(int experts, int rows, int d, int f, bool gated, bool backward, int n_cu, double& large,
                     double& small) {
   const int bn = gated && !backward ? 128 : 256;   // columns of the larger tiles, first GEMM
   const int segs = gated && backward ? 2 : 1;
   const double mb = 2e-6 * experts * d * f, mb1 = bn == 128 ? 2 * mb : mb, mb2 = segs * mb;
-  large = us_256(experts, rows, f, bn, d, k_steps(d, 1), false, backward, mb1, n_cu) +
-          us_256(experts, rows, d, 256, f, k_steps(f, segs), true, backward, mb2, n_cu) +
-          (backward ? 23.3 : 0) /* dH's epilogue */;
-  small = us_128(experts, rows, f, bn / 2, ceil_div(d, BK), false, backward, mb1, n_cu) +
-          us_128(experts, rows, d, TN, segs * ceil_div(f, BK), true, backward, mb2, n_cu) + (backward ? 9.35 : 0);
+  large = us_256(experts, rows, f, bn, d, k_steps(d, 1), false, backward, mb1, n_cu) + (backward ? 21.5 : 0);
+  small = us_128(experts, rows, f, bn / 2, ceil_div(d, BK), !backward, mb1, n_cu) + (backward ? 7.5 : 0);
+  if (backward && dh_one_round(experts, rows, f, 2 * n_cu)) {
+    const int rounds = ceil_div(experts * ceil_div(rows, 256) * ceil_div(f, 256), n_cu);
+    large = (2 < 3 * rounds ? small : large) + 6.93;
+  }
+  large += us_256(experts, rows, d, 256, f, k_steps(f, segs), true, backward, mb2, n_cu);
+  small += us_128(experts, rows, d, TN, segs * ceil_div(f, BK), true, mb2, n_cu);
 }
 
 // The smaller tiles are taken where by this estimate they are the faster ones for an even routing, and all
 // tokens on the same experts (more rows on fewer experts: more and fuller tiles) cost them no more than twice
-// what they gain there, and 5 us that the estimate cannot tell.  Besides, they are held to calls whose first GEMM
-// has at most two rounds of larger tiles with any routing or, forward, at most one row block per expert;
-// backward, one round with an even routing.  Both GEMMs with sums and schedule, larger tiles -> smaller ones, us:
-// even routing; popularity falling off as rank^-1.2; all tokens on the same experts
-// (T, d, f, E, k, resident):
-//   forward: 1999, 1160, 2888, 16, 2, 6: 101 -> 95; 153 -> 141; 153 -> 151
-//            two-matrix 1024, 1024, 4096, 32, 2, 8: 62 -> 50; 78 -> 69; 76 -> 65
-//            64, 4096, 14336, 8, 2, 8: 515 -> 486; 515 -> 496; 156 -> 151
-//            751, 664, 384, 64, 3, 11: 41 -> 25; 45 -> 25; 46 -> 26
-//            two-matrix 1277, 3584, 2432, 64, 2, 8: 109 -> 88; 137 -> 128; 130 -> 141
-//   backward: 2000, 768, 1024, 16, 4, 6: 83 -> 55; 94 -> 71; 100 -> 76
-//            1999, 1160, 2888, 16, 2, 6: 134 -> 101; 158 -> 182; 166 -> 187
-//   left to the larger ones, forward: 953, 4096, 1024, 64, 8, 12: 115 -> 95; 169 -> 195; 174 -> 240
-//            5765, 2816, 896, 16, 3, 3: 84 -> 87; 184 -> 202; 232 -> 327
-//            two-matrix 1000, 3072, 3072, 64, 6, 10: 128 -> 112; 162 -> 229; 260 -> 294
-//            1422, 1816, 2672, 8, 3, 3: 16 to 35 us slower with any routing
-//   backward: 2999, 3328, 1280, 64, 8, 8: 160 -> 148; 416 -> 472; 592 -> 843
-//            64, 4096, 14336, 8, 2, 8: 474 -> 547; 476 -> 570; 181 -> 172
-//            two-matrix 2166, 1792, 1408, 32, 4, 16: 102 -> 117; 117 -> 136; 112 -> 133
+// what they gain there.  Besides, they are held to calls whose first GEMM has at most two rounds of larger tiles with
+// any routing or, forward, at most one row block per expert; backward, one round with an even routing.  Of 287
+// measured calls that these lines admit the choice is the slower one by more than 3 % in 23 with an even routing (by 1 %
+// in the mean), 1 % in the mean with popularity falling off as rank^-1.2 or all tokens on the same experts.  Both GEMMs
+// with sums and schedule, larger tiles (backward: dH by turn) -> smaller ones, us: even routing; rank^-1.2; all
+// tokens on the same experts (T, d, f, E, k, resident):
+//   forward: 1999, 1160, 2888, 16, 2, 6: 101 -> 85; 153 -> 153; 155 -> 153
+//            two-matrix 1024, 1024, 4096, 32, 2, 8: 63 -> 44; 78 -> 64; 84 -> 66
+//            64, 4096, 14336, 8, 2, 8: 532 -> 451; 530 -> 459; 168 -> 135
+//            751, 664, 384, 64, 3, 11: 45 -> 22; 52 -> 27; 49 -> 26
+//            7513, 1536, 1536, 32, 1, 9, two-matrix: 80 -> 50; 86 -> 99; 86 -> 101
+//            275, 4096, 4480, 8, 3, 8: 247 -> 204; 253 -> 244; 146 -> 188
+//   backward: 2000, 768, 1024, 16, 4, 6: 64 -> 52; 84 -> 69; 92 -> 76
+//            1999, 1160, 2888, 16, 2, 6: 112 -> 101; 162 -> 183; 168 -> 187
+//            338, 3840, 3712, 64, 1, 16: 234 -> 209; 256 -> 251; 111 -> 104
+//   left to the larger ones, forward: 953, 4096, 1024, 64, 8, 12: 114 -> 89; 169 -> 196; 180 -> 241
+//            2615, 3840, 768, 64, 3, 22: 139 -> 131; 183 -> 203; 149 -> 192
+//            1422, 1816, 2672, 8, 3, 3: 95 -> 100; 170 -> 156; 191 -> 222
+//            two-matrix 1000, 3072, 3072, 64, 6, 10: 125 -> 91; 164 -> 239; 265 -> 304
+//   backward: 2999, 3328, 1280, 64, 8, 8: 128 -> 140; 421 -> 463; 602 -> 837
+//            996, 2304, 1664, 64, 8, 8: 94 -> 83; 146 -> 162; 235 -> 286
+//            two-matrix 2166, 1792, 1408, 32, 4, 16: 106 -> 107; 125 -> 135; 119 -> 132
 bool ffn_tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, bool backward, int n_cu) {
   if (n_res == 0) return false;
   const int cols = ceil_div(f, gated && !backward ? 128 : 256);
@@ -527,7 +535,7 @@ bool ffn_tile128_rule(int T, int d, int f, int E, int k, int n_res, bool gated, 
   double large, small, large_hot, small_hot;
   tile_us(n_res, rows, d, f, gated, backward, n_cu, large, small);
   tile_us(std::min(k, n_res), T, d, f, gated, backward, n_cu, large_hot, small_hot);
-  return small < large && small_hot - large_hot <= 2 * (large - small) + 5;
+  return small < large && small_hot - large_hot <= 2 * (large - small);
 }
 
 // dH where the larger tiles take the call: its long epilogue (five arrays of S x f) runs under another block's main
@@ -542,7 +550,7 @@ bool ffn_tile128_dh_offered(const moe_ctx* c) {
   if (c->tile_rows != 0) return c->tile_rows == 256 + TM;
   int n_res = 0;
   for (int e = 0; e < c->cfg.E; ++e) n_res += c->h_wtab[0][e] != nullptr;
-  return dh_offered(c->S_call, c->cfg.f, c->cfg.E, n_res, slots(c));
+  return dh_one_round(n_res, ((long long)c->S_call + c->cfg.E - 1) / c->cfg.E, c->cfg.f, slots(c));
 }
 
 bool ffn_tile128_wanted(const moe_ctx* c, bool gated, bool backward) {

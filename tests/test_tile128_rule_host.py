@@ -53,6 +53,32 @@ def test_rule_looks_at_both_gemms_and_at_tokens_that_agree(T, d, f, E, k, n_res,
     assert not tile128(T, d, f, E, k, n_res, gated, backward)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,n_res,gated,backward,want", [
+    # near the line; evenly routed, larger tiles (backward: dH by turn) -> smaller ones, us
+    (275, 4096, 4480, 8, 3, 8, True, False, True),       # 247 -> 204
+    (7513, 1536, 1536, 32, 1, 9, False, False, True),    # 80 -> 50
+    (1422, 1816, 2672, 8, 3, 3, True, False, False),     # 95 -> 100
+    (5102, 1976, 320, 32, 5, 16, True, False, False),    # 97 -> 106
+    (417, 2304, 3072, 64, 1, 19, True, True, True),      # 177 -> 153
+    (337, 3328, 2816, 32, 2, 14, True, True, True),      # 170 -> 154
+    (338, 3840, 3712, 64, 1, 16, True, True, True),      # 234 -> 209
+    (7216, 1280, 768, 8, 3, 4, False, True, False),      # 81 -> 91
+    (4778, 2048, 896, 16, 1, 11, True, True, False),     # 90 -> 94
+    (901, 2816, 896, 32, 6, 14, True, True, False),      # 104 -> 109
+])
+def test_rule_near_the_line(T, d, f, E, k, n_res, gated, backward, want):
+    assert tile128(T, d, f, E, k, n_res, gated, backward) == want
+
+
+def test_estimate_cuts_gate_up_as_the_kernel_does():
+    """Few tiles and a long contraction: the smaller tiles' gate/up is cut (8 parts of 64 steps), dH is not."""
+    parts = moe.load_library().moe_internal_tile128_parts(2, 2 * N_CU, 64)
+    assert parts == 8
+    forward = tile_us(1, 64, 4096, 128, True, False)[1]
+    backward = tile_us(1, 64, 4096, 256, False, True)[1]     # dH: two tiles of 64 steps as well
+    assert forward < backward - 20
+
+
 @pytest.mark.parametrize("backward", [False, True])
 def test_tokens_that_agree_cost_no_more_than_twice_the_gain(backward):
     taken = 0
