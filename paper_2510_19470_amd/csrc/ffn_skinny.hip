@@ -4,7 +4,7 @@
 // ffn_mfma_kernel serve that badly where few experts are used: one block per 128 to 256 weight
 // rows leaves compute units idle and needs a K-split with partial sums through memory, and a
 // tile list has to be built first.  Here a block takes 16 weight rows (of W1 and the same ones
-// of W3 for gate/up; of a single matrix 32 in small calls), its 8 wavefronts cut the contraction among themselves in units of 64 (one
+// of W3 for gate/up; 32 in small calls), its 8 wavefronts cut the contraction among themselves in units of 64 (one
 // 128-byte line per weight row), and nothing is staged: a weight fragment is one 16-byte load per
 // lane, used for all of the expert's rows, and the wavefronts' sums meet in LDS (added in
 // wavefront order: deterministic).  No schedule launch, no partial sums in memory.  The token rows
@@ -196,20 +196,25 @@ __global__ __launch_bounds__(NT, 4) void ffn_skinny_kernel(const SkinnyArgs p) {
 }
 
 template <int MODE>
-int launch(const SkinnyArgs& a, int T, hipStream_t s) {
-  // One matrix: a wavefront has K / 512 units, with four or less it asks for all of them at once (16 registers a unit
-  // and row group; with two matrices only half of them would fit), and a block that takes 32 weight rows has twice as
-  // much in flight behind one start (kernel arguments, counts, sums).  16 rows -> 32, both GEMMs, us: 2048 x 1408, 12 of 64
-  // experts, T = 8: 57.8 -> 54.4, T = 16: 57.2 -> 53.5; 4096 x 2048, 16 experts, T = 16: 161 -> 152; two-matrix, 2048 x
-  // 14336, T = 8: 201 -> 183.  For gate/up as well: 2048 x 4096, 16 experts, T = 12: 159 -> 167 to 176; 1024 x 4096, 6 of 16,
-  // T = 8: 40.5 -> 43.0.  Rows up to 4096: 2048 x 4096, T = 12: 159 -> 164; one token on 1024 x 4096: 18.2 -> 21.5; two-matrix
-  // 3072 x 3072, T = 8: 71 -> 65.  With more token rows there are too few registers.
-  if constexpr (MODE != SK_UP)
-    if (T <= 16 && a.K <= 2048) {
-      const dim3 grid((a.N + 2 * WROWS - 1) / (2 * WROWS), a.n_list);
-      hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 2>), grid, dim3(NT), 0, s, a);
-      return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
-    }
+int launch(const SkinnyArgs& a, int T, int n_cu, hipStream_t s) {
+  // A wavefront has K / 512 units.  Where it can ask for all of them at once (16 registers a unit and row group: four
+  // units of one matrix, two of two), a block that takes 32 weight rows has twice as much in flight behind one start
+  // (kernel arguments, counts, sums).  16 rows -> 32, both GEMMs, us; one matrix: 2048 x 1408, 12 of 64 experts, T = 8:
+  // 57.8 -> 54.4, T = 16: 57.2 -> 53.5; 4096 x 2048, 16 experts, T = 16: 161 -> 152; two-matrix, 2048 x 14336, T = 8: 201 -> 183;
+  // two (gate/up): 256 x 6784, 32 of 64, T = 7: 110 -> 83; 512 x 2944, 32 experts, T = 6: 78 -> 68; 768 x 6144, 37 of 64, T = 2: 109 ->
+  // 97.  Two units of two matrices lose where blocks are few (1024 x 4096, 6 of 16, T = 8:
+  // 40.5 -> 43.0; 32 of 64 experts of 1024 x 6272: 91 -> 85), four more so (2048 x 4096, 16 experts, T = 12: 159 -> 176).  One
+  // matrix up to K = 4096: 159 -> 164; one token on 1024 x 4096: 18.2 -> 21.5; two-matrix 3072 x 3072, T = 8: 71 -> 65.  With
+  // more token rows there are too few registers.  Blocks that have rows have to be left for every unit twice (11 tokens on 2
+  // experts of 512 x 1024: 10.5 -> 11.5; one token, k = 1, 16 experts of 1376 x 1296: 9.6 -> 11.0), unless there are many
+  // without (64 experts of 1024 x 1408, 3 tokens: 26 -> 16).
+  const int blocks = (a.N + 2 * WROWS - 1) / (2 * WROWS);
+  if (T <= 16 && a.K <= (MODE == SK_UP ? 768 : 2048) &&
+      (blocks * std::min(a.n_list, a.S) >= 2 * n_cu || blocks * a.n_list >= 8 * n_cu)) {
+    const dim3 grid(blocks, a.n_list);
+    hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 2>), grid, dim3(NT), 0, s, a);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+  }
   const dim3 grid((a.N + WROWS - 1) / WROWS, a.n_list);
   hipLaunchKernelGGL((ffn_skinny_kernel<MODE, 1>), grid, dim3(NT), 0, s, a);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
@@ -304,7 +309,7 @@ int launch_ffn_skinny(moe_ctx* c, bool gated, const int32_t* counts, const int32
     a.Us = (uint16_t*)U;
     a.K = c->cfg.d;
     a.N = c->cfg.f;
-    const int st = gated ? launch<SK_UP>(a, c->S_call / c->cfg.k, s) : launch<SK_UP1>(a, c->S_call / c->cfg.k, s);
+    const int st = gated ? launch<SK_UP>(a, c->S_call / c->cfg.k, c->n_cu, s) : launch<SK_UP1>(a, c->S_call / c->cfg.k, c->n_cu, s);
     if (st != MOE_OK) return st;
   }
   prof_mark(c, 2, s);
@@ -316,7 +321,7 @@ int launch_ffn_skinny(moe_ctx* c, bool gated, const int32_t* counts, const int32
     a.Gs = a.Us = nullptr;
     a.K = c->cfg.f;
     a.N = c->cfg.d;
-    const int st = launch<SK_DOWN>(a, c->S_call / c->cfg.k, s);
+    const int st = launch<SK_DOWN>(a, c->S_call / c->cfg.k, c->n_cu, s);
     if (st != MOE_OK) return st;
   }
   prof_mark(c, 3, s);

@@ -31,12 +31,13 @@ def test_given_rows_match_oracle(d, f, rows, gated, tile):
     _check_given_rows(d, f, rows, gated, tile)
 
 
-# The kernel for few rows takes 32 weight rows of a single matrix a block in calls of at most 16 tokens and contractions
-# of at most 2048 (the first GEMM here, the second, both, neither); counts may hold more rows of an expert than there
-# are tokens.
+# The kernel for few rows takes 32 weight rows a block in calls of at most 16 tokens and contractions of at most 2048,
+# of two matrices 768, where there are blocks enough (the first GEMM here, the second, both, neither); counts may hold
+# more rows of an expert than there are tokens.
 @pytest.mark.parametrize("gated", [True, False])
 @pytest.mark.parametrize("d,f,rows", [
     (2048, 2056, [16, 0, 1, 9]), (2056, 2048, [20, 3, 0, 9]), (520, 40, [17, 15]), (2056, 2064, [32, 0]),
+    (768, 4104, [16, 0, 1, 9]), (776, 2048, [3, 20, 0, 9]), (4104, 2048, [5, 4, 3, 20]),
 ])
 def test_few_rows_match_oracle(d, f, rows, gated):
     _check_given_rows(d, f, rows, gated, 16)
