@@ -247,15 +247,16 @@ int launch(const SkinnyArgs& a, int T, int n_cu, hipStream_t s) {
 // for them a longer row means more k-steps in a row: where they would take the layer, the rows are held to 48 KB
 // per element of d (98 MB up to d = 2048).  128-row tiles -> this kernel, us, all tokens on the same experts |
 // on the resident ones evenly | on all evenly:
-//   1024 x 4096, E = 16, k = 2, 6 resident: T = 8: 29 -> 20 | 44 -> 40 | 45 -> 40, 32 (67 MB): 29 -> 27 | 45 -> 46 |
-//   45 -> 42, 48 (101 MB): 33 -> 35 | 45 -> 49 | 45 -> 43, 64: 33 -> 38 | 45 -> 57 | 46 -> 45; 4 resident,
-//   T = 64 (134 MB): 34 -> 40 | 34 -> 41 | 35 -> 31
-//   2048 x 1408, E = 64, k = 6, 12 resident: T = 8: 42 -> 36 | 58 -> 58 | 60 -> 57, 16 (69 MB): 42 -> 41 | 58 -> 61 |
-//   58 -> 58, 24 (104 MB): 42 -> 49 | 58 -> 64 | 58 -> 58, 32: 42 -> 49 | 59 -> 68 | 58 -> 57
-//   4096 x 2048, E = 16, k = 2, 16 resident: T = 16: 59 -> 36 | 185 -> 165, 32 (134 MB): 59 -> 41 | 166 -> 166
-//   4096 x 14336, E = 8, k = 2, 8 resident: T = 1: 131 -> 139, 2: 139 -> 139 | 268 -> 250, 4: 139 -> 146 | 476 -> 473
-//   two-matrix: 2048 x 14336, T = 8 (117 MB): 51 -> 62 | 182 -> 196; 768 x 2048, T = 64: 26 -> 20 | 24 -> 17;
-//   3072 x 3072, k = 6, T = 8 (113 MB): 69 -> 69 | 79 -> 79
+//   1024 x 4096, E = 16, k = 2, 6 resident: T = 8: 29 -> 20 | 39 -> 40 | 39 -> 40, 32 (67 MB): 29 -> 28 | 40 -> 46 |
+//   39 -> 41, 48 (101 MB): 35 -> 36 | 40 -> 50 | 40 -> 42, 64: 35 -> 40 | 41 -> 57 | 40 -> 44; 4 resident,
+//   T = 64 (134 MB): 35 -> 42 | 33 -> 41 | 32 -> 30
+//   2048 x 1408, E = 64, k = 6, 12 resident: T = 8: 38 -> 36 | 50 -> 54 | 53 -> 53, 16 (69 MB): 37 -> 39 | 50 -> 56 |
+//   50 -> 53, 24 (104 MB): 37 -> 49 | 51 -> 64 | 50 -> 58, 32: 37 -> 51 | 51 -> 68 | 50 -> 58
+//   two-matrix: 768 x 2048, T = 64: 29 -> 21 | 26 -> 19 | 25 -> 16; 2048 x 14336, T = 8 (117 MB): 58 -> 61 | 166 -> 178;
+//   3072 x 3072, k = 6, T = 8 (113 MB): 53 -> 66 | 67 -> 77 | 67 -> 68
+// Many weights, which the 128-row tiles copy past the last-level cache, take these longer: 4096 x 2048, E = 16, k = 2, 16
+// resident: T = 16: 34 -> 28 | 134 -> 151; 4096 x 14336, E = 8, k = 2, 8 resident: T = 1: 126 -> 135, 4: 130 -> 144 | 438 -> 468.
+// That is less than where few are read (one token on 1024 x 4096: 29 -> 19), and is left.
 static bool few_rows(long long T, int d, int f, int E, int k, int n_res, bool gated, int n_cu) {
   const int bn = gated ? 128 : 256;
   const bool fills = (long long)n_res * ((f + bn - 1) / bn) >= n_cu;

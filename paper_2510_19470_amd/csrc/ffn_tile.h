@@ -261,79 +261,4 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& p, const f32x16 (&
   }
 }
 
-// ---- Contractions that are cut into parts.  The blocks add the parts of a tile themselves, as a tree over
-// neighbours (0 + 1) + (2 + 3) ...: of two neighbours the one that is done first publishes its sum and ends, the
-// other adds it to its own registers and goes on to the next level.  Nobody waits for anybody, so the blocks
-// need not be resident together, and the result does not depend on who comes first (a + b is b + a).
-// The sums and the counters are written and read with device-scope relaxed atomics, which go past the L2 of an
-// XCD to what all XCDs share; a sum is complete there (vmcnt 0 in every wavefront, then the barrier) before its
-// counter says so.
-constexpr int JOIN_PARTS = 8;      // parts of a tile at most
-constexpr int JOIN_COUNTERS = 8;   // of a tile: 4 + 2 + 1 pairs; zero between launches
-
-typedef unsigned long long join_word;
-__device__ __forceinline__ int join_get(int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// Called by all THREADS threads of a block, each with its own 32 NI accumulators.  slots: one partial tile of
-// 32 NI x THREADS floats for every part; n_act: 32-row blocks of this wavefront that hold rows (the same in
-// every part); flag: JOIN_COUNTERS integers of LDS.  True: the accumulators hold the whole sum.
-template <int NI, int THREADS>
-__device__ __forceinline__ bool join_parts(f32x16 (&acc)[2][NI], float* slots, int32_t* counters, int part, int parts,
-                                           int n_act, int32_t* flag) {
-  const int tid = threadIdx.x;
-  int node = part, width = parts, first = 0;
-  for (int level = 0; width > 1; ++level) {
-    if ((node ^ 1) < width) {
-      int32_t* count = counters + first + (node >> 1);
-      if (tid == 0) flag[2 * level] = join_get(count);
-      __syncthreads();
-      if (__builtin_amdgcn_readfirstlane(flag[2 * level]) == 0) {   // the neighbour is not there yet: publish
-        join_word* mine = reinterpret_cast<join_word*>(slots + (size_t)(node << level) * (32 * NI * THREADS)) + tid;
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-          if (i < n_act)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int q = 0; q < 8; ++q) {
-                const float2 v = make_float2(acc[j][i][2 * q], acc[j][i][2 * q + 1]);
-                __hip_atomic_store(mine + ((i * 2 + j) * 8 + q) * THREADS, __builtin_bit_cast(join_word, v),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0)
-          flag[2 * level + 1] = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(flag[2 * level + 1]) == 0) return false;   // the neighbour goes on with it
-      }
-      if (tid == 0) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      join_word* theirs = reinterpret_cast<join_word*>(slots + (size_t)((node ^ 1) << level) * (32 * NI * THREADS)) + tid;
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-        if (i < n_act) {
-          join_word v[2][8];
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-              v[j][q] = __hip_atomic_load(theirs + ((i * 2 + j) * 8 + q) * THREADS, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              const float2 t = __builtin_bit_cast(float2, v[j][q]);
-              acc[j][i][2 * q] += t.x;
-              acc[j][i][2 * q + 1] += t.y;
-            }
-        }
-    }
-    first += (width + 1) >> 1;
-    node >>= 1;
-    width = (width + 1) >> 1;
-  }
-  return true;
-}
-
 }  // namespace

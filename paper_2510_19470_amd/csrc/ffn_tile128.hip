@@ -26,7 +26,7 @@ constexpr int TN = 128;          // weight rows per tile (gate/up: 64 of each ma
 constexpr int NT = 256;          // threads
 constexpr int OPERAND = TM * BK * 2;      // bytes of an operand's part of a stage
 constexpr int STAGE = 2 * OPERAND;
-constexpr int SPLIT_MAX = JOIN_PARTS;
+constexpr int SPLIT_MAX = 8;     // parts of a contraction at most
 constexpr int SPLIT_STEPS = 4;   // k-steps of a part at least
 constexpr int ORDER_GROUP_M = 8; // row blocks per group of the tile order
 
@@ -115,6 +115,79 @@ __host__ __device__ inline int parts_of(int tiles, int slots, int kt, bool one_b
     return parts;
   };
   return best(best(SPLIT_MAX, 1.f), one_block ? 2.3f : 1.8f);   // no more than of one tile alone: the workspace is sized for those
+}
+
+// ---- Contractions that are cut into parts.  The blocks add the parts of a tile themselves, as a tree over
+// neighbours (0 + 1) + (2 + 3) ...: of two neighbours the one that is done first publishes its sum and ends, the
+// other adds it to its own registers and goes on to the next level.  Nobody waits for anybody, so the blocks
+// need not be resident together, and the result does not depend on who comes first (a + b is b + a).
+// The sums and the counters are written and read with device-scope relaxed atomics, which go past the L2 of an
+// XCD to what all XCDs share; a sum is complete there (vmcnt 0 in every wavefront, then the barrier) before its
+// counter says so.
+constexpr int JOIN_COUNTERS = SPLIT_MAX;   // of a tile: 4 + 2 + 1 pairs; zero between launches
+
+typedef unsigned long long join_word;
+__device__ __forceinline__ int join_get(int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Called by all threads of a block, each with its own 64 accumulators.  slots: one partial tile for every part;
+// n_act: 32-row blocks of this wavefront that hold rows (the same in every part); flag: JOIN_COUNTERS integers of
+// LDS.  True: the accumulators hold the whole sum.
+__device__ __forceinline__ bool join_parts(f32x16 (&acc)[2][2], float* slots, int32_t* counters, int part, int parts,
+                                           int n_act, int32_t* flag) {
+  const int tid = threadIdx.x;
+  int node = part, width = parts, first = 0;
+  for (int level = 0; width > 1; ++level) {
+    if ((node ^ 1) < width) {
+      int32_t* count = counters + first + (node >> 1);
+      if (tid == 0) flag[2 * level] = join_get(count);
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(flag[2 * level]) == 0) {   // the neighbour is not there yet: publish
+        join_word* mine = reinterpret_cast<join_word*>(slots + (size_t)(node << level) * (TM * TN)) + tid;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (i < n_act)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int q = 0; q < 8; ++q) {
+                const float2 v = make_float2(acc[j][i][2 * q], acc[j][i][2 * q + 1]);
+                __hip_atomic_store(mine + ((i * 2 + j) * 8 + q) * NT, __builtin_bit_cast(join_word, v),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0)
+          flag[2 * level + 1] = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(flag[2 * level + 1]) == 0) return false;   // the neighbour goes on with it
+      }
+      if (tid == 0) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      join_word* theirs = reinterpret_cast<join_word*>(slots + (size_t)((node ^ 1) << level) * (TM * TN)) + tid;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (i < n_act) {
+          join_word v[2][8];
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              v[j][q] = __hip_atomic_load(theirs + ((i * 2 + j) * 8 + q) * NT, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              const float2 t = __builtin_bit_cast(float2, v[j][q]);
+              acc[j][i][2 * q] += t.x;
+              acc[j][i][2 * q + 1] += t.y;
+            }
+        }
+    }
+    first += (width + 1) >> 1;
+    node >>= 1;
+    width = (width + 1) >> 1;
+  }
+  return true;
 }
 
 // One tile, or one part of its contraction (all fields wave-uniform).
@@ -349,7 +422,7 @@ __global__ __launch_bounds__(NT, 2) void ffn_tile128_kernel(const TileArgs p) {
     const int na_n = blocks(nxt);
     if (nxt.valid) start(nxt, na_n);
     if (!CUT || cur.parts == 1 ||
-        join_parts<2, NT>(acc, g.split_ws + (size_t)cur.tile * cur.parts * (TM * TN), g.joined + cur.tile * JOIN_COUNTERS,
+        join_parts(acc, g.split_ws + (size_t)cur.tile * cur.parts * (TM * TN), g.joined + cur.tile * JOIN_COUNTERS,
                           cur.part, cur.parts, mine, join_flag))
       tile_epilogue<MODE, true, 2>(g, acc, cur.row0, cur.rows, cur.nblk, wm, wn, lane);
     if (!nxt.valid) break;
@@ -410,7 +483,7 @@ void launch(const moe_ctx* c, const TileArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// (two parts at least, on at most `slots` blocks; the 256-row tiles have half as many blocks)
+// (two parts at least, on at most `slots` blocks)
 size_t ffn_join_counters(const moe_ctx* c) { return (size_t)slots(c) / 2 * JOIN_COUNTERS; }
 
 size_t ffn_tile128_split_floats(const moe_ctx* c) {
@@ -506,7 +579,7 @@ static void tile_us(int experts, int rows, int d, int f, bool gated, bool backwa
 // tokens on the same experts (more rows on fewer experts: more and fuller tiles) cost them no more than twice
 // what they gain there.  Besides, they are held to calls whose first GEMM has at most two rounds of larger tiles with
 // any routing or, forward, at most one row block per expert; backward, one round with an even routing.  Of 287
-// measured calls that these lines admit the choice is the slower one by more than 3 % in 23 with an even routing (by 1 %
+// measured calls that these lines admit the choice is the slower one by more than 3 % in 21 with an even routing (by 1 %
 // in the mean), 1 % in the mean with popularity falling off as rank^-1.2 or all tokens on the same experts.  Both GEMMs
 // with sums and schedule, larger tiles (backward: dH by turn) -> smaller ones, us: even routing; rank^-1.2; all
 // tokens on the same experts (T, d, f, E, k, resident):

@@ -156,7 +156,8 @@ int moe_create(moe_ctx** out, const moe_config* cfg) {
                        cut(&c->d_rt_hist, rt ? (size_t)n_blk * E : 0)};
   const Cut zero[] = {cut(&c->d_totals, 2 * MOE_MAX_EXPERTS + 2),
                       cut(&c->d_wtab, MOE_WTAB_ROWS * MOE_MAX_EXPERTS),
-                      cut(&c->d_zero, 512), cut(&c->d_joined, mfma ? ffn_join_counters(c) : 0), cut(&c->d_rt_super, rt ? n_sup : 0)};
+                      cut(&c->d_zero, 512), cut(&c->d_joined, mfma ? ffn_join_counters(c) : 0),
+                      cut(&c->d_rt_super, rt ? n_sup : 0)};
   // (what ran before on the null stream is over when moe_set_placement's copies below are)
   bool ok = carve(&c->d_fixed, plain, sizeof(plain) / sizeof(plain[0]), false) &&
             carve(&c->d_fixed_zero, zero, sizeof(zero) / sizeof(zero[0]), true);

@@ -41,7 +41,7 @@
 // What bounds it, n = 14336 x 4096 bf16: the pass over both matrices (235 MB).  Encode 157 -> 95 us
 // against the version that streamed both matrices twice (histogram, then list) and picked bins in
 // one-block launches (matrices not in the last-level cache); of it the pass takes 58 us (4.1 TB/s; 46 us
-// with non-temporal loads, see sr_once), the five short launches 4.6-12 us each.  Half of the pass is
+// with the expert past the cache, see sr_once), the five short launches 4.6-12 us each.  Half of the pass is
 // vector instructions (selecting the residual by a tree of moves instead of one comparison per word
 // made it 80 us, reading it again from memory 64; two chunks ahead instead of one: no faster).  Decode
 // 60 -> 46 us (5.1 TB/s): the shared expert is requested before the search, 1 KB per load instruction,
@@ -893,7 +893,7 @@ __global__ __launch_bounds__(SR_THREADS) void sr_decode_kernel(
   }
 }
 
-// From two matrices of 64 MB on, the expert's is read past the last-level cache (256 MB) and the rebuilt one written
+// From two matrices of 32 MB on, the expert's is read past the last-level cache (256 MB) and the rebuilt one written
 // past it; the shared one, which the next expert's encode or decode reads again, is not.  Plain -> all three past the
 // cache -> this, us:
 //   one of eight experts encoded in a row, 42, 64, 117 MB a matrix: 47.0, 58.0, 77.5 -> 47.7, 59.2, 81.1 -> 46.1, 56.7, 76.0;

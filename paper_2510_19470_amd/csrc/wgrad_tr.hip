@@ -72,8 +72,10 @@ struct WgradArgs {
 // the rows 8g + 4(lane >> 5) + {0..3} of each 32-row block.  The gradients are the call's largest array, and the
 // dX GEMM after this launch reads the weights and [dG|dU]: stores past the last-level cache leave those in it
 // (training step, us: 6190 rows, 2048 x 2048, 302 MB of gradients: 782 -> 768; two-matrix, 64 rows per expert of
-// 1024 x 4096, 268 MB: 197 -> 190; 2048 tokens, 1024 x 1024, 75 MB: 174 -> 171).  Only where the 32 columns of a store are
-// a 128-byte line: pieces of lines lose (1160 x 2888: 291 -> 296; 648 x 1400: 243 -> 248).
+// 1024 x 4096, 268 MB: 197 -> 190; 2048 tokens, 1024 x 1024, 75 MB: 174 -> 171).  With an update of fp32 weights that reads
+// them right after it, backward and update, us: 25 MB: 66 -> 66; 50 MB: 83 -> 84; 75 MB: 117 -> 115; 151 MB: 192 -> 186, 317 -> 312;
+// 268 MB: 243 -> 238; 302 MB: 523 -> 505; 415 MB: 507 -> 475.  Only where the 32 columns of a store are a 128-byte line:
+// pieces of lines lose (1160 x 2888: 291 -> 296; 648 x 1400: 243 -> 248).
 template <bool RAG, bool LINES, int NI = 4, int NJ = 2>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[2][4], float* dW, int m0, int n0, int Mo, int No,
                                            int lane) {
@@ -416,22 +418,16 @@ int launch_wgrad_tr(moe_ctx* c, bool gated, const void* dy, const void* xp, cons
   for (int i = 0; i < a.n_list; ++i)
     for (int w = 3; w < 6; ++w) lines &= ((uintptr_t)c->h_wtab[w][a.list[i]] & 127) == 0;
   const bool rag = d % 256 != 0 || f % 256 != 0 || !lines;
-  // By the rows per expert of an even routing.  The two cross between 96 and 512 of them, later on whole sizes
-  // and earlier where popularity falls off as rank^-1.2; up to the line the kernel for few rows gains up to 6 %
-  // of the whole backward and loses up to 1 %.  Backward, us, many -> few at 64, 128, 192, 256 rows; even, and
-  // rank^-1.2:
-  //   2048 x 2048, 6 of 32 experts: 171 -> 162, 191 -> 182, 214 -> 206, 234 -> 228; 223 -> 214, 265 -> 258,
-  //   305 -> 301, 336 -> 331
-  //   two-matrix 1024 x 4096, 8 of 32: 138 -> 130, 151 -> 146, 170 -> 164, 185 -> 182; 175 -> 171, 206 -> 204,
-  //   282 -> 287, 317 -> 326
-  //   1160 x 2888, 6 of 16: 159 -> 158, 187 -> 185, 213 -> 215, 239 -> 241; 200 -> 201, 237 -> 238, 268 -> 270,
-  //   293 -> 294
-  //   2048 x 1408, 12 of 64: 212 -> 207, 237 -> 233, 262 -> 261, 286 -> 288; 277 -> 278, 327 -> 326, 408 -> 415,
-  //   551 -> 557
-  // With whole lines to store that kernel gains by its stores too: on whole tiles and at least three rounds of the
-  // larger ones (fewer are one round more in the smaller ones), many -> few at 512 rows, step, even routing: 2048 x 2048,
-  // 6 experts: 524 -> 514; 1536 x 2048: 400 -> 391; popularity rank^-1, 2048 x 2048: 1094 -> 1103.  At 1024 rows: 774
-  // -> 772; 288 tiles of 1024 x 1024, 256 rows: 158 -> 161; 2048 x 1408, 256 rows: 264 -> 273.
+  // By the rows per expert of an even routing.  On sizes that are no multiples of 256 the two differ by 2 % up to 128
+  // rows and the kernel for few rows loses beyond; with whole lines to store and at least three rounds of the larger
+  // tiles (fewer are one round more in the smaller ones) it gains up to 512 and loses 2 % there where popularity falls
+  // off as rank^-1.2.  Backward, us, many -> few at 64, 128, 256, 512 rows; even, and rank^-1.2:
+  //   2048 x 2048, 6 of 32 experts: 150 -> 145, 173 -> 163, 232 -> 219, 277 -> 267; 214 -> 204, 264 -> 254, 364 -> 356, 645 -> 648
+  //   two-matrix 1024 x 4096, 8 of 32: 119 -> 115, 137 -> 129, 189 -> 180, 233 -> 225; 159 -> 150, 205 -> 192, 323 -> 322,
+  //   517 -> 530
+  //   1160 x 2888, 6 of 16: 161 -> 162, 190 -> 190, 248 -> 252, 304 -> 313; 214 -> 217, 240 -> 243, 301 -> 306, 458 -> 474
+  //   2048 x 1408, 12 of 64: 182 -> 180, 206 -> 206, 269 -> 269, 333 -> 336; 263 -> 266, 333 -> 339, 584 -> 607, 1025 -> 1067
+  // 2048 x 2048 at 1024 rows, step: 774 -> 772; 288 tiles of 1024 x 1024, 256 rows: 158 -> 161.
   const int tiles256 = a.n_jobs * a.n_list * ((d + 255) / 256) * ((f + 255) / 256);
   const int line = !rag && tiles256 >= 3 * c->n_cu ? 512 : 128;
   const bool few = c->wgrad_rows != 0 ? c->wgrad_rows == 128 : c->S_call <= line * E;
