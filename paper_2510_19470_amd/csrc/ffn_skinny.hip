@@ -254,9 +254,9 @@ int launch(const SkinnyArgs& a, int T, int n_cu, hipStream_t s) {
 //   50 -> 53, 24 (104 MB): 37 -> 49 | 51 -> 64 | 50 -> 58, 32: 37 -> 51 | 51 -> 68 | 50 -> 58
 //   two-matrix: 768 x 2048, T = 64: 29 -> 21 | 26 -> 19 | 25 -> 16; 2048 x 14336, T = 8 (117 MB): 58 -> 61 | 166 -> 178;
 //   3072 x 3072, k = 6, T = 8 (113 MB): 53 -> 66 | 67 -> 77 | 67 -> 68
-// Many weights, which the 128-row tiles copy past the last-level cache, take these longer: 4096 x 2048, E = 16, k = 2, 16
-// resident: T = 16: 34 -> 28 | 134 -> 151; 4096 x 14336, E = 8, k = 2, 8 resident: T = 1: 126 -> 135, 4: 130 -> 144 | 438 -> 468.
-// That is less than where few are read (one token on 1024 x 4096: 29 -> 19), and is left.
+// Many weights, which the 128-row tiles copy past the last-level cache and whose parts they join, they read faster now:
+// 2048 x 4096, E = 16, k = 2, 16 resident, T = 12: 34 -> 35 | 125 -> 159; 4096 x 2048, T = 16: 34 -> 28 | 134 -> 151; 4096 x 14336,
+// E = 8, k = 2, 8 resident: T = 1: 126 -> 135, 4: 130 -> 144 | 438 -> 468.  The line is from before that and has not been moved.
 static bool few_rows(long long T, int d, int f, int E, int k, int n_res, bool gated, int n_cu) {
   const int bn = gated ? 128 : 256;
   const bool fills = (long long)n_res * ((f + bn - 1) / bn) >= n_cu;

@@ -40,7 +40,7 @@
 //
 // What bounds it, n = 14336 x 4096 bf16: the pass over both matrices (235 MB).  Encode 157 -> 95 us
 // against the version that streamed both matrices twice (histogram, then list) and picked bins in
-// one-block launches (matrices not in the last-level cache); of it the pass takes 58 us (4.1 TB/s; 46 us
+// one-block launches (matrices not in the last-level cache); of it the pass takes 58 us (4.1 TB/s; 51 us
 // with the expert past the cache, see sr_once), the five short launches 4.6-12 us each.  Half of the pass is
 // vector instructions (selecting the residual by a tree of moves instead of one comparison per word
 // made it 80 us, reading it again from memory 64; two chunks ahead instead of one: no faster).  Decode
